@@ -34,7 +34,7 @@
 //     to workgroup ids so that each XCD owns one contiguous range of tiles,
 //     ordered in groups of 8 M-tiles so concurrently running tiles share A and
 //     W panels in that XCD's L2.
-// fp32 path: VALU tiles (64x64, 4x4 per thread) with the same epilogue.
+// fp32 path: fp32 MFMA tiles (64 x 64, or 32 x 32 with K split over the waves) with the same epilogue.
 #include <atomic>
 #include <type_traits>
 
@@ -821,66 +821,228 @@ static hipError_t dispatch_bf16(const GemmPair& pr, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 VALU GEMM (64x64 tile, 16-deep k slices, 4x4 outputs per thread)
+// fp32 GEMM on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums).
+// As in the bf16 path, MFMA operand "A" = rows of W, "B" = rows of A, so a lane owns one output row m
+// and runs of 4 consecutive features n. A lane reads 4 consecutive k of its row with one ds_read_b128
+// and gives element j to the j-th of four MFMAs; lane group g = lane / 16 then supplies k = 4 g + j of
+// both operands, which is a permutation of the 16 k the four instructions sum over. LDS rows are 32
+// floats = 8 chunks of 16 bytes, swizzled like the bf16 tiles (the reads have the same pattern).
+// Operands go straight to LDS (buffer loads with the LDS bit) from a 64-bit base per tile with the
+// offsets relative to the tile's first row; rows past the end repeat the last row and are not stored.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void mfma_k16(float4 w, float4 a, f32x4& c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, a.x, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, a.y, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, a.z, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, a.w, c, 0, 0, 0);
+}
+
+// buffer descriptor of a tile's operand rows, starting at the tile's first row
+__device__ __forceinline__ u32x4_t tile_rsrc(const float* p) {
+  const uint64_t u = (uint64_t)p;
+  return u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(u >> 32) & 0xffffu)), 0x7fffffffu, 0x00020000u};
+}
+
+// 64 x 64 tile, 4 waves of 32 x 32, 32-deep k-tiles in a ring of three LDS stages (48 KB, three
+// workgroups per CU), one barrier per k-tile. Bound by the fp32 matrix rate (256 flop per clock and
+// CU): a k-tile takes 1024 cycles of it and moves 16 KB.
 template <int EPI>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmPair pr, int tiles0, int total_tiles) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float sa[BK][BM + 4];
-  __shared__ float sw[BK][BN + 4];
-  int t = blockIdx.x;
+  constexpr int BM = 64, BN = 64, ST = 3, STAGE = (BM + BN) * 128;
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ __attribute__((aligned(1024))) char smem[ST * STAGE];
+  const int per = gridDim.x >> 3;
+  const int t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);   // XCD-aware, as in the bf16 kernel
   if (t >= total_tiles) return;
-  int pi = t < tiles0 ? 0 : 1;
-  const GemmProblem& P = pr.p[pi];
-  int tl = pi == 0 ? t : t - tiles0;
-  int nt = cdiv(P.N, BN);
-  int m0 = (tl / nt) * BM, n0 = (tl % nt) * BN;
-  const float* A = (const float*)P.A;
-  const float* W = (const float*)P.W;
-  int tid = threadIdx.x;
-  int tr = tid / 16, tc = tid % 16;   // 16 x 16 threads, each 4 rows x 4 consecutive n
-  float acc[4][4] = {};
-  // loader: 64 rows x 16 k per operand = 1024 values, 4 per thread
-  int lr = tid / 4, lk = (tid % 4) * 4;
-  int64_t arow = m0 + lr < P.M ? row_offset(P.amap, m0 + lr) : -1;
-  int64_t wrow = n0 + lr < P.N ? (int64_t)(n0 + lr) * P.K : -1;
-  for (int k0 = 0; k0 < P.K; k0 += BK) {
+  const int pi = t < tiles0 ? 0 : 1;
+  const GemmProblem P = pr.p[pi];
+  int tm, tn;
+  tile_coords(pi == 0 ? t : t - tiles0, cdiv(P.M, BM), cdiv(P.N, BN), tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int64_t a0 = row_offset(P.amap, m0);
+  const u32x4_t ra = tile_rsrc((const float*)P.A + a0);
+  const u32x4_t rw = tile_rsrc((const float*)P.W + (int64_t)n0 * P.K);
+  // a wave load fills 8 rows: lane -> row lane / 8, slot lane % 8, which holds chunk slot ^ swz(row)
+  uint32_t aoff[2], woff[2];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-      int k = k0 + lk + q;
-      sa[lk + q][lr] = (arow >= 0 && k < P.K) ? A[arow + k] : 0.f;
-      sw[lk + q][lr] = (wrow >= 0 && k < P.K) ? W[wrow + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; k++) {
-      float a[4], w[4];
-#pragma unroll
-      for (int q = 0; q < 4; q++) a[q] = sa[k][tr * 4 + q];
-#pragma unroll
-      for (int q = 0; q < 4; q++) w[q] = sw[k][tc * 4 + q];
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int i = 0; i < 2; i++) {
+    const int r = 8 * (wave * 2 + i) + (lane >> 3);
+    const uint32_t chunk = ((lane & 7) ^ swz(r)) * 16;
+    aoff[i] = (uint32_t)((row_offset(P.amap, min(m0 + r, P.M - 1)) - a0) * 4) + chunk;
+    woff[i] = (uint32_t)(min(n0 + r, P.N - 1) - n0) * (uint32_t)P.K * 4u + chunk;
   }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  auto issue = [&](int kt, int st) {
+    const uint32_t base = lds0 + st * STAGE + wave_s * 2048;
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      dma_b128(ra, base + i * 1024, aoff[i], kt * 128);
+      dma_b128(rw, base + BM * 128 + i * 1024, woff[i], kt * 128);
+    }
+  };
+  const int wm = wave >> 1, wn = wave & 1, r16 = lane & 15, kq = lane >> 4;
+  f32x4 acc[2][2] = {};
+  const int nk = P.K / 32;
+  issue(0, 0);
+  if (nk > 1) issue(1, 1);
+  int st = 0;
+  for (int kt = 0; kt < nk; kt++) {
+    // tile kt has landed (the 4 loads of tile kt + 1 may be in flight) in every wave, and every wave is
+    // done reading tile kt - 1, whose stage takes tile kt + 2
+    if (kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0f74);
+    else __builtin_amdgcn_s_waitcnt(0x0f70);
+    __syncthreads();
+    if (kt + 2 < nk) issue(kt + 2, st == 0 ? 2 : st - 1);
+    const char* sa = smem + st * STAGE;
+    const char* sw = sa + BM * 128;
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+      float4 fw[2], fa[2];
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        const int rw_ = 32 * wn + 16 * i + r16, ra_ = 32 * wm + 16 * i + r16;
+        fw[i] = *(const float4*)(sw + rw_ * 128 + (((4 * s + kq) ^ swz(rw_)) << 4));
+        fa[i] = *(const float4*)(sa + ra_ * 128 + (((4 * s + kq) ^ swz(ra_)) << 4));
+      }
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) mfma_k16(fw[i], fa[j], acc[i][j]);
+    }
+    st = st == 2 ? 0 : st + 1;
+  }
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const int m = m0 + 32 * wm + 16 * j + r16;
+    if (m >= P.M) continue;
+    const RowEpi R = row_epi(P, m);
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      const int n = n0 + 32 * wn + 16 * i + 4 * kq;
+      float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+      if (n < P.N) epilogue4<EPI, float, float>(P, R, n, v);
+    }
+  }
+#endif
+}
+
+// 32 x 32 tile for problems with too few 64 x 64 tiles: the 4 waves of a workgroup take every 4th
+// 32-deep k slice of the same tile, each with two LDS stages of its own (64 KB in all), so no barrier
+// stands in the k loop and two slices of every wave are in flight; the four partial tiles meet in LDS
+// and are summed in a fixed order. A quarter of the serial chain of the 64 x 64 kernel per tile, at
+// twice its operand bytes per flop.
+template <int EPI>
+__global__ void __launch_bounds__(256) gemm_f32_ksplit_kernel(GemmPair pr, int tiles0, int total_tiles) {
+  constexpr int BM = 32, BN = 32, STAGE = (BM + BN) * 128;
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ __attribute__((aligned(1024))) char smem[4 * 2 * STAGE];
+  const int per = gridDim.x >> 3;
+  const int t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (t >= total_tiles) return;
+  const int pi = t < tiles0 ? 0 : 1;
+  const GemmProblem P = pr.p[pi];
+  int tm, tn;
+  tile_coords(pi == 0 ? t : t - tiles0, cdiv(P.M, BM), cdiv(P.N, BN), tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int64_t a0 = row_offset(P.amap, m0);
+  const u32x4_t ra = tile_rsrc((const float*)P.A + a0);
+  const u32x4_t rw = tile_rsrc((const float*)P.W + (int64_t)n0 * P.K);
+  uint32_t aoff[4], woff[4];
 #pragma unroll
   for (int i = 0; i < 4; i++) {
-    int m = m0 + tr * 4 + i, n = n0 + tc * 4;
-    if (m < P.M && n < P.N) epilogue4<EPI, float, float>(P, row_epi(P, m), n, acc[i]);
+    const int r = 8 * i + (lane >> 3);
+    const uint32_t chunk = ((lane & 7) ^ swz(r)) * 16;
+    aoff[i] = (uint32_t)((row_offset(P.amap, min(m0 + r, P.M - 1)) - a0) * 4) + chunk;
+    woff[i] = (uint32_t)(min(n0 + r, P.N - 1) - n0) * (uint32_t)P.K * 4u + chunk;
   }
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem + wave_s * 2 * STAGE;
+  auto issue = [&](int slice, int st) {
+    const uint32_t base = lds0 + st * STAGE;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      dma_b128(ra, base + i * 1024, aoff[i], slice * 128);
+      dma_b128(rw, base + BM * 128 + i * 1024, woff[i], slice * 128);
+    }
+  };
+  const int r16 = lane & 15, kq = lane >> 4;
+  f32x4 acc[2][2] = {};
+  const int nk = P.K / 32;
+  if (wave_s < nk) issue(wave_s, 0);
+  if (wave_s + 4 < nk) issue(wave_s + 4, 1);
+  int st = 0;
+  for (int kt = wave_s; kt < nk; kt += 4) {
+    // this wave's slice kt has landed (the 8 loads of its next slice may be in flight)
+    if (kt + 4 < nk) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const char* sa = smem + wave_s * 2 * STAGE + st * STAGE;
+    const char* sw = sa + BM * 128;
+    float4 fw[2][2], fa[2][2];
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        const int r = 16 * i + r16;
+        fw[s][i] = *(const float4*)(sw + r * 128 + (((4 * s + kq) ^ swz(r)) << 4));
+        fa[s][i] = *(const float4*)(sa + r * 128 + (((4 * s + kq) ^ swz(r)) << 4));
+      }
+    if (kt + 8 < nk) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the fragments are in registers: the stage is free
+      issue(kt + 8, st);
+    }
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) mfma_k16(fw[s][i], fa[s][j], acc[i][j]);
+    st ^= 1;
+  }
+  __syncthreads();   // every wave's loads have landed and been read
+  f32x4* part = (f32x4*)smem;   // [block][wave][lane]
+#pragma unroll
+  for (int i = 0; i < 2; i++)
+#pragma unroll
+    for (int j = 0; j < 2; j++) part[((2 * i + j) * 4 + wave) * 64 + lane] = acc[i][j];
+  __syncthreads();
+  // wave q finishes block (q / 2, q % 2)
+  f32x4 c = part[(wave * 4) * 64 + lane];
+#pragma unroll
+  for (int g = 1; g < 4; g++) {
+    const f32x4 p = part[(wave * 4 + g) * 64 + lane];
+#pragma unroll
+    for (int r = 0; r < 4; r++) c[r] += p[r];
+  }
+  const int m = m0 + 16 * (wave & 1) + r16, n = n0 + 16 * (wave >> 1) + 4 * kq;
+  if (m < P.M && n < P.N) {
+    float v[4] = {c[0], c[1], c[2], c[3]};
+    epilogue4<EPI, float, float>(P, row_epi(P, m), n, v);
+  }
+#endif
 }
 
 template <int EPI>
 static hipError_t launch_f32(const GemmPair& pr, hipStream_t s) {
-  int tiles[2] = {0, 0};
+  int tiles[2] = {0, 0}, small[2] = {0, 0};
   for (int i = 0; i < pr.nprob; i++)
-    if (pr.p[i].M > 0 && pr.p[i].N > 0) tiles[i] = cdiv(pr.p[i].M, 64) * cdiv(pr.p[i].N, 64);
-  int total = tiles[0] + tiles[1];
+    if (pr.p[i].M > 0 && pr.p[i].N > 0) {
+      tiles[i] = cdiv(pr.p[i].M, 64) * cdiv(pr.p[i].N, 64);
+      small[i] = cdiv(pr.p[i].M, 32) * cdiv(pr.p[i].N, 32);
+    }
+  const int total = tiles[0] + tiles[1], total_small = small[0] + small[1];
   if (total == 0) return hipSuccess;
-  gemm_f32_kernel<EPI><<<total, 256, 0, s>>>(pr, tiles[0], total);
+  // matrix cycles of the fullest CU: a 64 x 64 tile takes 32 per k, a 32 x 32 one 8, and the small
+  // tiles' doubled operand traffic costs them about a quarter
+  const int cus = cu_count();
+  const double big = 32.0 * cdiv(total, cus), little = 1.25 * 8.0 * cdiv(total_small, cus);
+  if (little < big)
+    gemm_f32_ksplit_kernel<EPI><<<8 * cdiv(total_small, 8), 256, 0, s>>>(pr, small[0], total_small);
+  else
+    gemm_f32_kernel<EPI><<<8 * cdiv(total, 8), 256, 0, s>>>(pr, tiles[0], total);
   return hipGetLastError();
 }
 
