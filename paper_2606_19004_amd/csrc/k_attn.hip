@@ -38,7 +38,7 @@
 //   * Workgroups are dispatched round-robin over the 8 XCDs; each XCD gets a
 //     contiguous range of (sample, head, query block) tiles, so the query blocks
 //     of one (sample, head) read its K/V through the same L2.
-// fp32 path: one thread per query, K/V tiles in LDS (small configurations).
+// fp32 path: the same orientation on the fp32 matrix instruction, 64 queries per workgroup.
 #include "internal.h"
 
 namespace dit {
@@ -359,54 +359,124 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_bf16(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 attention: one thread per query, online softmax, K/V tiles in LDS
+// fp32 attention on v_mfma_f32_16x16x4_f32 (fp32 operands, products and sums). A workgroup's 4 waves
+// take 16 queries each of one (sample, head) and share K/V tiles of 32 keys (16 at head_dim 128), staged through registers
+// one tile ahead into two LDS buffers. Scores are computed transposed, S^T = K Q^T, so that a lane owns
+// one query (lane % 16) and keys 16 kb + 4 (lane / 16) + r; P then is operand B of O^T = V^T P^T as it
+// sits in the score registers: MFMA r of a key block sums over keys 4 g + r, g = lane / 16. Online
+// softmax in the exp2 domain, one rescale per tile. LDS rows are padded by 4 floats, which spreads
+// both the 16-byte K reads (16 rows) and the 4-byte V reads (4 rows, 4 apart) over the banks.
+// Bound by the fp32 matrix rate; 4 B H S^2 d flops.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(64) attn_fwd_f32(AttnArgs a) {
-  constexpr int KB = 32;
-  __shared__ float sk[KB][D];
-  __shared__ float sv[KB][D];
+__global__ void __launch_bounds__(256) attn_fwd_f32(AttnArgs a) {
+  constexpr int KB = D == 64 ? 32 : 16, NKB = KB / 16, LD = D + 4, NDB = D / 16, NKC = D / 16;
+  constexpr int CPT = KB * D / 4 / 256;   // 16-byte chunks of K (and of V) each thread stages per tile
+  __shared__ __attribute__((aligned(16))) float sk[2][KB * LD];
+  __shared__ __attribute__((aligned(16))) float sv[2][KB * LD];
   const int b = blockIdx.z, h = blockIdx.y;
-  const int qi = blockIdx.x * 64 + threadIdx.x;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int S = a.S;
   const float* Q = (const float*)a.q + (int64_t)b * a.qs_b + (int64_t)h * a.qs_h;
   const float* Kg = (const float*)a.k + (int64_t)b * a.qs_b + (int64_t)h * a.qs_h;
   const float* Vg = (const float*)a.v + (int64_t)b * a.qs_b + (int64_t)h * a.qs_h;
-  float q[D], acc[D];
-  const float* qrow = Q + (int64_t)min(qi, a.S - 1) * a.qs_s;
+  const int qi = blockIdx.x * 64 + wave * 16 + l16;
+  float4 qf[NKC];   // q[qi][16 c + 4 g + 0..3]
+  {
+    const float* qrow = Q + (int64_t)min(qi, S - 1) * a.qs_s;
 #pragma unroll
-  for (int e = 0; e < D; e++) {
-    q[e] = qrow[e] * a.scale;
-    acc[e] = 0.f;
+    for (int c = 0; c < NKC; c++) qf[c] = *(const float4*)(qrow + 16 * c + 4 * g);
   }
-  float m = -INFINITY, l = 0.f;
-  for (int k0 = 0; k0 < a.S; k0 += KB) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < KB * D; idx += 64) {
-      int key = idx / D, e = idx % D;
-      bool ok = k0 + key < a.S;
-      sk[key][e] = ok ? Kg[(int64_t)(k0 + key) * a.qs_s + e] : 0.f;
-      sv[key][e] = ok ? Vg[(int64_t)(k0 + key) * a.qs_s + e] : 0.f;
-    }
-    __syncthreads();
-    int nkeys = min(KB, a.S - k0);
-    for (int j = 0; j < nkeys; j++) {
-      float s = 0.f;
+  float4 rk[CPT], rv[CPT];
+  auto fetch = [&](int kt) {   // rows past the end repeat the last key; their scores are masked
 #pragma unroll
-      for (int e = 0; e < D; e++) s = fmaf(q[e], sk[j][e], s);
-      float mn = fmaxf(m, s);
-      float al = __expf(m - mn);
-      float p = __expf(s - mn);
-      l = l * al + p;
-#pragma unroll
-      for (int e = 0; e < D; e++) acc[e] = fmaf(acc[e], al, p * sv[j][e]);
-      m = mn;
+    for (int i = 0; i < CPT; i++) {
+      const int idx = tid + 256 * i, row = idx / (D / 4), c = idx % (D / 4);
+      const int64_t off = (int64_t)min(kt * KB + row, S - 1) * a.qs_s + 4 * c;
+      rk[i] = *(const float4*)(Kg + off);
+      rv[i] = *(const float4*)(Vg + off);
     }
+  };
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < CPT; i++) {
+      const int idx = tid + 256 * i, row = idx / (D / 4), c = idx % (D / 4);
+      *(float4*)(&sk[buf][row * LD + 4 * c]) = rk[i];
+      *(float4*)(&sv[buf][row * LD + 4 * c]) = rv[i];
+    }
+  };
+  f32x4 o[NDB];
+#pragma unroll
+  for (int i = 0; i < NDB; i++) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float c2 = a.scale * 1.4426950408889634f;
+  float m_run = -INFINITY, l_run = 0.f;
+  const int nt = cdiv(S, KB);
+  fetch(0);
+  stage(0);
+  for (int kt = 0; kt < nt; kt++) {
+    const int buf = kt & 1;
+    __syncthreads();   // tile kt is staged, and every wave is done with the other buffer
+    if (kt + 1 < nt) fetch(kt + 1);
+    f32x4 s[NKB];
+#pragma unroll
+    for (int kb = 0; kb < NKB; kb++) {
+      s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NKC; c++) {
+        const float4 kf = *(const float4*)(&sk[buf][(16 * kb + l16) * LD + 16 * c + 4 * g]);
+        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.x, qf[c].x, s[kb], 0, 0, 0);
+        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.y, qf[c].y, s[kb], 0, 0, 0);
+        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.z, qf[c].z, s[kb], 0, 0, 0);
+        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.w, qf[c].w, s[kb], 0, 0, 0);
+      }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < NKB; kb++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        s[kb][r] *= c2;
+        if (kt * KB + 16 * kb + 4 * g + r >= S) s[kb][r] = -INFINITY;
+        mx = fmaxf(mx, s[kb][r]);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    m_run = m_new;
+    l_run *= alpha;
+#pragma unroll
+    for (int i = 0; i < NDB; i++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) o[i][r] *= alpha;
+    float psum = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < NKB; kb++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        s[kb][r] = __builtin_amdgcn_exp2f(s[kb][r] - m_new);
+        psum += s[kb][r];
+      }
+    l_run += psum;
+#pragma unroll
+    for (int kb = 0; kb < NKB; kb++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const float* vr = &sv[buf][(16 * kb + 4 * g + r) * LD + l16];
+#pragma unroll
+        for (int i = 0; i < NDB; i++) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[16 * i], s[kb][r], o[i], 0, 0, 0);
+      }
+    if (kt + 1 < nt) stage(buf ^ 1);
   }
-  if (qi < a.S) {
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (qi < S) {
     float* orow = (float*)a.o + (int64_t)b * a.os_b + (int64_t)qi * a.os_s + (int64_t)h * a.os_h;
-    float inv = 1.0f / l;
+    const float inv = 1.0f / l_run;
 #pragma unroll
-    for (int e = 0; e < D; e++) orow[e] = acc[e] * inv;
+    for (int i = 0; i < NDB; i++)   // dims 16 i + 4 g + 0..3 of this lane's query
+      *(float4*)(orow + 16 * i + 4 * g) = make_float4(o[i][0] * inv, o[i][1] * inv, o[i][2] * inv, o[i][3] * inv);
   }
 }
 
@@ -423,8 +493,8 @@ hipError_t attention(const AttnArgs& a, int dtype, hipStream_t s) {
     else attn_fwd_bf16<64><<<grid, 256, 0, s>>>(a);
   } else {
     dim3 grid(cdiv(a.S, 64), a.H, a.B);
-    if (a.d == 128) attn_fwd_f32<128><<<grid, 64, 0, s>>>(a);
-    else attn_fwd_f32<64><<<grid, 64, 0, s>>>(a);
+    if (a.d == 128) attn_fwd_f32<128><<<grid, 256, 0, s>>>(a);
+    else attn_fwd_f32<64><<<grid, 256, 0, s>>>(a);
   }
   return hipGetLastError();
 }
