@@ -390,8 +390,8 @@ dit_status run_mlp_half(const dit_block_config* c, const dit_block_weights* w, i
   }
   DBG_CHECK(dbg_gemm(up, esize(c->dtype), "gemm_mlp_up_gelu"));
   DBG_CHECK(dbg_gemm(down, esize(c->dtype), "gemm_mlp_down_gate"));
-  TIMED("gemm_mlp_up_gelu", gemm_flops(up), 0, s, gemm(up, EPI_GELU, c->dtype, false, s));
-  TIMED("gemm_mlp_down_gate", gemm_flops(down), 0, s, gemm(down, EPI_RESID, c->dtype, false, s));
+  TIMED("gemm_mlp_up_gelu", gemm_flops(up), 0, s, gemm(up, EPI_GELU, c->dtype, s));
+  TIMED("gemm_mlp_down_gate", gemm_flops(down), 0, s, gemm(down, EPI_RESID, c->dtype, s));
   return DIT_OK;
 }
 
@@ -474,12 +474,13 @@ dit_status run_patch(const dit_block_config* c, const dit_step_weights* w, int B
   GemmPair p{};
   p.nprob = 1;
   p.p[0] = problem(A, contiguous_rows(C), w->in_w, w->in_b, x_img, contiguous_rows(D), M, D, C);
-  TIMED("gemm_patch_embed", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, false, s));
+  TIMED("gemm_patch_embed", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, s));
   return DIT_OK;
 }
 
+// resid (bf16 only, may be null): added to x_img before the head
 dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B, int C, const float* temb,
-                     const void* x_img, float* v, char* ws, hipStream_t s) {
+                     const void* x_img, const float* resid, float* v, char* ws, hipStream_t s) {
   const int D = c->hidden;
   float* s1 = (float*)ws;
   float* fm = (float*)(ws + al256((size_t)B * D * 4));
@@ -498,6 +499,11 @@ dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B
   g.nstreams = 1;
   dit_status st = run_gemv(c, g, true, s1, xs, "final_gemv", s);
   if (st) return st;
+  if (c->dtype == DIT_BF16) {
+    FinalArgs f{x_img, resid, fm, w->fout_w, w->fout_b, v, (int64_t)B * c->n_img, c->n_img, D, C, c->ln_eps};
+    TIMED("final_head", 2.0 * f.M * D * C, (resid ? 6.0 : 2.0) * f.M * D, s, final_head(f, s));
+    return DIT_OK;
+  }
   LnArgs a{};
   a.x[0] = x_img;
   a.xmap[0] = stream_rows(c->n_img, D);
@@ -515,7 +521,7 @@ dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B
   GemmPair p{};
   p.nprob = 1;
   p.p[0] = problem(h, contiguous_rows(D), w->fout_w, w->fout_b, v, contiguous_rows(C), B * c->n_img, C, D);
-  TIMED("gemm_final", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, true, s));
+  TIMED("gemm_final", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, s));
   return DIT_OK;
 }
 
@@ -604,7 +610,7 @@ dit_status block_body(const dit_block_config* c, const dit_block_weights* w, int
     qkv.p[0].rope_npos = std::max(c->grid_h, c->grid_w);
   }
   DBG_CHECK(dbg_gemm(qkv, esize(c->dtype), "gemm_qkv_rope"));
-  TIMED("gemm_qkv_rope", gemm_flops(qkv), 0, s, gemm(qkv, EPI_QKV, c->dtype, false, s));
+  TIMED("gemm_qkv_rope", gemm_flops(qkv), 0, s, gemm(qkv, EPI_QKV, c->dtype, s));
   // joint attention over [text ; image]; output o reuses the h buffer
   AttnArgs at{};
   char* qkvp = ws + L.qkv;
@@ -636,21 +642,19 @@ dit_status block_body(const dit_block_config* c, const dit_block_weights* w, int
     proj.p[i].gate_bstride = 6 * D;
   }
   DBG_CHECK(dbg_gemm(proj, esize(c->dtype), "gemm_out_gate"));
-  TIMED("gemm_out_gate", gemm_flops(proj), 0, s, gemm(proj, EPI_RESID, c->dtype, false, s));
+  TIMED("gemm_out_gate", gemm_flops(proj), 0, s, gemm(proj, EPI_RESID, c->dtype, s));
   return run_mlp_half(c, w, B, x_img, x_txt, mod, ws, L, s);
 }
 
 // Blocks [0, n) in order on the block workspace `inner`; their modulation is computed MOD_GROUP
-// blocks at a time into mods (first_ready: the first group's is there already).
+// blocks at a time into mods.
 dit_status run_blocks(const dit_block_config* c, const dit_block_weights* blocks, int n, int B, const float* temb,
-                      void* ximg, void* xtxt, float* mods, char* inner, const BlockWs& BL, bool first_ready,
-                      hipStream_t s) {
+                      void* ximg, void* xtxt, float* mods, char* inner, const BlockWs& BL, hipStream_t s) {
   dit_status st = DIT_OK;
   const size_t per = (size_t)2 * B * 6 * c->hidden;
   for (int g0 = 0; g0 < n; g0 += MOD_GROUP) {
     const int gn = std::min(MOD_GROUP, n - g0);
-    if (!(g0 == 0 && first_ready) && (st = run_modulation_group(c, blocks + g0, gn, B, temb, mods, inner, BL, s)))
-      return st;
+    if ((st = run_modulation_group(c, blocks + g0, gn, B, temb, mods, inner, BL, s))) return st;
     for (int i = 0; i < gn; i++)
       if ((st = block_body(c, &blocks[g0 + i], B, temb, ximg, xtxt, inner, BL, mods + i * per, g0 + i > 0, s)))
         return st;
@@ -846,7 +850,7 @@ dit_status dit_final_layer(const dit_block_config* c, const dit_step_weights* w,
   if (!temb || !x_img || !v || !aligned16(temb) || !aligned16(x_img) || !aligned16(v))
     return set_error(DIT_ERR_INVALID_ARG, "temb/x_img/v NULL or not 16-byte aligned");
   if ((st = check_ws(workspace, workspace_bytes, final_ws(c, batch)))) return st;
-  return run_final(c, w, batch, latent_dim, temb, x_img, v, (char*)workspace, hs(stream));
+  return run_final(c, w, batch, latent_dim, temb, x_img, nullptr, v, (char*)workspace, hs(stream));
 }
 
 size_t dit_denoise_workspace_bytes(const dit_block_config* c, int32_t batch, int32_t latent_dim) {
@@ -887,9 +891,9 @@ dit_status dit_denoise_step(const dit_block_config* c, const dit_step_weights* s
     HIP_TRY(hipMemcpyAsync(xtxt, x_txt, (size_t)B * c->n_txt * c->hidden * esize(c->dtype), hipMemcpyDeviceToDevice, s));
   const BlockWs BL = block_layout(c, B);
   if (n_blocks > 0 && (st = check_ws(inner, workspace_bytes - L.inner, BL.total))) return st;
-  if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, (float*)(ws + L.mods), inner, BL, false, s)))
+  if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, (float*)(ws + L.mods), inner, BL, s)))
     return st;
-  if ((st = run_final(c, sw, B, C, temb, ximg, v, inner, s))) return st;
+  if ((st = run_final(c, sw, B, C, temb, ximg, nullptr, v, inner, s))) return st;
   TIMED("flow_step", 0, (noise_level > 0.f ? 16.0 : 12.0) * B * c->n_img * C, s,
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;
@@ -958,18 +962,36 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   double* sums = (double*)(cb + TL.sums);
   if ((st = run_timestep(c, sw, B, nullptr, t, temb, inner, s))) return st;
   if ((st = run_patch(c, sw, B, C, latent, ximg, inner, s))) return st;
-  if (c->n_txt > 0)
-    HIP_TRY(hipMemcpyAsync(xtxt, x_txt, (size_t)B * c->n_txt * D * esize(c->dtype), hipMemcpyDeviceToDevice, s));
-  // block 0's modulated input: the first group's modulation GEMV and block 0's pre-attention LN
-  // (both streams; the image rows are compared), in the block workspace the first block will overwrite
+  // block 0's modulated image input, which needs only the shift1 and scale1 rows of its image
+  // modulation; the rest of the modulation and the text stream are fetched once the blocks run
   const BlockWs BL = block_layout(c, B);
   if ((st = check_ws(inner, workspace_bytes - L.inner, BL.total))) return st;
   float* mods = (float*)(ws + L.mods);
-  if ((st = run_modulation_group(c, blocks, std::min(n_blocks, MOD_GROUP), B, temb, mods, inner, BL, s))) return st;
-  if ((st = run_ln(c, B, ximg, xtxt, mods, inner, BL, 0, D, s))) return st;
+  GemvArgs g{};
+  g.W[0] = blocks[0].mod_w[0];
+  g.bias[0] = blocks[0].mod_b[0];
+  g.out[0] = mods;
+  g.out_bstride = 6 * D;
+  g.in = temb;
+  g.in_bstride = D;
+  g.N = 2 * D;
+  g.K = D;
+  g.B = B;
+  g.nstreams = 1;
+  if ((st = run_gemv(c, g, true, (float*)(inner + BL.silu), inner + BL.xs, "mod_gemv", s))) return st;
   const bool measure = state->has_prev != 0;
+  LnArgs la{};
+  la.x[0] = ximg;
+  la.xmap[0] = stream_rows(c->n_img, D);
+  la.mod[0] = mods;
+  la.mod_bstride = 6 * D;
+  la.shift_off = 0;
+  la.scale_off = D;
+  la.rows[0] = (int64_t)B * c->n_img;
+  la.D = D;
+  la.eps = c->ln_eps;
   TIMED("teacache_distance", 0, (measure ? 3.0 : 2.0) * n_act * esize(c->dtype), s,
-        teacache_distance(inner + BL.h, cb + TL.hprev, B, c->n_img, c->n_txt, D, measure, parts, sums, c->dtype, s));
+        teacache_ln_distance(la, cb + TL.hprev, measure, parts, sums, c->dtype, s));
   double r = std::numeric_limits<double>::quiet_NaN();
   if (measure) {
     double hsums[2];
@@ -986,16 +1008,18 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   }
   state->has_prev = 1;
   if (run) {
+    if (c->n_txt > 0)
+      HIP_TRY(hipMemcpyAsync(xtxt, x_txt, (size_t)B * c->n_txt * D * esize(c->dtype), hipMemcpyDeviceToDevice, s));
     TIMED("small_elementwise", 0, 0, s, teacache_residual(ximg, resid, n_act, 0, c->dtype, s));
-    if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, mods, inner, BL, true, s))) return st;
+    if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, mods, inner, BL, s))) return st;
     TIMED("small_elementwise", 0, 0, s, teacache_residual(ximg, resid, n_act, 1, c->dtype, s));
     state->has_residual = 1;
-  } else {
+  } else if (c->dtype != DIT_BF16) {   // bf16: the velocity head adds the residual as it reads x
     TIMED("small_elementwise", 0, 0, s, teacache_residual(ximg, resid, n_act, 2, c->dtype, s));
   }
   if (ran_blocks) *ran_blocks = run;
   if (rel) *rel = r;
-  if ((st = run_final(c, sw, B, C, temb, ximg, v, inner, s))) return st;
+  if ((st = run_final(c, sw, B, C, temb, ximg, !run && c->dtype == DIT_BF16 ? resid : nullptr, v, inner, s))) return st;
   TIMED("flow_step", 0, (noise_level > 0.f ? 16.0 : 12.0) * B * c->n_img * C, s,
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;

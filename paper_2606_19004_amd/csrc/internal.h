@@ -96,7 +96,7 @@ struct GemmPair {              // up to two problems (image stream, text stream)
 
 enum Dtype { DT_F32 = 0, DT_BF16 = 1 };
 
-hipError_t gemm(const GemmPair& pr, int epi, int dtype, bool out_f32, hipStream_t s);
+hipError_t gemm(const GemmPair& pr, int epi, int dtype, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // attention
@@ -147,12 +147,22 @@ hipError_t rope_table(float* tab, int npos, int head_dim, float theta, hipStream
 // mean = x + h (v + k1 (x + omt v))
 hipError_t flow_logprob_launch(const float* x, const float* v, const float* xn, int batch, int64_t n, double h,
                                double k1, double omt, double inv2var, double cst, double* logp, hipStream_t s);
-// TeaCache: per-block partial sums of |h - h_prev| and |h_prev| over the image rows of the joint
-// buffer h ([B][S][D], image rows at offset n_txt) against h_prev ([B][N_i][D]), summed in a fixed
-// order into sums[2] (skipped when !measure); h_prev is then overwritten with h.
-hipError_t teacache_distance(const void* h, void* h_prev, int B, int n_img, int n_txt, int D, bool measure,
-                             double* partials, double* sums, int dtype, hipStream_t s);
-// residual r (fp32) of the activation x (n elements): mode 0 r = x, 1 r = x - r, 2 x = x + r
+// TeaCache: h = LN(x)(1 + scale) + shift over the image rows (stream 0 of a), rounded to dtype and
+// compared with h_prev ([rows][D]): sums[0..1] = sum |h - h_prev|, sum |h_prev| in a fixed order (skipped
+// when !measure); h_prev is then overwritten with h.
+hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, double* partials, double* sums, int dtype,
+                                hipStream_t s);
+// velocity head, bf16: v[m][c] = sum_k W[c][k] h[m][k] + bias[c], h = LN(x + resid)(1 + scale) + shift with
+// (shift, scale) = mod[b][0..D), mod[b][D..2D), b = m / rows_per_batch; resid (fp32) may be null. D a
+// multiple of 32 and at most 4096, C a multiple of 64.
+struct FinalArgs {
+  const void* x; const float* resid; const float* mod; const void* W; const void* bias; float* v;
+  int64_t M, rows_per_batch;
+  int D, C;
+  float eps;
+};
+hipError_t final_head(const FinalArgs& a, hipStream_t s);
+// residual r (fp32) of the activation x (n elements): mode 0 r = x, 1 r = x - r, 2 x = x + r (fp32 x only)
 hipError_t teacache_residual(void* x, float* r, int64_t n, int mode, int dtype, hipStream_t s);
 constexpr int TEACACHE_PARTS = 512;
 hipError_t flow_update(float* x, const float* v, const float* noise, int64_t n,

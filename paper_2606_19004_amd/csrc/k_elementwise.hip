@@ -5,6 +5,8 @@
 //   gemv           batched GEMV for the adaLN / timestep / final modulation vectors
 //   reward_stats   per prompt-group mean, std, advantages, stable descending ranks
 //   small helpers  SiLU, fp32->bf16 cast, timestep sinusoid, RoPE cos/sin table
+#include <type_traits>
+
 #include "internal.h"
 
 namespace dit {
@@ -111,77 +113,6 @@ hipError_t flow_logprob_launch(const float* x, const float* v, const float* xn, 
   return hipGetLastError();
 }
 
-// TeaCache distance: each thread walks 8-element chunks of the image rows (grid-stride), sums
-// |h - h_prev| and |h_prev| in fp64, and refreshes h_prev; one partial pair per workgroup.
-template <typename T>
-__global__ void __launch_bounds__(256) teacache_distance_kernel(const T* __restrict__ h, T* __restrict__ hp,
-                                                                int64_t chunks, int64_t per_b, int n_txt, int S,
-                                                                int D, int measure, double* __restrict__ part) {
-  __shared__ double sd[4], sp[4];
-  double ad = 0.0, ap = 0.0;
-  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < chunks; q += (int64_t)gridDim.x * 256) {
-    const int64_t e = q * 8, b = e / per_b, rem = e - b * per_b;
-    const int64_t r = rem / D, c = rem - r * D;
-    const T* src = h + (b * S + n_txt + r) * D + c;
-    float a[8], p[8];
-    load4<T>(src, a);
-    load4<T>(src + 4, a + 4);
-    if (measure) {
-      load4<T>(hp + e, p);
-      load4<T>(hp + e + 4, p + 4);
-#pragma unroll
-      for (int j = 0; j < 8; j++) {
-        ad += fabs((double)a[j] - (double)p[j]);
-        ap += fabs((double)p[j]);
-      }
-    }
-    store4<T>(hp + e, a);
-    store4<T>(hp + e + 4, a + 4);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    ad += __shfl_xor(ad, o, 64);
-    ap += __shfl_xor(ap, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    sd[threadIdx.x >> 6] = ad;
-    sp[threadIdx.x >> 6] = ap;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = sd[0] + sd[1] + sd[2] + sd[3];
-    part[2 * blockIdx.x + 1] = sp[0] + sp[1] + sp[2] + sp[3];
-  }
-}
-
-__global__ void teacache_sum_kernel(const double* __restrict__ part, int nparts, double* __restrict__ sums) {
-  if (threadIdx.x == 0) {
-    double a = 0.0, b = 0.0;
-    for (int i = 0; i < nparts; i++) {
-      a += part[2 * i];
-      b += part[2 * i + 1];
-    }
-    sums[0] = a;
-    sums[1] = b;
-  }
-}
-
-hipError_t teacache_distance(const void* h, void* h_prev, int B, int n_img, int n_txt, int D, bool measure,
-                             double* partials, double* sums, int dtype, hipStream_t s) {
-  const int64_t per_b = (int64_t)n_img * D, chunks = B * per_b / 8;
-  if (chunks == 0) return hipSuccess;
-  const int grid = (int)std::min<int64_t>(TEACACHE_PARTS, cdiv(chunks, (int64_t)256));
-  const int S = n_img + n_txt;
-  if (dtype == DT_BF16)
-    teacache_distance_kernel<u16><<<grid, 256, 0, s>>>((const u16*)h, (u16*)h_prev, chunks, per_b, n_txt, S, D,
-                                                       measure, partials);
-  else
-    teacache_distance_kernel<float><<<grid, 256, 0, s>>>((const float*)h, (float*)h_prev, chunks, per_b, n_txt, S,
-                                                         D, measure, partials);
-  if (measure) teacache_sum_kernel<<<1, 64, 0, s>>>(partials, grid, sums);
-  return hipGetLastError();
-}
-
 template <typename T, int MODE>
 __global__ void __launch_bounds__(256) teacache_residual_kernel(T* __restrict__ x, float* __restrict__ r, int64_t n4) {
   for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n4; q += (int64_t)gridDim.x * 256) {
@@ -206,7 +137,7 @@ hipError_t teacache_residual(void* x, float* r, int64_t n, int mode, int dtype, 
   if (dtype == DT_BF16) {
     if (mode == 0) teacache_residual_kernel<u16, 0><<<grid, 256, 0, s>>>((u16*)x, r, n4);
     else if (mode == 1) teacache_residual_kernel<u16, 1><<<grid, 256, 0, s>>>((u16*)x, r, n4);
-    else teacache_residual_kernel<u16, 2><<<grid, 256, 0, s>>>((u16*)x, r, n4);
+    else return hipErrorInvalidValue;   // the bf16 velocity head adds the residual itself
   } else {
     if (mode == 0) teacache_residual_kernel<float, 0><<<grid, 256, 0, s>>>((float*)x, r, n4);
     else if (mode == 1) teacache_residual_kernel<float, 1><<<grid, 256, 0, s>>>((float*)x, r, n4);
@@ -400,6 +331,377 @@ static hipError_t ln_launch(const LnArgs& a, hipStream_t s) {
 }
 hipError_t ln_modulate(const LnArgs& a, int dtype, hipStream_t s) {
   return dtype == DT_BF16 ? ln_launch<u16>(a, s) : ln_launch<float>(a, s);
+}
+
+// Keeps a packed row packed: the compiler would otherwise carry the fp32 expansion (twice the registers)
+// from one pass over the row to the next.
+__device__ __forceinline__ void opaque(uint4& u) { asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w)); }
+
+// ---------------------------------------------------------------------------
+// TeaCache distance, fused with the LayerNorm + modulate that makes the compared input: a wave takes
+// rows of the image stream as in ln_modulate_kernel, rounds h to the storage type, adds |h - h_prev| and
+// |h_prev| in fp64 and replaces h_prev, so h itself is never stored. One partial pair per workgroup
+// (at most TEACACHE_PARTS), summed in a fixed order. Bound by HBM: x and h_prev read, h_prev written.
+// ---------------------------------------------------------------------------
+template <typename T, int CH>
+__global__ void __launch_bounds__(256) teacache_ln_distance_kernel(LnArgs a, T* __restrict__ hp, int measure,
+                                                                   double* __restrict__ part) {
+  __shared__ double sd[4], sp[4];
+  constexpr int Q = sizeof(T) / 2;   // 16-byte registers per chunk of 8 elements
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int D = a.D;
+  const int64_t step = (int64_t)gridDim.x * 4;
+  double ad = 0.0, ap = 0.0;
+  uint4 xr[CH][Q], pr[CH][Q];   // the row as stored; bf16 rows are fetched one row ahead
+  auto fetch = [&](int64_t row, uint4 (*x)[Q], uint4 (*p)[Q]) {
+    const T* xp = (const T*)a.x[0] + row_offset(a.xmap[0], row);
+    const T* hrow = hp + row * D;
+#pragma unroll
+    for (int c = 0; c < CH; c++) {
+      const int k = (c * 64 + lane) * 8;
+#pragma unroll
+      for (int q = 0; q < Q; q++) {
+        x[c][q] = k < D ? ((const uint4*)(xp + k))[q] : make_uint4(0u, 0u, 0u, 0u);
+        p[c][q] = k < D && measure ? ((const uint4*)(hrow + k))[q] : make_uint4(0u, 0u, 0u, 0u);
+      }
+    }
+  };
+  auto expand = [](const uint4* u, float* f) {
+    if constexpr (Q == 1) {
+      const uint32_t w[4] = {u[0].x, u[0].y, u[0].z, u[0].w};
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        f[2 * i] = __uint_as_float(w[i] << 16);
+        f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 2; q++) {
+        f[4 * q] = __uint_as_float(u[q].x);
+        f[4 * q + 1] = __uint_as_float(u[q].y);
+        f[4 * q + 2] = __uint_as_float(u[q].z);
+        f[4 * q + 3] = __uint_as_float(u[q].w);
+      }
+    }
+  };
+  int64_t row = (int64_t)blockIdx.x * 4 + wave;
+  if (row < a.rows[0]) fetch(row, xr, pr);
+  for (; row < a.rows[0]; row += step) {
+    const float* mod = a.mod[0] + (row / a.xmap[0].rows_per_batch) * a.mod_bstride;
+    T* hrow = hp + row * D;
+    uint4 xn[CH][Q], pn[CH][Q];
+    if constexpr (Q == 1) fetch(min(row + step, a.rows[0] - 1), xn, pn);
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; c++) {   // (zeros past the row's end)
+      float v[8];
+      expand(xr[c], v);
+#pragma unroll
+      for (int i = 0; i < 8; i++) sum += v[i];
+    }
+    const float mean = wave_sum(sum) / (float)D;
+    float sq = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; c++)
+      if ((c * 64 + lane) * 8 < D) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < Q; q++) opaque(xr[c][q]);
+        expand(xr[c], v);
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+          const float d = v[i] - mean;
+          sq += d * d;
+        }
+      }
+    const float rstd = rsqrtf(wave_sum(sq) / (float)D + a.eps);
+#pragma unroll
+    for (int c = 0; c < CH; c++) {
+      const int k = (c * 64 + lane) * 8;
+      if (k < D) {
+        float v[8], p[8], sh[8], sc[8], o[8];
+#pragma unroll
+        for (int q = 0; q < Q; q++) opaque(xr[c][q]);
+        expand(xr[c], v);
+        expand(pr[c], p);
+        Vec8<float>::load(mod + a.shift_off + k, sh);
+        Vec8<float>::load(mod + a.scale_off + k, sc);
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+          o[i] = to_f32(from_f32<T>(fmaf((v[i] - mean) * rstd, 1.0f + sc[i], sh[i])));
+          if (measure) {
+            ad += fabs((double)o[i] - (double)p[i]);
+            ap += fabs((double)p[i]);
+          }
+        }
+        Vec8<T>::store(hrow + k, o);
+        __builtin_amdgcn_sched_barrier(0);   // one chunk's shift and scale at a time in registers
+      }
+    }
+    if constexpr (Q == 1) {
+#pragma unroll
+      for (int c = 0; c < CH; c++) {
+        xr[c][0] = xn[c][0];
+        pr[c][0] = pn[c][0];
+      }
+    } else if (row + step < a.rows[0]) {
+      fetch(row + step, xr, pr);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    ad += __shfl_xor(ad, o, 64);
+    ap += __shfl_xor(ap, o, 64);
+  }
+  if (lane == 0) {
+    sd[wave] = ad;
+    sp[wave] = ap;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double d = 0.0, q = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+      d += sd[w];
+      q += sp[w];
+    }
+    part[2 * blockIdx.x] = d;
+    part[2 * blockIdx.x + 1] = q;
+  }
+}
+
+// sums[0..1] of up to TEACACHE_PARTS pairs: a thread per strided share, then a fixed tree
+__global__ void __launch_bounds__(256) teacache_sum_kernel(const double* __restrict__ part, int nparts,
+                                                           double* __restrict__ sums) {
+  __shared__ double sd[4], sp[4];
+  double a = 0.0, b = 0.0;
+  for (int i = threadIdx.x; i < nparts; i += 256) {
+    a += part[2 * i];
+    b += part[2 * i + 1];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, 64);
+    b += __shfl_xor(b, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sd[threadIdx.x >> 6] = a;
+    sp[threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    sums[0] = (sd[0] + sd[1]) + (sd[2] + sd[3]);
+    sums[1] = (sp[0] + sp[1]) + (sp[2] + sp[3]);
+  }
+}
+
+template <typename T>
+static void teacache_ln_launch(const LnArgs& a, T* hp, bool measure, double* partials, int grid, hipStream_t s) {
+  const int ch = cdiv(a.D, 512);
+  if (ch <= 1) teacache_ln_distance_kernel<T, 1><<<grid, 256, 0, s>>>(a, hp, measure, partials);
+  else if (ch <= 2) teacache_ln_distance_kernel<T, 2><<<grid, 256, 0, s>>>(a, hp, measure, partials);
+  else if (ch <= 4) teacache_ln_distance_kernel<T, 4><<<grid, 256, 0, s>>>(a, hp, measure, partials);
+  else if (ch <= 6) teacache_ln_distance_kernel<T, 6><<<grid, 256, 0, s>>>(a, hp, measure, partials);
+  else teacache_ln_distance_kernel<T, 8><<<grid, 256, 0, s>>>(a, hp, measure, partials);
+}
+hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, double* partials, double* sums, int dtype,
+                                hipStream_t s) {
+  if (a.rows[0] == 0) return hipSuccess;
+  const int grid = (int)std::min<int64_t>(TEACACHE_PARTS, cdiv(a.rows[0], 4));
+  if (dtype == DT_BF16) teacache_ln_launch<u16>(a, (u16*)h_prev, measure, partials, grid, s);
+  else teacache_ln_launch<float>(a, (float*)h_prev, measure, partials, grid, s);
+  if (measure) teacache_sum_kernel<<<1, 256, 0, s>>>(partials, grid, sums);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Velocity head in one pass (bf16): x (+ the TeaCache residual, rounded to bf16 as if stored) ->
+// LayerNorm + modulate -> bf16 -> W_out h + b_out, fp32 out. A workgroup takes 16 rows; its 8 waves take
+// every 8th 64-deep pair of k steps of them (whole 128-byte lines of a row), so that a lane's share (row
+// lane % 16, 8 elements at 8 (lane / 16) of each 32-deep step) is at once the LayerNorm input and, once modulated, operand B of
+// v_mfma_f32_16x16x32_bf16: the modulated row never leaves the registers. W_out (64 output features per
+// workgroup) is read from L2 straight into operand A. Row sums and the eight partial tiles meet in LDS, in a
+// fixed order. Bound by reading x (and the fp32 residual) once.
+// ---------------------------------------------------------------------------
+// FULL: every wave has exactly NS steps, no test per step
+template <int NS, bool RES, bool FULL>
+__global__ void __launch_bounds__(512, 4) final_head_kernel(FinalArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist only in the device pass
+  constexpr int NW = 8;
+  __shared__ float red[2][NW][16];
+  __shared__ f32x4 part[NW][4][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  const int D = a.D, nks = D / 32;
+  const int np = nks / 2, nloc = np > wave ? 2 * ((np - wave + NW - 1) / NW) : 0;   // this wave's k steps
+  const int64_t m0 = (int64_t)blockIdx.x * 16, mrow = min(m0 + r16, a.M - 1);
+  // step i of this wave starts at element koff(i) of a row; loads go through buffer descriptors with that
+  // part of the address in a scalar, since per-access 64-bit pointers would take most of the registers
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  auto koff = [&](int i) { return 64 * wave_s + 64 * NW * (i >> 1) + 32 * (i & 1); };
+  auto rsrc = [](const void* p) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, 0x7fffffff, 0x00020000); };
+  auto load16 = [](__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+  };
+  auto load_f8 = [&](__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float* f) {
+    const f32x4 lo = __builtin_bit_cast(f32x4, load16(r, voff, soff)), hi = __builtin_bit_cast(f32x4, load16(r, voff + 16, soff));
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      f[e] = lo[e];
+      f[4 + e] = hi[e];
+    }
+  };
+  const uint32_t row = (uint32_t)(mrow - m0);
+  const int64_t b0 = m0 / a.rows_per_batch;
+  const auto rx = rsrc((const u16*)a.x + m0 * D), rr = rsrc(RES ? a.resid + m0 * D : nullptr), rm = rsrc(a.mod + b0 * 2 * D);
+  const uint32_t xo = (row * D + 8 * kq) * 2, ro = (row * D + 8 * kq) * 4;
+  const uint32_t mo = (uint32_t)(mrow / a.rows_per_batch - b0) * 8u * D + 32 * kq, wo = (uint32_t)(r16 * D + 8 * kq) * 2;
+  uint4 xv[NS];
+  float sum = 0.f;
+  auto unpack = [](const uint4& u, float* f) {
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      f[2 * i] = __uint_as_float(w[i] << 16);
+      f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+  };
+  auto pack = [](const float* f) {
+    return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+  };
+#pragma unroll
+  for (int i = 0; i < NS; i++) {
+    if (FULL || i < nloc) xv[i] = load16(rx, xo, koff(i) * 2);
+    else xv[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (RES) {
+#pragma unroll
+    for (int i = 0; i < NS; i++)
+      if (FULL || i < nloc) {
+        float f[8], q[8];
+        unpack(xv[i], f);
+        load_f8(rr, ro, koff(i) * 4, q);
+#pragma unroll
+        for (int e = 0; e < 8; e++) f[e] += q[e];
+        xv[i] = pack(f);
+        if (i % 6 == 5) __builtin_amdgcn_sched_barrier(0);   // six steps' residuals in flight
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < NS; i++) {   // (zeros past the wave's steps)
+    float f[8];
+    opaque(xv[i]);
+    unpack(xv[i], f);
+#pragma unroll
+    for (int e = 0; e < 8; e++) sum += f[e];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  sum += __shfl_xor(sum, 16, 64);
+  sum += __shfl_xor(sum, 32, 64);
+  if (kq == 0) red[0][wave][r16] = sum;
+  __syncthreads();
+  auto total = [&](int k) {   // the waves' sums of row r16, in a fixed order
+    float t = red[k][0][r16];
+#pragma unroll
+    for (int w = 1; w < NW; w++) t += red[k][w][r16];
+    return t / (float)D;
+  };
+  const float mean = total(0);
+  float sq = 0.f;
+#pragma unroll
+  for (int i = 0; i < NS; i++)
+    if (FULL || i < nloc) {
+      float f[8];
+      opaque(xv[i]);
+      unpack(xv[i], f);
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        const float d = f[e] - mean;
+        sq += d * d;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  sq += __shfl_xor(sq, 16, 64);
+  sq += __shfl_xor(sq, 32, 64);
+  if (kq == 0) red[1][wave][r16] = sq;
+  __syncthreads();
+  const float rstd = rsqrtf(total(1) + a.eps);
+#pragma unroll
+  for (int i = 0; i < NS; i++)
+    if (FULL || i < nloc) {
+      float f[8], sh[8], sc[8];
+      opaque(xv[i]);
+      unpack(xv[i], f);
+      load_f8(rm, mo, koff(i) * 4, sh);
+      load_f8(rm, mo, (D + koff(i)) * 4, sc);
+#pragma unroll
+      for (int e = 0; e < 8; e++) f[e] = fmaf((f[e] - mean) * rstd, 1.0f + sc[e], sh[e]);
+      xv[i] = pack(f);
+      if (i & 1) __builtin_amdgcn_sched_barrier(0);   // two steps' shift and scale at a time in registers
+    }
+  const int c0 = blockIdx.y * 64;
+  const auto rw = rsrc((const u16*)a.W + (int64_t)c0 * D);
+  f32x4 acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // W fragments one step ahead
+  bf16x8 fw[2][4];
+  auto load_w = [&](int i, int slot) {
+#pragma unroll
+    for (int j = 0; j < 4; j++) fw[slot][j] = __builtin_bit_cast(bf16x8, load16(rw, wo, (16 * j * D + koff(i)) * 2));
+  };
+  if (FULL || nloc > 0) load_w(0, 0);
+#pragma unroll
+  for (int i = 0; i < NS; i++)
+    if (FULL || i < nloc) {
+      if (FULL ? i + 1 < NS : i + 1 < nloc) load_w(i + 1, (i + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; j++)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i & 1][j], __builtin_bit_cast(bf16x8, xv[i]), acc[j], 0, 0, 0);
+    }
+#pragma unroll
+  for (int j = 0; j < 4; j++) part[wave][j][lane] = acc[j];
+  __syncthreads();
+  if (wave >= 4) return;
+  // wave j finishes features c0 + 16 j + 4 kq + 0..3 of row r16
+  f32x4 o = part[0][wave][lane];
+#pragma unroll
+  for (int q = 1; q < NW; q++) {
+    const f32x4 p = part[q][wave][lane];
+#pragma unroll
+    for (int r = 0; r < 4; r++) o[r] += p[r];
+  }
+  const int n = c0 + 16 * wave + 4 * kq;
+  float b[4] = {0.f, 0.f, 0.f, 0.f};
+  if (a.bias) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) b[q] = to_f32(((const u16*)a.bias)[n + q]);
+  }
+  if ((int64_t)blockIdx.x * 16 + r16 < a.M)
+    *(float4*)(a.v + mrow * a.C + n) = make_float4(o[0] + b[0], o[1] + b[1], o[2] + b[2], o[3] + b[3]);
+#endif
+}
+
+template <int NS, bool RES>
+static void final_head_ns(const FinalArgs& a, dim3 grid, hipStream_t s) {
+  if (a.D == 256 * NS) final_head_kernel<NS, RES, true><<<grid, 512, 0, s>>>(a);
+  else final_head_kernel<NS, RES, false><<<grid, 512, 0, s>>>(a);
+}
+template <bool RES>
+static hipError_t final_head_launch(const FinalArgs& a, hipStream_t s) {
+  const dim3 grid(cdiv(a.M, 16), a.C / 64);
+  const int ns = 2 * cdiv(a.D, 512);   // k steps of the wave that has most
+  if (ns <= 2) final_head_ns<2, RES>(a, grid, s);
+  else if (ns <= 4) final_head_ns<4, RES>(a, grid, s);
+  else if (ns <= 8) final_head_ns<8, RES>(a, grid, s);
+  else if (ns <= 12) final_head_ns<12, RES>(a, grid, s);
+  else final_head_ns<16, RES>(a, grid, s);
+  return hipGetLastError();
+}
+hipError_t final_head(const FinalArgs& a, hipStream_t s) {
+  if (a.M == 0) return hipSuccess;
+  return a.resid ? final_head_launch<true>(a, s) : final_head_launch<false>(a, s);
 }
 
 // ---------------------------------------------------------------------------

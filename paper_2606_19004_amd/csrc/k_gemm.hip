@@ -223,7 +223,7 @@ template <> struct Mfma<16> {
 // form delivers more MFMA throughput per watt on this chip.
 // TRI (256 x 256 tiles only): three LDS stages for A and two for W (160 KB), so the activation
 // operand is loaded two k-tiles ahead.
-template <int BM, int BN, int WM, int WN, int EPI, bool OUTF32, int MS = 32, bool TRI = false>
+template <int BM, int BN, int WM, int WN, int EPI, int MS = 32, bool TRI = false>
 __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, int tiles0, int total_tiles) {
   typedef typename Mfma<MS>::acc_t acc_t;
   constexpr int NACC = sizeof(acc_t) / 4;              // accumulator registers per block
@@ -496,14 +496,14 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
   //   MS = 32: n = 32 i + 8 g + 4 (lane / 32) + q, m = 32 j + lane % 32
   //   MS = 16: n = 16 i + 4 (lane / 16) + q,        m = 16 j + lane % 16
   constexpr int NG = NACC / 4;
-  // MS = 16 with bf16 output: blocks i and i + 1 of a row group (32 adjacent columns) are finished
+  // MS = 16: blocks i and i + 1 of a row group (32 adjacent columns) are finished
   // together and regrouped with v_permlane16_swap, which exchanges lanes 16-31 of one register with
   // lanes 0-15 of another (and 48-63 with 32-47). Lane group g = lane / 16 then holds the 8 adjacent
   // columns 32 p + 16 (g & 1) + 8 (g >> 1) of pair p, stored with one 16-byte store. A CU issues a
   // store of 16 rows x 32 B (the accumulator layout) in ~74 cycles and one of 16 rows x 64 B in ~20,
   // and with 256 stores per tile that issue time, not HBM, bounded the epilogue. The paired layout
   // needs 16-byte aligned output rows; otherwise the accumulator layout is stored as it is.
-  constexpr bool PAIRS = MS == 16 && !OUTF32;
+  constexpr bool PAIRS = MS == 16;
   static_assert(!PAIRS || TI % 2 == 0, "the paired store joins blocks 2p and 2p + 1");
   const bool pairs = PAIRS && (P.N & 7) == 0 && ((uintptr_t)P.C & 15) == 0 &&
                      ((P.cmap.batch_stride | P.cmap.row_stride | P.cmap.offset) & 7) == 0;
@@ -642,8 +642,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
             v[2] = a1 * t.z - b1 * t.w;
             v[3] = a1 * t.w + b1 * t.z;
           }
-          if (OUTF32) store4<float>((float*)P.C + R.off + n, v);
-          else store4<u16>((u16*)P.C + R.off + n, v);
+          store4<u16>((u16*)P.C + R.off + n, v);
         }
       }
     }
@@ -729,7 +728,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
 #endif
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, bool OUTF32, int MS, bool TRI = false>
+template <int BM, int BN, int WM, int WN, int EPI, int MS, bool TRI = false>
 static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s) {
   int tiles[2] = {0, 0};
   for (int i = 0; i < pr.nprob; i++)
@@ -744,13 +743,13 @@ static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
   if (lds > 65536 && (dev < 0 || dev >= 64 || !attr_set[dev].load(std::memory_order_acquire))) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, OUTF32, MS, TRI>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, MS, TRI>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64) attr_set[dev].store(true, std::memory_order_release);
   }
   int grid = 8 * cdiv(total, 8);
-  gemm_bf16_kernel<BM, BN, WM, WN, EPI, OUTF32, MS, TRI><<<grid, WM * WN * 64, lds, s>>>(pr, tiles[0], total);
+  gemm_bf16_kernel<BM, BN, WM, WN, EPI, MS, TRI><<<grid, WM * WN * 64, lds, s>>>(pr, tiles[0], total);
   return hipGetLastError();
 }
 
@@ -768,7 +767,7 @@ static int cu_count() {
   return n;
 }
 
-template <int EPI, bool OUTF32>
+template <int EPI>
 static hipError_t dispatch_bf16(const GemmPair& pr, hipStream_t s) {
   int maxn = 0;
   int64_t big_tiles = 0;
@@ -776,7 +775,7 @@ static hipError_t dispatch_bf16(const GemmPair& pr, hipStream_t s) {
     maxn = std::max(maxn, pr.p[i].N);
     big_tiles += (int64_t)cdiv(pr.p[i].M, 256) * cdiv(pr.p[i].N, 256);
   }
-  if (maxn <= 64) return launch_bf16<64, 64, 2, 2, EPI, OUTF32, 32>(pr, s);
+  if (maxn <= 64) return launch_bf16<64, 64, 2, 2, EPI, 32>(pr, s);
   // 128 x 128 tiles (4 waves, two workgroups per CU) or 256 x 256 tiles (8 waves, one per CU): the
   // one with fewer estimated rounds, a round of 2 x CUs small tiles costing C128 of a large round
   // (a quarter of the flops per tile, at lower MFMA efficiency)
@@ -787,7 +786,7 @@ static hipError_t dispatch_bf16(const GemmPair& pr, hipStream_t s) {
     for (int i = 0; i < pr.nprob; i++) small_tiles += (int64_t)cdiv(pr.p[i].M, 128) * cdiv(pr.p[i].N, 128);
     const double big = (double)((big_tiles + cus - 1) / cus);
     const double small = C128 * (double)((small_tiles + 2 * cus - 1) / (2 * cus));
-    if (small < big) return launch_bf16<128, 128, 2, 2, EPI, OUTF32, 32>(pr, s);
+    if (small < big) return launch_bf16<128, 128, 2, 2, EPI, 32>(pr, s);
   }
   // large problems: 8 waves of 64x128 on 16x16x32 MFMAs (measured 3-7% faster than 32x32x16 here),
   // with three A stages, so the activation rows are requested two k-tiles ahead (in the denoise step
@@ -812,12 +811,12 @@ static hipError_t dispatch_bf16(const GemmPair& pr, hipStream_t s) {
       a.nprob = 1;
       b.nprob = 1;
       b.p[0] = pr.p[1];
-      hipError_t e = launch_bf16<256, 256, 4, 2, EPI, OUTF32, 16, true>(a, s);
+      hipError_t e = launch_bf16<256, 256, 4, 2, EPI, 16, true>(a, s);
       if (e != hipSuccess) return e;
-      return launch_bf16<256, 192, 4, 2, EPI, OUTF32, 16, true>(b, s);
+      return launch_bf16<256, 192, 4, 2, EPI, 16, true>(b, s);
     }
   }
-  return launch_bf16<256, 256, 4, 2, EPI, OUTF32, 16, true>(pr, s);
+  return launch_bf16<256, 256, 4, 2, EPI, 16, true>(pr, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1046,7 +1045,7 @@ static hipError_t launch_f32(const GemmPair& pr, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t gemm(const GemmPair& pr, int epi, int dtype, bool out_f32, hipStream_t s) {
+hipError_t gemm(const GemmPair& pr, int epi, int dtype, hipStream_t s) {
   if (dtype == DT_F32) {
     switch (epi) {
       case EPI_STORE: return launch_f32<EPI_STORE>(pr, s);
@@ -1056,15 +1055,11 @@ hipError_t gemm(const GemmPair& pr, int epi, int dtype, bool out_f32, hipStream_
     }
     return hipErrorInvalidValue;
   }
-  if (out_f32) {
-    if (epi == EPI_STORE) return dispatch_bf16<EPI_STORE, true>(pr, s);
-    return hipErrorInvalidValue;
-  }
   switch (epi) {
-    case EPI_STORE: return dispatch_bf16<EPI_STORE, false>(pr, s);
-    case EPI_GELU: return dispatch_bf16<EPI_GELU, false>(pr, s);
-    case EPI_RESID: return dispatch_bf16<EPI_RESID, false>(pr, s);
-    case EPI_QKV: return dispatch_bf16<EPI_QKV, false>(pr, s);
+    case EPI_STORE: return dispatch_bf16<EPI_STORE>(pr, s);
+    case EPI_GELU: return dispatch_bf16<EPI_GELU>(pr, s);
+    case EPI_RESID: return dispatch_bf16<EPI_RESID>(pr, s);
+    case EPI_QKV: return dispatch_bf16<EPI_QKV>(pr, s);
   }
   return hipErrorInvalidValue;
 }

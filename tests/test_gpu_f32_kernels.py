@@ -1,0 +1,58 @@
+"""The fp32 matrix-instruction kernels at the edges of their tiles.
+
+GEMM (through the patch embedding, the ABI's plain GEMM): integer operands make every partial sum an
+integer below 2^24, so fp32 results are exact in any order and are compared bit for bit, on both tile
+shapes (32 x 32 with K split over four waves, 64 x 64) with ragged rows and one to many k slices.
+
+Attention against float64: the score of a query and a key is a d-term fp32 sum, off by at most
+(d + 2) 2^-24 sum|q k| scale; with N(0, 1) inputs sum|q k| scale stays below 12 at d = 128, so
+probabilities (and with them the output, a convex combination of v) are off by at most 1e-4 of max|v|
+in the worst case. Typical errors are a hundred times smaller; 1e-5 separates them from a wrong tile."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def d():
+    from paper_2606_19004_amd import ditstep
+    return ditstep
+
+
+# (grid_h, grid_w, batch, hidden, K): one row; both sides of a 32- and a 64-row tile; 2, 6 and 20 k
+# slices; enough tiles for the 64 x 64 kernel (3 and 20 slices of 32, last row tile partial)
+@pytest.mark.parametrize("gh,gw,b,hidden,k", [(1, 1, 1, 64, 64), (1, 31, 1, 128, 64), (1, 33, 1, 64, 192), (5, 13, 1, 64, 640),
+                                              (7, 9, 3, 320, 64), (50, 41, 4, 1024, 64), (31, 33, 8, 1024, 640)])
+def test_gemm_f32_integer_operands_exact(d, gh, gw, b, hidden, k):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    n = gh * gw
+    c = d.block_config(hidden, hidden // 64, 64, 4 * hidden, n, 0, gh, gw, dtype="f32")
+    lat = torch.randint(-3, 4, (b, n, k), generator=g, device="cuda").float()
+    sw = {nm: torch.zeros(shp, device="cuda") for nm, shp in
+          {"t1_w": (hidden, 256), "t1_b": (hidden,), "t2_w": (hidden, hidden), "t2_b": (hidden,), "in_w": (hidden, k),
+           "in_b": (hidden,), "fmod_w": (2 * hidden, hidden), "fmod_b": (2 * hidden,), "fout_w": (k, hidden),
+           "fout_b": (k,)}.items()}
+    sw["in_w"] = torch.randint(-3, 4, (hidden, k), generator=g, device="cuda").float()
+    sw["in_b"] = torch.randint(-3, 4, (hidden,), generator=g, device="cuda").float()
+    x = torch.full((b, n, hidden), 0.5, device="cuda")
+    d.dit_patch_embed(c, d.step_weights(sw), lat, x, d.workspace(256))
+    want = lat.double().reshape(-1, k) @ sw["in_w"].double().t() + sw["in_b"].double()
+    assert torch.equal(x.double().reshape(-1, hidden), want)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("seq", [1, 15, 16, 17, 32, 33, 63, 64, 65, 130])
+def test_attention_f32_tile_edges(d, hd, seq):
+    b, h = 2, 3
+    g = torch.Generator(device="cuda").manual_seed(seq + hd)
+    qkv = torch.randn(b, seq, 3, h, hd, generator=g, device="cuda")
+    o = torch.full((b, h, seq, hd), 9.0, device="cuda")      # head-major output: other strides than the input's
+    d.joint_attention(qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2], o, b, h, seq, hd,
+                      (seq * 3 * h * hd, 3 * h * hd, hd), (h * seq * hd, hd, seq * hd), dtype="f32")
+    q, k, v = (t.permute(0, 2, 1, 3).double().cpu().numpy() for t in qkv.unbind(2))
+    s = q @ k.swapaxes(-1, -2) / np.sqrt(hd)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    want = (p / p.sum(-1, keepdims=True)) @ v
+    assert np.max(np.abs(o.cpu().numpy() - want)) <= 1e-5 * np.max(np.abs(v))
