@@ -946,10 +946,10 @@ hipError_t gemv(const GemvArgs& a, int dtype, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// per-group reward statistics. One 256-thread workgroup per group; rewards of
-// the group in LDS; fp64 sums; rank of seed i = #{j : r_j > r_i or
-// (r_j == r_i and j < i)}, so order[rank_i] = i is the stable descending sort
-// (ties by index), computed without atomics and bit-exactly.
+// per-group reward statistics. One workgroup per group; rewards of the group in LDS; fp64 sums.
+// The order is the stable descending one (ties by index). Up to SORT_MIN seeds it comes from ranks, rank
+// of seed i = #{j : r_j > r_i or (r_j == r_i and j < i)}; past that from a bitonic sort in LDS of
+// 64-bit keys (value, descending, above the index), which are all different, so the result is as unique.
 // ---------------------------------------------------------------------------
 __device__ double block_sum_f64(double v, double* red) {
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -960,26 +960,55 @@ __device__ double block_sum_f64(double v, double* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-// status[0] = 0 when every one of the `count` rewards is finite, else the non-finite code; one
-// workgroup strides over the input (the reward matrix is small: groups x seeds)
-__global__ void __launch_bounds__(256) reward_check_kernel(const float* __restrict__ rw, int64_t count,
-                                                           int32_t bad_code, int32_t* status) {
-  __shared__ int any[4];
+// whether any of the `count` rewards is not finite, seen by the whole workgroup (NT threads)
+template <int NT>
+__device__ bool any_bad(const float* __restrict__ rw, int64_t count) {
+  __shared__ int any[NT / 64];
   int bad = 0;
-  for (int64_t i = threadIdx.x; i < count; i += 256) bad |= !isfinite(rw[i]);
+  int64_t i = threadIdx.x;
+  for (; i + 7 * NT < count; i += 8 * NT) {
+    float f[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) f[u] = rw[i + u * NT];
+#pragma unroll
+    for (int u = 0; u < 8; u++) bad |= !isfinite(f[u]);
+  }
+  for (; i < count; i += NT) bad |= !isfinite(rw[i]);
   bad = __any(bad);
   if ((threadIdx.x & 63) == 0) any[threadIdx.x >> 6] = bad;
   __syncthreads();
-  if (threadIdx.x == 0) status[0] = (any[0] | any[1] | any[2] | any[3]) ? bad_code : 0;
+  int r = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; w++) r |= any[w];
+  return r != 0;
 }
 
-__global__ void __launch_bounds__(256) reward_stats_kernel(const float* __restrict__ rw, int n, float adv_eps,
-                                                           int k, float* mean, float* stdv, float* adv,
-                                                           int32_t* order, int32_t* sel, const int32_t* status) {
-  extern __shared__ float sr[];               // n rewards, then n ints of order
+// status[0] = 0 when every one of the `count` rewards is finite, else the non-finite code; one
+// workgroup strides over the input (the reward matrix is small: groups x seeds)
+__global__ void __launch_bounds__(1024) reward_check_kernel(const float* __restrict__ rw, int64_t count,
+                                                            int32_t bad_code, int32_t* status) {
+  const bool bad = any_bad<1024>(rw, count);
+  if (threadIdx.x == 0) status[0] = bad ? bad_code : 0;
+}
+
+constexpr int SORT_MIN = 128;
+
+// check_count > 0: this launch also checks all rewards (every workgroup for itself) and workgroup 0
+// writes the status; otherwise status, when given, is what the check pass left.
+__global__ void __launch_bounds__(256) reward_stats_kernel(const float* rw, int n, float adv_eps, int k, float* mean,
+                                                           float* stdv, float* adv, int32_t* order, int32_t* sel,
+                                                           int32_t* status, int64_t check_count, int32_t bad_code) {
+  extern __shared__ __attribute__((aligned(16))) char rsm[];
   __shared__ double red[4];
-  if (status && status[0] != 0) return;       // non-finite input: nothing is written
-  int32_t* so = (int32_t*)(sr + n);
+  if (check_count > 0) {
+    const bool bad = any_bad<256>(rw, check_count);
+    if (blockIdx.x == 0 && threadIdx.x == 0) status[0] = bad ? bad_code : 0;
+    if (bad) return;                            // non-finite input: nothing else is written
+  } else if (status && status[0] != 0) {
+    return;
+  }
+  float* sr = (float*)rsm;                      // n rewards
+  int32_t* so = (int32_t*)(rsm + (((size_t)n * 4 + 15) & ~(size_t)15));   // order, or the sort keys
   int g = blockIdx.x;
   const float* r = rw + (int64_t)g * n;
   double part = 0.0;
@@ -999,34 +1028,84 @@ __global__ void __launch_bounds__(256) reward_stats_kernel(const float* __restri
     if (mean) mean[g] = (float)mu;
     if (stdv) stdv[g] = (float)sd;
   }
-  for (int i = threadIdx.x; i < n; i += 256) {
-    float ri = sr[i];
-    if (adv) adv[(int64_t)g * n + i] = sd > 0.0 ? (float)(((double)ri - mu) / (sd + (double)adv_eps)) : 0.0f;
-    int rank = 0;
-    for (int j = 0; j < n; j++) {
-      float rj = sr[j];
-      rank += (rj > ri) || (rj == ri && j < i);
+  if (adv)
+    for (int i = threadIdx.x; i < n; i += 256)
+      adv[(int64_t)g * n + i] = sd > 0.0 ? (float)(((double)sr[i] - mu) / (sd + (double)adv_eps)) : 0.0f;
+  const int top = (k + 1) / 2;
+  if (n <= SORT_MIN) {
+    for (int i = threadIdx.x; i < n; i += 256) {
+      float ri = sr[i];
+      int rank = 0;
+      for (int j = 0; j < n; j++) {
+        float rj = sr[j];
+        rank += (rj > ri) || (rj == ri && j < i);
+      }
+      so[rank] = i;
     }
-    so[rank] = i;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += 256)
+      if (order) order[(int64_t)g * n + i] = so[i];
+    for (int q = threadIdx.x; q < k; q += 256)
+      if (sel) sel[(int64_t)g * k + q] = so[q < top ? q : n - k + q];
+    return;
   }
+  uint64_t* key = (uint64_t*)so;
+  int np = 2;
+  while (np < n) np *= 2;
+  for (int i = threadIdx.x; i < np; i += 256) {
+    uint64_t kk = ~(uint64_t)0;                 // padding sorts last
+    if (i < n) {
+      const uint32_t u = __float_as_uint(sr[i] + 0.0f);            // -0 equals +0
+      const uint32_t asc = u & 0x80000000u ? ~u : u | 0x80000000u;   // ascending as the float is
+      kk = (uint64_t)~asc << 32 | (uint32_t)i;
+    }
+    key[i] = kk;
+  }
+  for (int len = 2; len <= np; len *= 2)
+    for (int st = len / 2; st > 0; st /= 2) {
+      __syncthreads();
+      for (int p = threadIdx.x; p < np / 2; p += 256) {
+        const int i = 2 * p - (p & (st - 1)), j = i + st;   // pair p of this stage
+        const uint64_t a = key[i], b = key[j];
+        if ((a > b) == ((i & len) == 0)) {
+          key[i] = b;
+          key[j] = a;
+        }
+      }
+    }
   __syncthreads();
-  int top = (k + 1) / 2;
   for (int i = threadIdx.x; i < n; i += 256)
-    if (order) order[(int64_t)g * n + i] = so[i];
+    if (order) order[(int64_t)g * n + i] = (int32_t)(uint32_t)key[i];
   for (int q = threadIdx.x; q < k; q += 256)
-    if (sel) sel[(int64_t)g * k + q] = so[q < top ? q : n - k + q];
+    if (sel) sel[(int64_t)g * k + q] = (int32_t)(uint32_t)key[q < top ? q : n - k + q];
 }
 
-hipError_t reward_stats(const float* r, int G, int n, float adv_eps, int k, float* mean, float* stdv,
-                        float* adv, int32_t* order, int32_t* sel, int32_t* status, int32_t bad_code, hipStream_t s) {
+// do [a, a + na) and [b, b + nb) share a byte
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
+hipError_t reward_stats(const float* r, int G, int n, float adv_eps, int k, float* mean, float* stdv, float* adv,
+                        int32_t* order, int32_t* sel, int32_t* status, int32_t bad_code, hipStream_t s) {
   if (G == 0) return hipSuccess;
-  if (status) {
-    reward_check_kernel<<<1, 256, 0, s>>>(r, (int64_t)G * n, bad_code, status);
+  const int64_t count = (int64_t)G * n;
+  const size_t in = (size_t)count * 4;
+  // One launch where every workgroup can afford to look at all rewards (up to 16 K of them, 64 loads per
+  // thread, against a second launch) and no output lies over the rewards, which a workgroup may still
+  // be checking while another writes.
+  const bool shared = overlap(mean, (size_t)G * 4, r, in) || overlap(stdv, (size_t)G * 4, r, in) || overlap(adv, in, r, in) ||
+                      overlap(order, in, r, in) || overlap(sel, (size_t)G * k * 4, r, in) || overlap(status, 4, r, in);
+  const bool fused = status && count <= 16384 && !shared;
+  if (status && !fused) {
+    reward_check_kernel<<<1, 1024, 0, s>>>(r, count, bad_code, status);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  size_t lds = (size_t)n * 8;
-  reward_stats_kernel<<<G, 256, lds, s>>>(r, n, adv_eps, k, mean, stdv, adv, order, sel, status);
+  size_t np = 2;
+  while (np < (size_t)n) np *= 2;
+  const size_t lds = (((size_t)n * 4 + 15) & ~(size_t)15) + (n <= SORT_MIN ? (size_t)n * 4 : np * 8);
+  reward_stats_kernel<<<G, 256, lds, s>>>(r, n, adv_eps, k, mean, stdv, adv, order, sel, status, fused ? count : 0,
+                                          bad_code);
   return hipGetLastError();
 }
 
