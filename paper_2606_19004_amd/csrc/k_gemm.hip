@@ -25,8 +25,9 @@
 //     steps of a k-tile (W after the barrier, A in the other step), and each
 //     wave lowers its issue priority as it advances between barriers, so the
 //     two waves of a SIMD share the matrix pipe instead of one running ahead
-//     and idling at the barrier. Smaller problems use 128 x 128 or 64 x 64
-//     tiles with v_mfma_f32_32x32x16_bf16 and two stages of each.
+//     and idling at the barrier. Smaller problems use 128 x 128 tiles with
+//     a ring of five stages, or 64 x 64 and 32 x 32 tiles whose waves split K
+//     (pick_tile below).
 //   * Epilogue: bias, gate vectors and the RoPE table are staged in LDS per
 //     tile; the gated residual reads of a wave's whole sub-tile are issued at
 //     once.
@@ -201,33 +202,20 @@ __device__ __forceinline__ void sched_step() {
   }
 }
 
-// One MFMA on MS x MS blocks: v_mfma_f32_32x32x16_bf16 (MS = 32) or v_mfma_f32_16x16x32_bf16
-// (MS = 16). Both take one 8-element bf16 fragment per lane for each operand.
-template <int MS> struct Mfma;
-template <> struct Mfma<32> {
-  typedef f32x16 acc_t;
-  static constexpr int KS = 16;   // k depth of one instruction
-  static __device__ __forceinline__ acc_t run(bf16x8 a, bf16x8 b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct Mfma<16> {
-  typedef f32x4 acc_t;
-  static constexpr int KS = 32;
-  static __device__ __forceinline__ acc_t run(bf16x8 a, bf16x8 b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-};
+// One MFMA on a 16 x 16 block, 32 deep: one 8-element bf16 fragment per lane for each operand.
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 
-// MS = MFMA block size (32 or 16); under sustained load with random operands the 16x16x32
-// form delivers more MFMA throughput per watt on this chip.
-// TRI (256 x 256 tiles only): three LDS stages for A and two for W (160 KB), so the activation
-// operand is loaded two k-tiles ahead.
-template <int BM, int BN, int WM, int WN, int EPI, int MS = 32, bool TRI = false>
+// The 16x16x32 MFMA form delivers more throughput per watt than 32x32x16 under sustained load with
+// random operands on this chip.
+// RING = 0 (256-row tiles): three LDS stages for A and two for W (160 KB), so the activation
+// operand is loaded two k-tiles ahead. RING > 0 (128 x 128 tiles): a ring of RING LDS stages of both
+// operands.
+template <int BM, int BN, int WM, int WN, int EPI, int RING = 0>
 __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, int tiles0, int total_tiles) {
-  typedef typename Mfma<MS>::acc_t acc_t;
-  constexpr int NACC = sizeof(acc_t) / 4;              // accumulator registers per block
-  constexpr int KS = Mfma<MS>::KS;
+  constexpr int MS = 16, KS = 32;                      // MFMA block and k depth
+  constexpr bool TRI = RING == 0;
   constexpr int NW = WM * WN;
   constexpr int BK = 64;
   constexpr int WTM = BM / WM, WTN = BN / WN;          // wave tile (m, n)
@@ -256,8 +244,6 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
 
   // buffer resources; rows outside the matrix get an offset beyond num_records -> zeros
   const uint32_t OOB = 0x80000000u;
-  __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)P.A, (short)0, 0x7fffffff, 0x00020000);
-  __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)P.W, (short)0, 0x7fffffff, 0x00020000);
   // a wave-load writes 8 rows x 8 slots (lane -> row lane/8, slot lane%8) and fetches chunk slot ^ f(row)
   const int lrow = lane >> 3;
   uint32_t aoff[A_LOADS], woff[W_LOADS];
@@ -275,9 +261,12 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     int n = n0 + 8 * g + lrow;
     woff[i] = n < P.N ? (uint32_t)((int64_t)n * K * 2 + chunk * 16) : OOB;
   }
-  // TRI layout: [W0][W1][A0][A1][A2]; tile kt uses W stage kt % 2 and A stage kt % 3
-  auto stage_w = [&](int kt) -> char* { return smem + (kt & 1) * W_BYTES; };
-  auto stage_a = [&](int kt) -> char* { return smem + 2 * W_BYTES + (kt % 3) * A_BYTES; };
+  // RING = 0: [W0][W1][A0][A1][A2], tile kt uses W stage kt % 2 and A stage kt % 3; else tile kt uses
+  // stage kt % RING of [W][A] pairs
+  auto stage_w = [&](int kt) -> char* { return smem + (TRI ? (kt & 1) * W_BYTES : (kt % (RING + TRI)) * (A_BYTES + W_BYTES)); };
+  auto stage_a = [&](int kt) -> char* {
+    return smem + (TRI ? 2 * W_BYTES + (kt % 3) * A_BYTES : (kt % (RING + TRI)) * (A_BYTES + W_BYTES) + W_BYTES);
+  };
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const uint64_t pa64 = (uint64_t)P.A, pw64 = (uint64_t)P.W;
   // refills as one burst per operand: offsets carry -1024 i plus a 4 KB bias taken back from the base
@@ -307,25 +296,11 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     for (int i = 0; i < (BW ? 0 : W_LOADS); i++) dma_b128(rw4, sw + (wave_s * W_LOADS + i) * 1024, woffb[i], soff);
     if constexpr (BW) dma_burst<W_LOADS>(rw4, sw + wave_s * W_LOADS * 1024, woffb, soff);
   };
-  auto issue = [&](int kt, int buf) {
-    char* sa = smem + buf * (A_BYTES + W_BYTES);
-    char* sw = sa + A_BYTES;
-    int soff = kt * BK * 2;
-#pragma unroll
-    for (int i = 0; i < A_LOADS; i++)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(sa + (wave * A_LOADS + i) * 1024), 16, aoff[i], soff, 0, 0);
-#pragma unroll
-    for (int i = 0; i < W_LOADS; i++)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr_t)(sw + (wave * W_LOADS + i) * 1024), 16, woff[i], soff, 0, 0);
-  };
-
-  acc_t acc[TI][TJ];
+  f32x4 acc[TI][TJ];
 #pragma unroll
   for (int i = 0; i < TI; i++)
 #pragma unroll
-    for (int j = 0; j < TJ; j++)
-#pragma unroll
-      for (int r = 0; r < NACC; r++) acc[i][j][r] = 0.f;
+    for (int j = 0; j < TJ; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int wm = wave / WN, wn = wave % WN;
   // lane -> (fragment row inside an MS-row block, 8-element k chunk inside a KS step)
@@ -339,9 +314,9 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
   const int wrow0 = (wn * WTN + frow) * 128, arow0 = (wm * WTM + frow) * 128;
   // fragments of k step s, register-double-buffered so step s+1 loads while step s multiplies
   bf16x8 fw[2][TI], fa[2][TJ];
-  auto frags = [&](int buf, int s, int rb) {   // TRI: buf is the k-tile index
-    const char* sa = TRI ? stage_a(buf) : smem + buf * (A_BYTES + W_BYTES);
-    const char* sw = TRI ? stage_w(buf) : sa + A_BYTES;
+  auto frags = [&](int kt, int s, int rb) {
+    const char* sa = stage_a(kt);
+    const char* sw = stage_w(kt);
     const int c = (KS / 8) * s + lkc;
 #pragma unroll
     for (int i = 0; i < TI; i++) fw[rb][i] = *(const bf16x8*)(sw + wrow0 + MS * i * 128 + ((c ^ fwk[i]) << 4));
@@ -349,47 +324,15 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     for (int j = 0; j < TJ; j++) fa[rb][j] = *(const bf16x8*)(sa + arow0 + MS * j * 128 + ((c ^ fak[j]) << 4));
   };
 
-  // One k-tile held in LDS stage `buf`. Every tile but the last ends with the hand-over: wait until
-  // tile kt+1 has landed and every wave is done reading stage `buf`, then, while the last MFMAs of
-  // tile kt run, refill `buf` with tile kt+2 (PH == 0; the next-to-last tile has nothing left to
-  // load, PH == 1) and read the first fragments of tile kt+1. The phases are separate code paths so
-  // that the refill needs no branch (the direct-to-LDS loads can then be interleaved with the MFMAs
-  // instead of stalling every wave behind the barrier), and so that the compiler never merges paths
-  // in front of those MFMAs (at a merge it also waits for the fresh fragment reads).
   // The reads and loads of a k step are spread over its MFMAs: loads over the first half, fragment
   // reads over the first three quarters, leaving the tail of the step to cover their latency.
   constexpr int NM = TI * TJ;
-  auto ktile = [&](int kt, auto ph_c) {
-    constexpr int PH = decltype(ph_c)::value;
-    const int buf = kt & 1;
-#pragma unroll
-    for (int s = 0; s < BK / KS; s++) {
-      const int rb = s & 1;
-      const bool seam = s == BK / KS - 1;
-      if (!seam) {
-        frags(buf, s + 1, rb ^ 1);
-      } else if (PH < 2) {
-        __builtin_amdgcn_s_waitcnt(0);   // tile kt+1 landed and this wave's reads of `buf` are done
-        __syncthreads();                 // ... in every wave: `buf` may be refilled
-        if (PH == 0) issue(kt + 2, buf);
-        frags(buf ^ 1, 0, rb ^ 1);
-      }
-#pragma unroll
-      for (int i = 0; i < TI; i++)
-#pragma unroll
-        for (int j = 0; j < TJ; j++)
-          acc[i][j] = Mfma<MS>::run(fw[rb][i], fa[rb][j], acc[i][j]);
-      if (!seam) sched_step<NM, 0, TI + TJ>();
-      else sched_step<NM, PH == 0 ? A_LOADS + W_LOADS : 0, PH < 2 ? TI + TJ : 0>();
-    }
-  };
-
   // Epilogue inputs (bias, gate vectors, RoPE table) are requested into registers before the last
   // k-tile, so their memory latency is covered by its MFMAs; after the loop they are written to LDS.
   // Tiles whose inputs exceed the register budget (more than one gate row per thread or four table
   // entries per thread) load them after the loop instead.
   constexpr int NT = NW * 64;
-  constexpr int LDS_BYTES = 2 * (A_BYTES + W_BYTES);
+  constexpr int LDS_BYTES = TRI ? 2 * (A_BYTES + W_BYTES) : RING * (A_BYTES + W_BYTES);
   const int rpb = (int)P.cmap.rows_per_batch;
   const int bfirst = m0 / rpb;
   const int nbt = (min(m0 + BM, P.M) - 1) / rpb - bfirst + 1;
@@ -453,7 +396,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
         for (int i = 0; i < TI / 2; i++)
 #pragma unroll
           for (int j = 0; j < TJ; j++)
-            acc[i][j] = Mfma<MS>::run(fw[rb][i], fa[rb][j], acc[i][j]);
+            acc[i][j] = mfma16(fw[rb][i], fa[rb][j], acc[i][j]);
         if (!seam) sched_step<NM / 2, PH <= 1 ? A_LOADS : 0, TI + TJ>();
         else sched_step<NM / 2, PH <= 1 ? W_LOADS : 0, PH < 3 ? TI + TJ : 0>();
         if (seam) __builtin_amdgcn_s_setprio(2);
@@ -462,7 +405,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
         for (int i = TI / 2; i < TI; i++)
 #pragma unroll
           for (int j = 0; j < TJ; j++)
-            acc[i][j] = Mfma<MS>::run(fw[rb][i], fa[rb][j], acc[i][j]);
+            acc[i][j] = mfma16(fw[rb][i], fa[rb][j], acc[i][j]);
       }
     };
     issue_a(0);
@@ -480,41 +423,76 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     ktile3(nk - 1, std::integral_constant<int, 3>());
     __builtin_amdgcn_s_setprio(0);
   } else {
-    issue(0, 0);
-    __builtin_amdgcn_s_waitcnt(0);
+    // All RING stages are filled up front; the hand-over from tile kt to kt + 1 sits before the last
+    // step's MFMAs, whose fragments are in registers: wait until tile kt + 1 has landed (the loads of
+    // the RING - 2 tiles after it stay in flight), barrier, then stage kt % RING, which every wave has
+    // read, takes tile kt + RING. Three to four k-tiles (96-128 KB) are on their way at any time, which
+    // is what covers the memory latency when a CU holds this one workgroup.
+    constexpr int L = A_LOADS + W_LOADS;
+    static_assert(RING <= 1 || (RING - 2) * L <= 15, "the waits below use the low four bits of vmcnt");
+    auto wait_tiles = [&](int n) {   // at most the loads of n tiles in flight, LDS reads done
+      if (n >= RING - 2) __builtin_amdgcn_s_waitcnt(0x0070 | ((RING - 2) * L & 15));
+      else if (n == 2) __builtin_amdgcn_s_waitcnt(0x0070 | (2 * L & 15));
+      else if (n == 1) __builtin_amdgcn_s_waitcnt(0x0070 | L);
+      else __builtin_amdgcn_s_waitcnt(0x0070);
+    };
+    auto step = [&](int kt, auto ph_c) {
+      constexpr int PH = decltype(ph_c)::value;   // 0: refill tile kt + RING; 1: none; 2: last tile
+#pragma unroll
+      for (int s = 0; s < BK / KS; s++) {
+        const int rb = s & 1;
+        const bool seam = s == BK / KS - 1;
+        if (!seam) {
+          frags(kt, s + 1, rb ^ 1);
+        } else if (PH < 2) {
+          wait_tiles(PH == 0 ? RING - 2 : nk - 2 - kt);
+          __syncthreads();
+          if (PH == 0) {
+            issue_a(kt + RING);
+            issue_w(kt + RING);
+          }
+          frags(kt + 1, 0, rb ^ 1);
+        }
+#pragma unroll
+        for (int i = 0; i < TI; i++)
+#pragma unroll
+          for (int j = 0; j < TJ; j++) acc[i][j] = mfma16(fw[rb][i], fa[rb][j], acc[i][j]);
+      }
+    };
+    for (int kt = 0; kt < RING && kt < nk; kt++) {
+      issue_a(kt);
+      issue_w(kt);
+    }
+    if (nk >= RING) __builtin_amdgcn_s_waitcnt(0x0070 | ((RING - 1) * L & 15) | (((RING - 1) * L >> 4) << 14));
+    else wait_tiles(nk - 1);
     __syncthreads();
-    if (nk > 1) issue(1, 1);
     frags(0, 0, 0);
-    for (int kt = 0; kt + 2 < nk; kt++) ktile(kt, std::integral_constant<int, 0>());
-    if (nk >= 2) ktile(nk - 2, std::integral_constant<int, 1>());
+    int kt = 0;
+    for (; kt + RING < nk; kt++) step(kt, std::integral_constant<int, 0>());
+    for (; kt + 1 < nk; kt++) step(kt, std::integral_constant<int, 1>());
     prefetch_epi();
-    ktile(nk - 1, std::integral_constant<int, 2>());
+    step(nk - 1, std::integral_constant<int, 2>());
   }
 
   // ---- epilogue: bias, gate vectors and the RoPE table are staged in LDS once per tile ----
-  // accumulator (i, j), register r = 4 g + q (q = 0..3):
-  //   MS = 32: n = 32 i + 8 g + 4 (lane / 32) + q, m = 32 j + lane % 32
-  //   MS = 16: n = 16 i + 4 (lane / 16) + q,        m = 16 j + lane % 16
-  constexpr int NG = NACC / 4;
-  // MS = 16: blocks i and i + 1 of a row group (32 adjacent columns) are finished
+  // accumulator (i, j), register q: n = 16 i + 4 (lane / 16) + q, m = 16 j + lane % 16
+  // Blocks i and i + 1 of a row group (32 adjacent columns) are finished
   // together and regrouped with v_permlane16_swap, which exchanges lanes 16-31 of one register with
   // lanes 0-15 of another (and 48-63 with 32-47). Lane group g = lane / 16 then holds the 8 adjacent
   // columns 32 p + 16 (g & 1) + 8 (g >> 1) of pair p, stored with one 16-byte store. A CU issues a
   // store of 16 rows x 32 B (the accumulator layout) in ~74 cycles and one of 16 rows x 64 B in ~20,
   // and with 256 stores per tile that issue time, not HBM, bounded the epilogue. The paired layout
   // needs 16-byte aligned output rows; otherwise the accumulator layout is stored as it is.
-  constexpr bool PAIRS = MS == 16;
-  static_assert(!PAIRS || TI % 2 == 0, "the paired store joins blocks 2p and 2p + 1");
-  const bool pairs = PAIRS && (P.N & 7) == 0 && ((uintptr_t)P.C & 15) == 0 &&
+  static_assert(TI % 2 == 0, "the paired store joins blocks 2p and 2p + 1");
+  const bool pairs = (P.N & 7) == 0 && ((uintptr_t)P.C & 15) == 0 &&
                      ((P.cmap.batch_stride | P.cmap.row_stride | P.cmap.offset) & 7) == 0;
   const int pair_col = 16 * (lkc & 1) + 8 * (lkc >> 1);
-  // MS = 16: the residual values of this wave's whole sub-tile (64 registers, free now that the
+  // The residual values of this wave's whole sub-tile (64 registers, free now that the
   // fragment registers are dead) are requested at once, before the staging barriers, so their memory
   // latency is paid once per tile and overlaps the staging. xq[j][p] holds blocks (2p, j) and
   // (2p + 1, j): in the paired layout as loaded (one 16-byte load), else as two 8-byte loads in the
   // accumulator layout.
-  constexpr bool XALL = EPI == EPI_RESID && MS == 16;
-  static_assert(!XALL || PAIRS, "the residual preload assumes paired blocks");
+  constexpr bool XALL = EPI == EPI_RESID;
   uint4 xq[XALL ? TJ : 1][XALL ? TI / 2 : 1];
   if constexpr (XALL) {
     // buffer loads, so that no load sits in a branch: a conditional load leaves the compiler unable to
@@ -592,25 +570,70 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
       if (m >= P.M) continue;
       const RowEpi R = row_epi(P, m);
       const int bt = m / rpb - bfirst;
-      // residual rows: prefetch the 32-column block i+1 while block i is finished
-      uint2 xr[2][4];
-      auto load_x = [&](int i, int slot) {
-#pragma unroll
-        for (int g = 0; g < NG; g++) {
-          int n = n0 + wn * WTN + MS * i + 8 * g + 4 * lkc;
-          if (EPI == EPI_RESID && n < P.N) xr[slot][g] = *(const uint2*)((const u16*)P.C + R.off + n);
-        }
-      };
-      if (EPI == EPI_RESID && !XALL) load_x(0, 0);
 #pragma unroll
       for (int i = 0; i < TI; i++) {
-        if (EPI == EPI_RESID && !XALL && i + 1 < TI) load_x(i + 1, (i + 1) & 1);
+        int nl = wn * WTN + MS * i + 4 * lkc;   // column inside the tile
+        int n = n0 + nl;
+        if (n >= P.N) continue;
+        float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+        float4 bv = *(const float4*)(s_bias + nl);
+        v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
+        if (EPI == EPI_GELU) {
 #pragma unroll
-        for (int g = 0; g < NG; g++) {
-          int nl = wn * WTN + MS * i + 8 * g + 4 * lkc;   // column inside the tile
-          int n = n0 + nl;
-          if (n >= P.N) continue;
-          float v[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+          for (int q = 0; q < 4; q++) v[q] = gelu_tanh_f(v[q]);
+        }
+        if (EPI == EPI_RESID) {
+          float4 gv = STAGED ? *(const float4*)(s_gate + bt * BN + nl) : *(const float4*)(P.gate + R.gate + n);
+          const uint4 xx = xq[j][i >> 1];
+          const uint2 u = (i & 1) ? make_uint2(xx.z, xx.w) : make_uint2(xx.x, xx.y);
+          v[0] = fmaf(gv.x, v[0], __uint_as_float(u.x << 16));
+          v[1] = fmaf(gv.y, v[1], __uint_as_float(u.x & 0xffff0000u));
+          v[2] = fmaf(gv.z, v[2], __uint_as_float(u.y << 16));
+          v[3] = fmaf(gv.w, v[3], __uint_as_float(u.y & 0xffff0000u));
+        }
+        if (EPI == EPI_QKV && rope_on && n < rope_cols) {
+          int dd = n & (head_dim - 1);
+          int hh = head_dim >> 1;
+          int pos = dd < hh ? R.rpos : R.cpos;
+          int pr = (dd & (hh - 1)) >> 1;
+          int ti = (pos * (head_dim >> 2) + pr) * 2;
+          float4 t = STAGED ? *(const float4*)(s_rope + ti) : *(const float4*)(P.rope_tab + ti);
+          float a0 = v[0], b0 = v[1], a1 = v[2], b1 = v[3];
+          v[0] = a0 * t.x - b0 * t.y;
+          v[1] = a0 * t.y + b0 * t.x;
+          v[2] = a1 * t.z - b1 * t.w;
+          v[3] = a1 * t.w + b1 * t.z;
+        }
+        store4<u16>((u16*)P.C + R.off + n, v);
+      }
+    }
+  };
+  // The paired store: the same arithmetic per accumulator block as store_tile, then the regrouping
+  // swap on the packed bf16 pairs and one 16-byte store per pair of blocks. The residual values arrive
+  // in the paired layout and go through the same swap (it is its own inverse) before use.
+  auto store_pairs = [&](auto staged_c) {
+    constexpr bool STAGED = decltype(staged_c)::value;
+#pragma unroll
+    for (int j = 0; j < TJ; j++) {
+      const int m = m0 + wm * WTM + MS * j + frow;
+      if (m >= P.M) continue;   // the swap partners (lanes l and l ^ 16) share the row m
+      const RowEpi R = row_epi(P, m);
+      const int bt = m / rpb - bfirst;
+#pragma unroll
+      for (int p = 0; p < TI / 2; p++) {
+        uint4 xr = make_uint4(0u, 0u, 0u, 0u);
+        if constexpr (XALL) {
+          xr = xq[j][p];
+          swap16(xr.x, xr.z);
+          swap16(xr.y, xr.w);
+        }
+        uint32_t w[2][2];
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          const int i = 2 * p + e;
+          const int nl = wn * WTN + MS * i + 4 * lkc;   // column inside the tile
+          const int n = n0 + nl;
+          float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
           float4 bv = *(const float4*)(s_bias + nl);
           v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
           if (EPI == EPI_GELU) {
@@ -618,16 +641,14 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
             for (int q = 0; q < 4; q++) v[q] = gelu_tanh_f(v[q]);
           }
           if (EPI == EPI_RESID) {
-            float4 gv = STAGED ? *(const float4*)(s_gate + bt * BN + nl) : *(const float4*)(P.gate + R.gate + n);
-            uint2 u = xr[i & 1][g];
-            if constexpr (XALL) {
-              const uint4 q = xq[j][i >> 1];
-              u = (i & 1) ? make_uint2(q.z, q.w) : make_uint2(q.x, q.y);
-            }
-            v[0] = fmaf(gv.x, v[0], __uint_as_float(u.x << 16));
-            v[1] = fmaf(gv.y, v[1], __uint_as_float(u.x & 0xffff0000u));
-            v[2] = fmaf(gv.z, v[2], __uint_as_float(u.y << 16));
-            v[3] = fmaf(gv.w, v[3], __uint_as_float(u.y & 0xffff0000u));
+            float4 gv = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (STAGED) gv = *(const float4*)(s_gate + bt * BN + nl);
+            else if (n < P.N) gv = *(const float4*)(P.gate + R.gate + n);
+            const uint32_t u0 = e ? xr.z : xr.x, u1 = e ? xr.w : xr.y;
+            v[0] = fmaf(gv.x, v[0], __uint_as_float(u0 << 16));
+            v[1] = fmaf(gv.y, v[1], __uint_as_float(u0 & 0xffff0000u));
+            v[2] = fmaf(gv.z, v[2], __uint_as_float(u1 << 16));
+            v[3] = fmaf(gv.w, v[3], __uint_as_float(u1 & 0xffff0000u));
           }
           if (EPI == EPI_QKV && rope_on && n < rope_cols) {
             int dd = n & (head_dim - 1);
@@ -642,75 +663,13 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
             v[2] = a1 * t.z - b1 * t.w;
             v[3] = a1 * t.w + b1 * t.z;
           }
-          store4<u16>((u16*)P.C + R.off + n, v);
+          w[e][0] = pack_bf16x2(v[0], v[1]);
+          w[e][1] = pack_bf16x2(v[2], v[3]);
         }
-      }
-    }
-  };
-  // The paired store: the same arithmetic per accumulator block as store_tile, then the regrouping
-  // swap on the packed bf16 pairs and one 16-byte store per pair of blocks. The residual values arrive
-  // in the paired layout and go through the same swap (it is its own inverse) before use.
-  auto store_pairs = [&](auto staged_c) {
-    constexpr bool STAGED = decltype(staged_c)::value;
-    if constexpr (PAIRS) {
-#pragma unroll
-      for (int j = 0; j < TJ; j++) {
-        const int m = m0 + wm * WTM + MS * j + frow;
-        if (m >= P.M) continue;   // the swap partners (lanes l and l ^ 16) share the row m
-        const RowEpi R = row_epi(P, m);
-        const int bt = m / rpb - bfirst;
-#pragma unroll
-        for (int p = 0; p < TI / 2; p++) {
-          uint4 xr = make_uint4(0u, 0u, 0u, 0u);
-          if constexpr (XALL) {
-            xr = xq[j][p];
-            swap16(xr.x, xr.z);
-            swap16(xr.y, xr.w);
-          }
-          uint32_t w[2][2];
-#pragma unroll
-          for (int e = 0; e < 2; e++) {
-            const int i = 2 * p + e;
-            const int nl = wn * WTN + MS * i + 4 * lkc;   // column inside the tile
-            const int n = n0 + nl;
-            float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-            float4 bv = *(const float4*)(s_bias + nl);
-            v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
-            if (EPI == EPI_GELU) {
-#pragma unroll
-              for (int q = 0; q < 4; q++) v[q] = gelu_tanh_f(v[q]);
-            }
-            if (EPI == EPI_RESID) {
-              float4 gv = make_float4(0.f, 0.f, 0.f, 0.f);
-              if (STAGED) gv = *(const float4*)(s_gate + bt * BN + nl);
-              else if (n < P.N) gv = *(const float4*)(P.gate + R.gate + n);
-              const uint32_t u0 = e ? xr.z : xr.x, u1 = e ? xr.w : xr.y;
-              v[0] = fmaf(gv.x, v[0], __uint_as_float(u0 << 16));
-              v[1] = fmaf(gv.y, v[1], __uint_as_float(u0 & 0xffff0000u));
-              v[2] = fmaf(gv.z, v[2], __uint_as_float(u1 << 16));
-              v[3] = fmaf(gv.w, v[3], __uint_as_float(u1 & 0xffff0000u));
-            }
-            if (EPI == EPI_QKV && rope_on && n < rope_cols) {
-              int dd = n & (head_dim - 1);
-              int hh = head_dim >> 1;
-              int pos = dd < hh ? R.rpos : R.cpos;
-              int pr = (dd & (hh - 1)) >> 1;
-              int ti = (pos * (head_dim >> 2) + pr) * 2;
-              float4 t = STAGED ? *(const float4*)(s_rope + ti) : *(const float4*)(P.rope_tab + ti);
-              float a0 = v[0], b0 = v[1], a1 = v[2], b1 = v[3];
-              v[0] = a0 * t.x - b0 * t.y;
-              v[1] = a0 * t.y + b0 * t.x;
-              v[2] = a1 * t.z - b1 * t.w;
-              v[3] = a1 * t.w + b1 * t.z;
-            }
-            w[e][0] = pack_bf16x2(v[0], v[1]);
-            w[e][1] = pack_bf16x2(v[2], v[3]);
-          }
-          swap16(w[0][0], w[1][0]);
-          swap16(w[0][1], w[1][1]);
-          const int c = n0 + wn * WTN + 32 * p + pair_col;
-          if (c < P.N) *(uint4*)((u16*)P.C + R.off + c) = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
-        }
+        swap16(w[0][0], w[1][0]);
+        swap16(w[0][1], w[1][1]);
+        const int c = n0 + wn * WTN + 32 * p + pair_col;
+        if (c < P.N) *(uint4*)((u16*)P.C + R.off + c) = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
       }
     }
   };
@@ -728,28 +687,164 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
 #endif
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int MS, bool TRI = false>
-static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s) {
-  int tiles[2] = {0, 0};
-  for (int i = 0; i < pr.nprob; i++)
-    if (pr.p[i].M > 0 && pr.p[i].N > 0) tiles[i] = cdiv(pr.p[i].M, BM) * cdiv(pr.p[i].N, BN);
-  int total = tiles[0] + tiles[1];
-  if (total == 0) return hipSuccess;
-  size_t lds = TRI ? (size_t)(2 * BN + 3 * BM) * 64 * 2 : 2 * (size_t)(BM + BN) * 64 * 2;
-  // The dynamic-LDS limit is raised once per device and kernel instance. Two host threads may reach
-  // this at once; setting the attribute twice is harmless, and the flag is an atomic so the check
-  // itself is race-free.
-  static std::atomic<bool> attr_set[64] = {};
+// buffer descriptor of a tile's operand rows, starting at the tile's first row
+__device__ __forceinline__ u32x4_t tile_rsrc(const void* p) {
+  const uint64_t u = (uint64_t)p;
+  return u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(u >> 32) & 0xffffu)), 0x7fffffffu, 0x00020000u};
+}
+
+// T x T tile (T = 32 or 64) for problems with few tiles: each of a workgroup's 4 waves takes every 4th
+// 64-deep k slice of the whole tile, with two LDS stages of its own (2 x T x 256 bytes), so no barrier
+// stands in the k loop and two slices per wave are in flight; the four partial tiles meet in LDS and
+// are summed in a fixed order, each wave finishing the 16 features x T rows (T = 64) or the 16 x 16
+// block (T = 32) of its index. Small problems are bound by the latency of the chain of k-tiles, which
+// this divides by four. Offsets are relative to the tile's first row; rows past the end repeat the last.
+template <int T, int EPI>
+__global__ void __launch_bounds__(256) gemm_bf16_ksplit_kernel(GemmPair pr, int tiles0, int total_tiles) {
+  constexpr int NB = T / 16, LD = T / 8, STAGE = 2 * T * 128;
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int per = gridDim.x >> 3;
+  const int t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (t >= total_tiles) return;
+  const int pi = t < tiles0 ? 0 : 1;
+  const GemmProblem P = pr.p[pi];
+  int tm, tn;
+  tile_coords(pi == 0 ? t : t - tiles0, cdiv(P.M, T), cdiv(P.N, T), tm, tn);
+  const int m0 = tm * T, n0 = tn * T;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t a0 = row_offset(P.amap, m0);
+  const u32x4_t ra = tile_rsrc((const u16*)P.A + a0);
+  const u32x4_t rw = tile_rsrc((const u16*)P.W + (int64_t)n0 * P.K);
+  uint32_t aoff[LD], woff[LD];
+#pragma unroll
+  for (int i = 0; i < LD; i++) {
+    const int r = 8 * i + (lane >> 3);
+    const uint32_t chunk = ((lane & 7) ^ swz(r)) * 16;
+    aoff[i] = (uint32_t)((row_offset(P.amap, min(m0 + r, P.M - 1)) - a0) * 2) + chunk;
+    woff[i] = (uint32_t)(min(n0 + r, P.N - 1) - n0) * (uint32_t)P.K * 2u + chunk;
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem + wave * 2 * STAGE;
+  auto issue = [&](int slice, int st) {
+    const uint32_t base = lds0 + st * STAGE;
+#pragma unroll
+    for (int i = 0; i < LD; i++) {
+      dma_b128(ra, base + i * 1024, aoff[i], slice * 128);
+      dma_b128(rw, base + T * 128 + i * 1024, woff[i], slice * 128);
+    }
+  };
+  const int r16 = lane & 15, kq = lane >> 4;
+  f32x4 acc[NB][NB];
+#pragma unroll
+  for (int i = 0; i < NB; i++)
+#pragma unroll
+    for (int j = 0; j < NB; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nk = P.K / 64;
+  if (wave < nk) issue(wave, 0);
+  if (wave + 4 < nk) issue(wave + 4, 1);
+  int st = 0;
+  for (int kt = wave; kt < nk; kt += 4) {
+    // this wave's slice kt has landed (the 2 LD loads of its next slice may be in flight)
+    if (kt + 4 >= nk) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (LD == 4) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    const char* sa = smem + wave * 2 * STAGE + st * STAGE;
+    const char* sw = sa + T * 128;
+    bf16x8 fw[2][NB], fa[2][NB];
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+      for (int i = 0; i < NB; i++) {
+        const int r = 16 * i + r16;
+        fw[s][i] = *(const bf16x8*)(sw + r * 128 + (((4 * s + kq) ^ swz(r)) << 4));
+        fa[s][i] = *(const bf16x8*)(sa + r * 128 + (((4 * s + kq) ^ swz(r)) << 4));
+      }
+    if (kt + 8 < nk) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the fragments are in registers: the stage is free
+      issue(kt + 8, st);
+    }
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+      for (int i = 0; i < NB; i++)
+#pragma unroll
+        for (int j = 0; j < NB; j++) acc[i][j] = mfma16(fw[s][i], fa[s][j], acc[i][j]);
+    st ^= 1;
+  }
+  __syncthreads();   // every wave's loads have landed and been read
+  f32x4* part = (f32x4*)smem;   // [block][wave][lane]
+#pragma unroll
+  for (int i = 0; i < NB; i++)
+#pragma unroll
+    for (int j = 0; j < NB; j++) part[((NB * i + j) * 4 + wave) * 64 + lane] = acc[i][j];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NB * NB / 4; q++) {
+    const int blk = wave * (NB * NB / 4) + q, i = blk / NB, j = blk % NB;
+    f32x4 c = part[(blk * 4) * 64 + lane];
+#pragma unroll
+    for (int g = 1; g < 4; g++) {
+      const f32x4 p = part[(blk * 4 + g) * 64 + lane];
+#pragma unroll
+      for (int r = 0; r < 4; r++) c[r] += p[r];
+    }
+    const int m = m0 + 16 * j + r16, n = n0 + 16 * i + 4 * kq;
+    if (m < P.M && n < P.N) {
+      float v[4] = {c[0], c[1], c[2], c[3]};
+      epilogue4<EPI, u16, u16>(P, row_epi(P, m), n, v);
+    }
+  }
+#endif
+}
+
+// Raises a kernel's dynamic-LDS limit once per device and kernel instance (the flags belong to it).
+// Two host threads may reach this at once; setting the attribute twice is harmless, and the flags are
+// atomics so the check itself is race-free.
+static hipError_t allow_lds(const void* kernel, size_t lds, std::atomic<bool>* attr_set) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
   if (lds > 65536 && (dev < 0 || dev >= 64 || !attr_set[dev].load(std::memory_order_acquire))) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, MS, TRI>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64) attr_set[dev].store(true, std::memory_order_release);
   }
-  int grid = 8 * cdiv(total, 8);
-  gemm_bf16_kernel<BM, BN, WM, WN, EPI, MS, TRI><<<grid, WM * WN * 64, lds, s>>>(pr, tiles[0], total);
+  return hipSuccess;
+}
+
+// tiles of each problem of a pair
+static int count_tiles(const GemmPair& pr, int bm, int bn, int* tiles) {
+  int total = 0;
+  for (int i = 0; i < 2; i++) {
+    tiles[i] = i < pr.nprob && pr.p[i].M > 0 && pr.p[i].N > 0 ? cdiv(pr.p[i].M, bm) * cdiv(pr.p[i].N, bn) : 0;
+    total += tiles[i];
+  }
+  return total;
+}
+
+template <int T, int EPI>
+static hipError_t launch_ksplit(const GemmPair& pr, hipStream_t s) {
+  int tiles[2];
+  const int total = count_tiles(pr, T, T, tiles);
+  if (total == 0) return hipSuccess;
+  constexpr size_t lds = (size_t)16 * T * 128;
+  static std::atomic<bool> attr_set[64] = {};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_bf16_ksplit_kernel<T, EPI>), lds, attr_set);
+  if (e != hipSuccess) return e;
+  gemm_bf16_ksplit_kernel<T, EPI><<<8 * cdiv(total, 8), 256, lds, s>>>(pr, tiles[0], total);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN, int EPI, int RING = 0>
+static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s) {
+  int tiles[2];
+  const int total = count_tiles(pr, BM, BN, tiles);
+  if (total == 0) return hipSuccess;
+  constexpr size_t lds = RING == 0 ? (size_t)(2 * BN + 3 * BM) * 64 * 2 : RING * (size_t)(BM + BN) * 64 * 2;
+  static std::atomic<bool> attr_set[64] = {};
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING>), lds, attr_set);
+  if (e != hipSuccess) return e;
+  gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING><<<8 * cdiv(total, 8), WM * WN * 64, lds, s>>>(pr, tiles[0], total);
   return hipGetLastError();
 }
 
@@ -767,56 +862,61 @@ static int cu_count() {
   return n;
 }
 
+// Which tile a problem pair takes, from the estimated time (us) of its rounds of workgroups. A CU takes
+// operand tiles in at about 54 KB/us whatever the tile, so a k-tile costs in proportion to its bytes
+// (1.2 us for 256 x 256, 0.59 for 128 x 128, 0.30 for 64 x 64; 32 x 32 runs two workgroups per CU), on
+// top of a fixed cost per tile (prologue, epilogue). Measured at hidden 3072, one seed at 512x512
+// (1024 + 256 rows; us for 32 / 64 / 128 / 256 tiles): out-projection 93 / 77 / 39 / 71, MLP down
+// 331 / 218 / 124 / 230, QKV 258 / 197 / 104 / 74; at 256 + 64 rows: out-projection 32 / 25 / 36 / 70;
+// at hidden 320, 286 + 74 rows: 6.7 / 9.7 / 10 / 18. 256 x 192 tiles for all rows take 0.85-0.88
+// of a 256 x 256 round (17% more operand bytes per flop) and win where they fill a round that 256 x 256
+// tiles leave part empty (QKV of one seed, 240 tiles against 180: 65 against 74 us); a text problem's own
+// launch of them, after the image rows' whole rounds, takes 0.83.
+enum Tile { TILE_32, TILE_64, TILE_128, TILE_192, TILE_256, TILE_256_192 };
+static Tile pick_tile(const GemmPair& pr) {
+  int t[2];
+  const int64_t cus = cu_count();
+  const double kt = pr.p[0].K / 64;
+  auto rounds = [&](int64_t tiles, int64_t slots) { return (double)((tiles + slots - 1) / slots); };
+  const double r256 = 1.2 * kt + 14.0;
+  double best = rounds(count_tiles(pr, 256, 256, t), cus) * r256;
+  Tile pick = TILE_256;
+  // image and text rows as two launches, the text rows on 256 x 192 tiles: with 4096 text rows and 3072 or
+  // 9216 output features those divide into whole rounds
+  if (t[0] > 0 && t[1] > 0) {
+    const int64_t t0 = t[0];
+    count_tiles(pr, 256, 192, t);
+    const double c = (rounds(t0, cus) + 0.83 * rounds(t[1], cus)) * r256;
+    if (c < best) best = c, pick = TILE_256_192;
+  }
+  auto consider = [&](Tile tile, double cost) {
+    if (cost < best) best = cost, pick = tile;
+  };
+  consider(TILE_192, rounds(count_tiles(pr, 256, 192, t), cus) * 0.87 * r256);
+  consider(TILE_128, rounds(count_tiles(pr, 128, 128, t), cus) * (0.59 * kt + 7.0));
+  consider(TILE_64, rounds(count_tiles(pr, 64, 64, t), cus) * (0.30 * kt + 7.0));
+  consider(TILE_32, rounds(count_tiles(pr, 32, 32, t), 2 * cus) * (0.22 * kt + 3.0));
+  return pick;
+}
+
 template <int EPI>
 static hipError_t dispatch_bf16(const GemmPair& pr, hipStream_t s) {
-  int maxn = 0;
-  int64_t big_tiles = 0;
-  for (int i = 0; i < pr.nprob; i++) {
-    maxn = std::max(maxn, pr.p[i].N);
-    big_tiles += (int64_t)cdiv(pr.p[i].M, 256) * cdiv(pr.p[i].N, 256);
-  }
-  if (maxn <= 64) return launch_bf16<64, 64, 2, 2, EPI, 32>(pr, s);
-  // 128 x 128 tiles (4 waves, two workgroups per CU) or 256 x 256 tiles (8 waves, one per CU): the
-  // one with fewer estimated rounds, a round of 2 x CUs small tiles costing C128 of a large round
-  // (a quarter of the flops per tile, at lower MFMA efficiency)
-  {
-    constexpr double C128 = 0.71;
-    const int64_t cus = cu_count();
-    int64_t small_tiles = 0;
-    for (int i = 0; i < pr.nprob; i++) small_tiles += (int64_t)cdiv(pr.p[i].M, 128) * cdiv(pr.p[i].N, 128);
-    const double big = (double)((big_tiles + cus - 1) / cus);
-    const double small = C128 * (double)((small_tiles + 2 * cus - 1) / (2 * cus));
-    if (small < big) return launch_bf16<128, 128, 2, 2, EPI, 32>(pr, s);
-  }
-  // large problems: 8 waves of 64x128 on 16x16x32 MFMAs (measured 3-7% faster than 32x32x16 here),
-  // with three A stages, so the activation rows are requested two k-tiles ahead (in the denoise step
-  // every block's weights and most activation panels arrive cold from HBM).
-  //
-  // Every CU runs one 256 x 256 tile at a time, so a launch takes ceil(tiles / CUs) rounds of equal
-  // length. When the image and text problems together leave the last round partly empty, the text
-  // problem can instead run as a second launch of 256 x 192 tiles: with 4096 text rows and 3072 or
-  // 9216 output features that divides into whole rounds. A round of 256 x 192 tiles was measured at
-  // 0.80-0.83 of a 256 x 256 round (17% more operand bytes per flop than the 0.75 of the flops), so
-  // the split is taken when ceil(t_img / CUs) + 0.83 ceil(t_txt' / CUs) rounds beat
-  // ceil((t_img + t_txt) / CUs).
-  if (pr.nprob == 2 && pr.p[0].M > 0 && pr.p[1].M > 0 && pr.p[0].N > 0 && pr.p[1].N > 0) {
-    const int64_t cus = cu_count();
-    const int64_t t0 = (int64_t)cdiv(pr.p[0].M, 256) * cdiv(pr.p[0].N, 256);
-    const int64_t t1 = (int64_t)cdiv(pr.p[1].M, 256) * cdiv(pr.p[1].N, 256);
-    const int64_t t1n = (int64_t)cdiv(pr.p[1].M, 256) * cdiv(pr.p[1].N, 192);
-    const double merged = (double)((t0 + t1 + cus - 1) / cus);
-    const double split = (double)((t0 + cus - 1) / cus) + 0.83 * (double)((t1n + cus - 1) / cus);
-    if (split < merged) {
+  switch (pick_tile(pr)) {
+    case TILE_32: return launch_ksplit<32, EPI>(pr, s);
+    case TILE_64: return launch_ksplit<64, EPI>(pr, s);
+    case TILE_128: return launch_bf16<128, 128, 2, 4, EPI, 5>(pr, s);
+    case TILE_192: return launch_bf16<256, 192, 4, 2, EPI>(pr, s);
+    case TILE_256: return launch_bf16<256, 256, 4, 2, EPI>(pr, s);
+    case TILE_256_192: {
       GemmPair a = pr, b = pr;
       a.nprob = 1;
       b.nprob = 1;
       b.p[0] = pr.p[1];
-      hipError_t e = launch_bf16<256, 256, 4, 2, EPI, 16, true>(a, s);
-      if (e != hipSuccess) return e;
-      return launch_bf16<256, 192, 4, 2, EPI, 16, true>(b, s);
+      hipError_t e = launch_bf16<256, 256, 4, 2, EPI>(a, s);
+      return e != hipSuccess ? e : launch_bf16<256, 192, 4, 2, EPI>(b, s);
     }
   }
-  return launch_bf16<256, 256, 4, 2, EPI, 16, true>(pr, s);
+  return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------
@@ -834,13 +934,6 @@ __device__ __forceinline__ void mfma_k16(float4 w, float4 a, f32x4& c) {
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, a.y, c, 0, 0, 0);
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, a.z, c, 0, 0, 0);
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, a.w, c, 0, 0, 0);
-}
-
-// buffer descriptor of a tile's operand rows, starting at the tile's first row
-__device__ __forceinline__ u32x4_t tile_rsrc(const float* p) {
-  const uint64_t u = (uint64_t)p;
-  return u32x4_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u),
-                 (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(u >> 32) & 0xffffu)), 0x7fffffffu, 0x00020000u};
 }
 
 // 64 x 64 tile, 4 waves of 32 x 32, 32-deep k-tiles in a ring of three LDS stages (48 KB, three

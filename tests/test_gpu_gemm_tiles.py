@@ -1,0 +1,77 @@
+"""Every bf16 GEMM tile shape at its edges, with integer operands whose results are exact in any order.
+
+Through the patch embedding (plain GEMM): rows and features around the 32, 64 and 128 tile edges and one
+to many 64-deep k-tiles, so that each of the four waves of a split-K workgroup gets none, one or several
+slices and the 128 x 128 ring is shorter than, as long as and longer than its five stages. Which tile a
+shape takes is the library's choice; the sizes below lie in the ranges of all of them (few rows: 32 x 32;
+hundreds: 64 x 64 and 128 x 128; thousands: 256-row tiles). A block then runs every epilogue on the
+small tiles, two streams in one launch, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import seeded_inputs as si
+from oracle import dit_oracle as O
+from tests.conftest import weights_f64
+from tests.gpu_util import block_cfg, dev, host64, rel_err, upload_block
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def d():
+    from paper_2606_19004_amd import ditstep
+    return ditstep
+
+
+def patch(d, b, n, hidden, k, skew=0):
+    g = torch.Generator(device="cuda").manual_seed(b * n + hidden + k)
+    c = d.block_config(hidden, hidden // 64, 64, 4 * hidden, n, 0, 1, n)
+    # at most 60 nonzero +-1 entries per row keep every partial sum an integer below 2^8
+    nz = min(60, k)
+    pos = torch.rand(b * n, k, generator=g, device="cuda").argsort(1)[:, :nz]
+    lat = torch.zeros(b * n, k, device="cuda").scatter_(1, pos, torch.randint(0, 2, (b * n, nz), generator=g, device="cuda") * 2.0 - 1)
+    w = torch.randint(-1, 2, (hidden * k + skew,), generator=g, device="cuda").to(torch.bfloat16)[skew:].view(hidden, k)
+    bias = torch.randint(-2, 3, (hidden + skew,), generator=g, device="cuda").to(torch.bfloat16)[skew:]
+    z = torch.zeros(2 * hidden * max(hidden, 256), dtype=torch.bfloat16, device="cuda")
+    sw = {nm: z for nm in ("t1_w", "t1_b", "t2_w", "t2_b", "fmod_w", "fmod_b", "fout_w", "fout_b")}
+    sw["in_w"], sw["in_b"] = w, bias
+    x = torch.full((b, n, hidden), 0.5, dtype=torch.bfloat16, device="cuda")
+    d.dit_patch_embed(c, d.step_weights(sw), lat.view(b, n, k), x, d.workspace(2 * b * n * k + 256))
+    want = lat.double() @ w.double().t() + bias.double()
+    assert want.abs().max() <= 256
+    assert torch.equal(x.double().view(-1, hidden), want)
+
+
+@pytest.mark.parametrize("k", [64, 128, 256, 320, 384, 576, 1280])
+@pytest.mark.parametrize("rows,hidden", [(1, 64), (31, 64), (33, 128), (65, 320), (127, 448)])
+def test_small_tiles_exact(d, rows, hidden, k):
+    patch(d, 1, rows, hidden, k)
+
+
+@pytest.mark.parametrize("k", [64, 192, 256, 320, 384, 1024])
+@pytest.mark.parametrize("b,n,hidden", [(2, 161, 3072), (3, 427, 1536), (5, 205, 3008), (1, 1024, 3072), (4, 1000, 2048)])
+def test_larger_tiles_exact(d, b, n, hidden, k):
+    patch(d, b, n, hidden, k)
+
+
+def test_weights_at_8_byte_alignment(d):
+    for rows, hidden, k in ((33, 128, 256), (1281, 1536, 1024), (300, 3072, 512)):
+        patch(d, 1, rows, hidden, k, skew=4)
+
+
+# every epilogue with both streams in one launch: 32 x 32, 64 x 64 and 128 x 128 tiles by size
+@pytest.mark.parametrize("hidden,hd,gh,gw,n_txt,b", [(128, 64, 3, 11, 1, 2), (576, 64, 13, 9, 45, 2), (1024, 128, 19, 21, 90, 2),
+                                                     (1024, 64, 9, 7, 130, 1)])
+def test_block_small_tiles(d, hidden, hd, gh, gw, n_txt, b):
+    cfg = si.Shape("tiles", hidden, hidden // hd, hd, gh, gw, n_txt, b)
+    inp = si.block_inputs(cfg)
+    w = upload_block(inp["weights"], "bf16")
+    c = block_cfg(d, cfg)
+    xi, xt = dev(inp["x_img"], "bf16"), dev(inp["x_txt"], "bf16")
+    d.dit_block_forward(c, d.block_weights(w["img"], w["txt"]), dev(inp["temb"]), xi, xt,
+                        d.workspace(d.dit_block_workspace_bytes(c, b)))
+    ri, rt = O.block_forward(cfg, weights_f64(inp["weights"], "bf16"), inp["temb"].astype(np.float64),
+                             si.as_f64(inp["x_img"], "bf16"), si.as_f64(inp["x_txt"], "bf16"))
+    assert rel_err(host64(xi), ri) <= 2e-2
+    assert rel_err(host64(xt), rt) <= 2e-2
