@@ -159,12 +159,13 @@ RowMap stream_rows(int64_t n, int64_t cols) { return RowMap{std::max<int64_t>(n,
 
 // out = W act(in) + b with act = SiLU when silu_in: MFMA (hi/lo split) for bf16
 // weights, VALU for fp32 weights (which first writes SiLU(in) to silu_buf)
+// (split_ready: xs holds the split input already, bf16 only; rope: a table to fill beside it, bf16 only)
 dit_status run_gemv(const dit_block_config* c, GemvArgs g, bool silu_in, float* silu_buf, void* xs,
-                    const char* name, hipStream_t s) {
+                    const char* name, hipStream_t s, bool split_ready = false, const RopeArgs& rope = RopeArgs{}) {
   double flops = 2.0 * g.nstreams * g.B * (double)g.N * g.K;
   double bytes = (double)g.nstreams * g.N * (double)g.K * esize(c->dtype);
   if (c->dtype == DIT_BF16) {
-    TIMED(name, flops, bytes, s, gemv_bf16(g, (u16*)xs, silu_in ? 1 : 0, s));
+    TIMED(name, flops, bytes, s, gemv_bf16(g, (u16*)xs, split_ready ? GEMV_SPLIT : silu_in ? GEMV_SILU : GEMV_RAW, rope, s));
     return DIT_OK;
   }
   if (silu_in) {
@@ -177,7 +178,7 @@ dit_status run_gemv(const dit_block_config* c, GemvArgs g, bool silu_in, float* 
 
 // mod[s][b][6D] = W_mod[s] SiLU(temb[b]) + b_mod[s]
 dit_status run_modulation(const dit_block_config* c, const dit_block_weights* w, int B, const float* temb,
-                          char* ws, const BlockWs& L, hipStream_t s) {
+                          char* ws, const BlockWs& L, const RopeArgs& rope, hipStream_t s) {
   const int D = c->hidden;
   float* mod = (float*)(ws + L.mod);
   GemvArgs g{};
@@ -193,7 +194,7 @@ dit_status run_modulation(const dit_block_config* c, const dit_block_weights* w,
   g.K = D;
   g.B = B;
   g.nstreams = 2;
-  return run_gemv(c, g, true, (float*)(ws + L.silu), ws + L.xs, "mod_gemv", s);
+  return run_gemv(c, g, true, (float*)(ws + L.silu), ws + L.xs, "mod_gemv", s, false, rope);
 }
 
 // The modulation depends only on the timestep embedding, which every block of a step shares, so the
@@ -201,7 +202,8 @@ dit_status run_modulation(const dit_block_config* c, const dit_block_weights* w,
 // dst + i * 2 B 6D holds block i's mod[s][b][6D], laid out as in run_modulation.
 constexpr int MOD_GROUP = GEMV_SLOTS / 2;
 dit_status run_modulation_group(const dit_block_config* c, const dit_block_weights* blocks, int n, int B,
-                                const float* temb, float* dst, char* ws, const BlockWs& L, hipStream_t s) {
+                                const float* temb, float* dst, char* ws, const BlockWs& L, bool split_ready,
+                                hipStream_t s) {
   const int D = c->hidden;
   GemvArgs g{};
   for (int i = 0; i < n; i++)
@@ -217,7 +219,7 @@ dit_status run_modulation_group(const dit_block_config* c, const dit_block_weigh
   g.K = D;
   g.B = B;
   g.nstreams = 2 * n;
-  return run_gemv(c, g, true, (float*)(ws + L.silu), ws + L.xs, "mod_gemv", s);
+  return run_gemv(c, g, true, (float*)(ws + L.silu), ws + L.xs, "mod_gemv", s, split_ready);
 }
 
 // h = LN(x)(1+scale)+shift for both streams into the joint [B][S][D] buffer
@@ -432,9 +434,38 @@ dit_status check_step_weights(const dit_step_weights* w) {
   return DIT_OK;
 }
 
+// bf16, B <= 16: the timestep MLP on the split sinusoid in xs_e, with no launch between its GEMVs: each
+// writes the next one's split input (xs_h, and xs_t = split SiLU(temb) unless null) beside its output.
+size_t chain_bytes(const dit_block_config* c) { return 2 * 16 * (256 + (size_t)c->hidden) * 2; }
+dit_status run_timestep_chain(const dit_block_config* c, const dit_step_weights* w, int B, u16* xs_e, u16* xs_h,
+                              u16* xs_t, float* temb, hipStream_t s) {
+  GemvArgs g{};
+  g.W[0] = w->t1_w;
+  g.bias[0] = w->t1_b;
+  g.N = c->hidden;
+  g.K = 256;
+  g.B = B;
+  g.nstreams = 1;
+  g.xs_out = xs_h;
+  dit_status st = run_gemv(c, g, false, nullptr, xs_e, "timestep_gemv", s, true);
+  if (st) return st;
+  g.W[0] = w->t2_w;
+  g.bias[0] = w->t2_b;
+  g.out[0] = temb;
+  g.out_bstride = c->hidden;
+  g.K = c->hidden;
+  g.xs_out = xs_t;
+  return run_gemv(c, g, true, nullptr, xs_h, "timestep_gemv", s, true);
+}
+
 dit_status run_timestep(const dit_block_config* c, const dit_step_weights* w, int B, const float* t_dev, float t,
                         float* temb, char* ws, hipStream_t s) {
   const int D = c->hidden;
+  if (c->dtype == DIT_BF16 && B <= 16 && timestep_ws(c, B) >= chain_bytes(c)) {
+    u16* xs_e = (u16*)ws;
+    TIMED("small_elementwise", 0, 0, s, step_prep(t_dev, t, B, xs_e, nullptr, nullptr, 0, s));
+    return run_timestep_chain(c, w, B, xs_e, xs_e + 2 * 16 * 256, nullptr, temb, s);
+  }
   float* e = (float*)ws;
   float* h1 = (float*)(ws + al256((size_t)B * 256 * 4));
   float* s1 = (float*)(ws + al256((size_t)B * 256 * 4) + al256((size_t)B * D * 4));
@@ -462,13 +493,15 @@ dit_status run_timestep(const dit_block_config* c, const dit_step_weights* w, in
   return run_gemv(c, g, true, s1, xs, "timestep_gemv", s);
 }
 
+// cast_ready: ws holds the latent in bf16 already
 dit_status run_patch(const dit_block_config* c, const dit_step_weights* w, int B, int C, const float* latent,
-                     void* x_img, char* ws, hipStream_t s) {
+                     void* x_img, char* ws, bool cast_ready, hipStream_t s) {
   const int D = c->hidden;
   const int M = B * c->n_img;
   const void* A = latent;
   if (c->dtype == DIT_BF16) {
-    TIMED("small_elementwise", 0, (double)M * C * 6, s, cast_f32_to_bf16(latent, (u16*)ws, (int64_t)M * C, s));
+    if (!cast_ready)
+      TIMED("small_elementwise", 0, (double)M * C * 6, s, cast_f32_to_bf16(latent, (u16*)ws, (int64_t)M * C, s));
     A = ws;
   }
   GemmPair p{};
@@ -478,9 +511,30 @@ dit_status run_patch(const dit_block_config* c, const dit_step_weights* w, int B
   return DIT_OK;
 }
 
-// resid (bf16 only, may be null): added to x_img before the head
+// The start of a step: temb and the patch embedding. Where the bf16 batch fits one GEMV pass and the
+// workspace has room beside the rounded latent, both start in one launch and the GEMVs chain (a launch of a
+// few microseconds saved each); xs_t then holds split SiLU(temb) for the modulation GEMVs (*xs_ready).
+dit_status run_step_start(const dit_block_config* c, const dit_step_weights* w, int B, int C, float t,
+                          const float* latent, float* temb, void* x_img, char* inner, size_t inner_bytes,
+                          const BlockWs& BL, bool* xs_ready, hipStream_t s) {
+  const size_t off = std::max(patch_ws(c, B, C), BL.h);   // clear of the rounded latent and of xs_t
+  *xs_ready = c->dtype == DIT_BF16 && B <= 16 && off + chain_bytes(c) <= inner_bytes;
+  dit_status st;
+  if (!*xs_ready) {
+    if ((st = run_timestep(c, w, B, nullptr, t, temb, inner, s))) return st;
+    return run_patch(c, w, B, C, latent, x_img, inner, false, s);
+  }
+  u16* xs_e = (u16*)(inner + off);
+  const int64_t n = (int64_t)B * c->n_img * C;
+  TIMED("small_elementwise", 0, 6.0 * n, s, step_prep(nullptr, t, B, xs_e, latent, (u16*)inner, n, s));
+  // the patch embedding reads the rounded latent before temb's chain writes xs_t, which may lie over it
+  if ((st = run_patch(c, w, B, C, latent, x_img, inner, true, s))) return st;
+  return run_timestep_chain(c, w, B, xs_e, xs_e + 2 * 16 * 256, (u16*)(inner + BL.xs), temb, s);
+}
+
+// resid (bf16 only, may be null): added to x_img before the head; xs_t: split SiLU(temb) (bf16), or null
 dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B, int C, const float* temb,
-                     const void* x_img, const float* resid, float* v, char* ws, hipStream_t s) {
+                     const void* x_img, const float* resid, float* v, char* ws, void* xs_t, hipStream_t s) {
   const int D = c->hidden;
   float* s1 = (float*)ws;
   float* fm = (float*)(ws + al256((size_t)B * D * 4));
@@ -497,7 +551,7 @@ dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B
   g.K = D;
   g.B = B;
   g.nstreams = 1;
-  dit_status st = run_gemv(c, g, true, s1, xs, "final_gemv", s);
+  dit_status st = run_gemv(c, g, true, s1, xs_t ? xs_t : xs, "final_gemv", s, xs_t != nullptr);
   if (st) return st;
   if (c->dtype == DIT_BF16) {
     FinalArgs f{x_img, resid, fm, w->fout_w, w->fout_b, v, (int64_t)B * c->n_img, c->n_img, D, C, c->ln_eps};
@@ -590,9 +644,10 @@ dit_status block_body(const dit_block_config* c, const dit_block_weights* w, int
   const DbgScope dbg_scope(&dbg_r);
 #endif
 
-  if (!mod_pre && (st = run_modulation(c, w, B, temb, ws, L, s))) return st;
-  if (c->rope && !rope_ready)
-    TIMED("small_elementwise", 0, 0, s, rope_table(rope, std::max(c->grid_h, c->grid_w), d, c->rope_theta, s));
+  const RopeArgs ra{rope, std::max(c->grid_h, c->grid_w), d, c->rope_theta};
+  const bool rope_due = c->rope && !rope_ready, rope_beside = rope_due && !mod_pre && c->dtype == DIT_BF16;
+  if (!mod_pre && (st = run_modulation(c, w, B, temb, ws, L, rope_beside ? ra : RopeArgs{}, s))) return st;
+  if (rope_due && !rope_beside) TIMED("small_elementwise", 0, 0, s, rope_table(ra, s));
   // pre-attention LN + modulate into h
   if ((st = run_ln(c, B, x_img, x_txt, mod, ws, L, 0, D, s))) return st;
   // QKV projection straight into the joint [B][S][3][H][d] buffer (+ RoPE on image q, k)
@@ -647,14 +702,15 @@ dit_status block_body(const dit_block_config* c, const dit_block_weights* w, int
 }
 
 // Blocks [0, n) in order on the block workspace `inner`; their modulation is computed MOD_GROUP
-// blocks at a time into mods.
+// blocks at a time into mods (xs_ready: BL.xs holds split SiLU(temb)).
 dit_status run_blocks(const dit_block_config* c, const dit_block_weights* blocks, int n, int B, const float* temb,
-                      void* ximg, void* xtxt, float* mods, char* inner, const BlockWs& BL, hipStream_t s) {
+                      void* ximg, void* xtxt, float* mods, char* inner, const BlockWs& BL, bool xs_ready,
+                      hipStream_t s) {
   dit_status st = DIT_OK;
   const size_t per = (size_t)2 * B * 6 * c->hidden;
   for (int g0 = 0; g0 < n; g0 += MOD_GROUP) {
     const int gn = std::min(MOD_GROUP, n - g0);
-    if ((st = run_modulation_group(c, blocks + g0, gn, B, temb, mods, inner, BL, s))) return st;
+    if ((st = run_modulation_group(c, blocks + g0, gn, B, temb, mods, inner, BL, xs_ready, s))) return st;
     for (int i = 0; i < gn; i++)
       if ((st = block_body(c, &blocks[g0 + i], B, temb, ximg, xtxt, inner, BL, mods + i * per, g0 + i > 0, s)))
         return st;
@@ -681,7 +737,7 @@ dit_status dit_block_mlp(const dit_block_config* c, const dit_block_weights* w, 
   BlockWs L = block_layout(c, batch);
   if ((st = check_ws(workspace, workspace_bytes, L.total))) return st;
   char* ws = (char*)workspace;
-  if ((st = run_modulation(c, w, batch, temb, ws, L, hs(stream)))) return st;
+  if ((st = run_modulation(c, w, batch, temb, ws, L, RopeArgs{}, hs(stream)))) return st;
 #ifdef DITSTEP_DEBUG
   const DbgRegions dbg_r = block_regions(c, w, batch, x_img, x_txt, ws, L.total, (const float*)(ws + L.mod));
   const DbgScope dbg_scope(&dbg_r);
@@ -836,7 +892,7 @@ dit_status dit_patch_embed(const dit_block_config* c, const dit_step_weights* w,
   if (!latent || !x_img || !aligned16(latent) || !aligned16(x_img))
     return set_error(DIT_ERR_INVALID_ARG, "latent/x_img NULL or not 16-byte aligned");
   if ((st = check_ws(workspace, workspace_bytes, patch_ws(c, batch, latent_dim)))) return st;
-  return run_patch(c, w, batch, latent_dim, latent, x_img, (char*)workspace, hs(stream));
+  return run_patch(c, w, batch, latent_dim, latent, x_img, (char*)workspace, false, hs(stream));
 }
 
 dit_status dit_final_layer(const dit_block_config* c, const dit_step_weights* w, int32_t batch, int32_t latent_dim,
@@ -850,7 +906,7 @@ dit_status dit_final_layer(const dit_block_config* c, const dit_step_weights* w,
   if (!temb || !x_img || !v || !aligned16(temb) || !aligned16(x_img) || !aligned16(v))
     return set_error(DIT_ERR_INVALID_ARG, "temb/x_img/v NULL or not 16-byte aligned");
   if ((st = check_ws(workspace, workspace_bytes, final_ws(c, batch)))) return st;
-  return run_final(c, w, batch, latent_dim, temb, x_img, nullptr, v, (char*)workspace, hs(stream));
+  return run_final(c, w, batch, latent_dim, temb, x_img, nullptr, v, (char*)workspace, nullptr, hs(stream));
 }
 
 size_t dit_denoise_workspace_bytes(const dit_block_config* c, int32_t batch, int32_t latent_dim) {
@@ -885,15 +941,16 @@ dit_status dit_denoise_step(const dit_block_config* c, const dit_step_weights* s
     if ((st = check_block_args(c, &blocks[i], batch, temb, ximg, xtxt))) return st;
   hipStream_t s = hs(stream);
   const int B = batch, C = latent_dim;
-  if ((st = run_timestep(c, sw, B, nullptr, t, temb, inner, s))) return st;
-  if ((st = run_patch(c, sw, B, C, latent, ximg, inner, s))) return st;
+  const BlockWs BL = block_layout(c, B);
+  const size_t inner_bytes = L.total - L.inner;
+  bool xs_ready = false;
+  if ((st = run_step_start(c, sw, B, C, t, latent, temb, ximg, inner, inner_bytes, BL, &xs_ready, s))) return st;
   if (c->n_txt > 0)
     HIP_TRY(hipMemcpyAsync(xtxt, x_txt, (size_t)B * c->n_txt * c->hidden * esize(c->dtype), hipMemcpyDeviceToDevice, s));
-  const BlockWs BL = block_layout(c, B);
   if (n_blocks > 0 && (st = check_ws(inner, workspace_bytes - L.inner, BL.total))) return st;
-  if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, (float*)(ws + L.mods), inner, BL, s)))
+  if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, (float*)(ws + L.mods), inner, BL, xs_ready, s)))
     return st;
-  if ((st = run_final(c, sw, B, C, temb, ximg, nullptr, v, inner, s))) return st;
+  if ((st = run_final(c, sw, B, C, temb, ximg, nullptr, v, inner, xs_ready ? inner + BL.xs : nullptr, s))) return st;
   TIMED("flow_step", 0, (noise_level > 0.f ? 16.0 : 12.0) * B * c->n_img * C, s,
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;
@@ -959,13 +1016,13 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   char* cb = (char*)cache;
   float* resid = (float*)(cb + TL.resid);
   double* parts = (double*)(cb + TL.parts);
-  double* sums = (double*)(cb + TL.sums);
-  if ((st = run_timestep(c, sw, B, nullptr, t, temb, inner, s))) return st;
-  if ((st = run_patch(c, sw, B, C, latent, ximg, inner, s))) return st;
+  const BlockWs BL = block_layout(c, B);
+  const size_t inner_bytes = L.total - L.inner;
+  if ((st = check_ws(inner, inner_bytes, BL.total))) return st;
+  bool xs_ready = false;
+  if ((st = run_step_start(c, sw, B, C, t, latent, temb, ximg, inner, inner_bytes, BL, &xs_ready, s))) return st;
   // block 0's modulated image input, which needs only the shift1 and scale1 rows of its image
   // modulation; the rest of the modulation and the text stream are fetched once the blocks run
-  const BlockWs BL = block_layout(c, B);
-  if ((st = check_ws(inner, workspace_bytes - L.inner, BL.total))) return st;
   float* mods = (float*)(ws + L.mods);
   GemvArgs g{};
   g.W[0] = blocks[0].mod_w[0];
@@ -978,7 +1035,7 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   g.K = D;
   g.B = B;
   g.nstreams = 1;
-  if ((st = run_gemv(c, g, true, (float*)(inner + BL.silu), inner + BL.xs, "mod_gemv", s))) return st;
+  if ((st = run_gemv(c, g, true, (float*)(inner + BL.silu), inner + BL.xs, "mod_gemv", s, xs_ready))) return st;
   const bool measure = state->has_prev != 0;
   LnArgs la{};
   la.x[0] = ximg;
@@ -991,12 +1048,17 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   la.D = D;
   la.eps = c->ln_eps;
   TIMED("teacache_distance", 0, (measure ? 3.0 : 2.0) * n_act * esize(c->dtype), s,
-        teacache_ln_distance(la, cb + TL.hprev, measure, parts, sums, c->dtype, s));
+        teacache_ln_distance(la, cb + TL.hprev, measure, parts, c->dtype, s));
   double r = std::numeric_limits<double>::quiet_NaN();
   if (measure) {
-    double hsums[2];
-    HIP_TRY(hipMemcpyAsync(hsums, sums, sizeof hsums, hipMemcpyDeviceToHost, s));
+    double hp[2 * TEACACHE_PARTS], hsums[2] = {0.0, 0.0};
+    const int np = teacache_parts(la.rows[0]);
+    HIP_TRY(hipMemcpyAsync(hp, parts, (size_t)np * 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    for (int i = 0; i < np; i++) {
+      hsums[0] += hp[2 * i];
+      hsums[1] += hp[2 * i + 1];
+    }
     r = hsums[1] > 0.0 ? hsums[0] / hsums[1] : (hsums[0] > 0.0 ? std::numeric_limits<double>::infinity() : 0.0);
   }
   int32_t run = 1;
@@ -1011,7 +1073,7 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
     if (c->n_txt > 0)
       HIP_TRY(hipMemcpyAsync(xtxt, x_txt, (size_t)B * c->n_txt * D * esize(c->dtype), hipMemcpyDeviceToDevice, s));
     TIMED("small_elementwise", 0, 0, s, teacache_residual(ximg, resid, n_act, 0, c->dtype, s));
-    if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, mods, inner, BL, s))) return st;
+    if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, mods, inner, BL, xs_ready, s))) return st;
     TIMED("small_elementwise", 0, 0, s, teacache_residual(ximg, resid, n_act, 1, c->dtype, s));
     state->has_residual = 1;
   } else if (c->dtype != DIT_BF16) {   // bf16: the velocity head adds the residual as it reads x
@@ -1019,7 +1081,8 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   }
   if (ran_blocks) *ran_blocks = run;
   if (rel) *rel = r;
-  if ((st = run_final(c, sw, B, C, temb, ximg, !run && c->dtype == DIT_BF16 ? resid : nullptr, v, inner, s))) return st;
+  if ((st = run_final(c, sw, B, C, temb, ximg, !run && c->dtype == DIT_BF16 ? resid : nullptr, v, inner,
+                      xs_ready ? inner + BL.xs : nullptr, s))) return st;
   TIMED("flow_step", 0, (noise_level > 0.f ? 16.0 : 12.0) * B * c->n_img * C, s,
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;

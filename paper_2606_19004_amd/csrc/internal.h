@@ -133,25 +133,38 @@ struct GemvArgs {
   int64_t out_bstride;
   const float* in; int64_t in_bstride;
   int N, K, B, nstreams;
+  u16* xs_out;   // bf16, B <= 16, one slot: also write SiLU(out) as the next GEMV's split input (or null)
+};
+// RoPE (cos, sin) table: tab[pos][i], pos < npos, i < head_dim / 4
+struct RopeArgs {
+  float* tab;
+  int npos, head_dim;
+  float theta;
 };
 hipError_t gemv(const GemvArgs& a, int dtype, hipStream_t s);   // VALU (fp32 weights)
-// bf16 weights through MFMA; xs = scratch [2][16][K] bf16; silu_in applies SiLU to the input first;
-// K must be a multiple of 32
-hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int silu_in, hipStream_t s);
+// bf16 weights through MFMA on the input's two bf16 parts, xs [2][16][K], which are made here from a.in
+// (GEMV_RAW) or SiLU(a.in) (GEMV_SILU), or are there already (GEMV_SPLIT, B <= 16). The launch that makes
+// them also fills rope (tab null: none). K must be a multiple of 32
+enum GemvInput { GEMV_RAW = 0, GEMV_SILU = 1, GEMV_SPLIT = 2 };
+hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int input, const RopeArgs& rope, hipStream_t s);
+// xs [2][16][256] = the split timestep sinusoid of t_dev[b] (or t_scalar), b < B <= 16, and lat16 = bf16
+// of n latent elements (n a multiple of 8, 16-byte aligned; may be 0), in one launch
+hipError_t step_prep(const float* t_dev, float t_scalar, int B, u16* xs, const float* latent, u16* lat16, int64_t n,
+                     hipStream_t s);
 
 hipError_t silu_f32(const float* in, float* out, int64_t n, hipStream_t s);
 hipError_t cast_f32_to_bf16(const float* in, u16* out, int64_t n, hipStream_t s);
 hipError_t timestep_sinusoid(const float* t_dev, float t_scalar, float* e, int B, hipStream_t s);
-hipError_t rope_table(float* tab, int npos, int head_dim, float theta, hipStream_t s);
+hipError_t rope_table(const RopeArgs& r, hipStream_t s);
 // per-sample Gaussian log-density of an SDE step: logp[b] = -sum (xn - mean)^2 * inv2var + cst,
 // mean = x + h (v + k1 (x + omt v))
 hipError_t flow_logprob_launch(const float* x, const float* v, const float* xn, int batch, int64_t n, double h,
                                double k1, double omt, double inv2var, double cst, double* logp, hipStream_t s);
 // TeaCache: h = LN(x)(1 + scale) + shift over the image rows (stream 0 of a), rounded to dtype and
-// compared with h_prev ([rows][D]): sums[0..1] = sum |h - h_prev|, sum |h_prev| in a fixed order (skipped
-// when !measure); h_prev is then overwritten with h.
-hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, double* partials, double* sums, int dtype,
-                                hipStream_t s);
+// compared with h_prev ([rows][D]): partials[2 p], [2 p + 1] = sum |h - h_prev|, sum |h_prev| over part p of
+// teacache_parts(rows) (zeros when !measure); h_prev is then overwritten with h.
+int teacache_parts(int64_t rows);
+hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, double* partials, int dtype, hipStream_t s);
 // velocity head, bf16: v[m][c] = sum_k W[c][k] h[m][k] + bias[c], h = LN(x + resid)(1 + scale) + shift with
 // (shift, scale) = mod[b][0..D), mod[b][D..2D), b = m / rows_per_batch; resid (fp32) may be null. D a
 // multiple of 32 and at most 4096, C a multiple of 64.

@@ -11,6 +11,36 @@
 
 namespace dit {
 
+template <typename T> struct Vec8;
+template <> struct Vec8<u16> {
+  static __device__ __forceinline__ void load(const u16* p, float* f) {
+    uint4 u = *(const uint4*)p;
+    uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      f[2 * i] = __uint_as_float(w[i] << 16);
+      f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+  }
+  static __device__ __forceinline__ void store(u16* p, const float* f) {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      w[i] = (uint32_t)from_f32<u16>(f[2 * i]) | ((uint32_t)from_f32<u16>(f[2 * i + 1]) << 16);
+    *(uint4*)p = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+};
+template <> struct Vec8<float> {
+  static __device__ __forceinline__ void load(const float* p, float* f) {
+    float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
+    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+  }
+  static __device__ __forceinline__ void store(float* p, const float* f) {
+    *(float4*)p = make_float4(f[0], f[1], f[2], f[3]);
+    *(float4*)(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
+  }
+};
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -191,34 +221,71 @@ hipError_t cast_f32_to_bf16(const float* in, u16* out, int64_t n, hipStream_t s)
   return hipGetLastError();
 }
 
-// e[b] = [cos(1000 t f_j) ; sin(1000 t f_j)], f_j = 10000^(-j/128), evaluated in fp64.
+// the two bf16 parts of x, hi + lo = x to 2^-16 relative
+__device__ __forceinline__ void split_hilo(float x, u16& hi, u16& lo) {
+  const __bf16 h = (__bf16)x, l = (__bf16)(x - (float)h);
+  hi = __builtin_bit_cast(u16, h);
+  lo = __builtin_bit_cast(u16, l);
+}
+
+// e = [cos(1000 t f_j) ; sin(1000 t f_j)], f_j = 10000^(-j/128), evaluated in fp64
+__device__ __forceinline__ void sinusoid(double t, int j, float& c, float& s) {
+  const double f = exp(-log(10000.0) * (double)j / 128.0);
+  const double arg = 1000.0 * t * f;
+  c = (float)cos(arg);
+  s = (float)sin(arg);
+}
 __global__ void sinusoid_kernel(const float* t_dev, float t_scalar, float* e, int B) {
   int b = blockIdx.x, j = threadIdx.x;  // 128 threads
-  double t = t_dev ? (double)t_dev[b] : (double)t_scalar;
-  double f = exp(-log(10000.0) * (double)j / 128.0);
-  double arg = 1000.0 * t * f;
-  e[(int64_t)b * 256 + j] = (float)cos(arg);
-  e[(int64_t)b * 256 + 128 + j] = (float)sin(arg);
+  sinusoid(t_dev ? (double)t_dev[b] : (double)t_scalar, j, e[(int64_t)b * 256 + j], e[(int64_t)b * 256 + 128 + j]);
 }
 hipError_t timestep_sinusoid(const float* t_dev, float t_scalar, float* e, int B, hipStream_t s) {
   if (B > 0) sinusoid_kernel<<<B, 128, 0, s>>>(t_dev, t_scalar, e, B);
   return hipGetLastError();
 }
 
-// tab[pos][i] = (cos, sin)(pos * theta^(-2i/m)), m = head_dim/2, i < m/2, in fp64.
-__global__ void rope_table_kernel(float* tab, int npos, int head_dim, float theta) {
-  int pairs = head_dim / 4;
-  int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= npos * pairs) return;
-  int pos = idx / pairs, i = idx % pairs;
-  double m = head_dim / 2;
-  double ang = (double)pos * pow((double)theta, -2.0 * i / m);
-  tab[2 * idx] = (float)cos(ang);
-  tab[2 * idx + 1] = (float)sin(ang);
+// The start of a step in one launch: workgroups 0..15 write the sinusoid of sample b, split, in the
+// MFMA GEMV's input layout ([2][16][256], zeros for b >= B); the others round the latent to bf16, 8
+// elements per thread.
+__global__ void __launch_bounds__(256) step_prep_kernel(const float* t_dev, float t_scalar, int B, u16* __restrict__ xs,
+                                                        const float* __restrict__ latent, u16* __restrict__ lat16,
+                                                        int64_t n8) {
+  if (blockIdx.x < 16) {
+    const int b = blockIdx.x, j = threadIdx.x;
+    if (j >= 128) return;
+    float c = 0.f, s = 0.f;
+    if (b < B) sinusoid(t_dev ? (double)t_dev[b] : (double)t_scalar, j, c, s);
+    split_hilo(c, xs[b * 256 + j], xs[(16 + b) * 256 + j]);
+    split_hilo(s, xs[b * 256 + 128 + j], xs[(16 + b) * 256 + 128 + j]);
+    return;
+  }
+  const int64_t i = ((int64_t)blockIdx.x - 16) * 256 + threadIdx.x;
+  if (i < n8) {
+    float f[8];
+    Vec8<float>::load(latent + 8 * i, f);
+    Vec8<u16>::store(lat16 + 8 * i, f);
+  }
 }
-hipError_t rope_table(float* tab, int npos, int head_dim, float theta, hipStream_t s) {
-  int n = npos * (head_dim / 4);
-  if (n > 0) rope_table_kernel<<<cdiv(n, 256), 256, 0, s>>>(tab, npos, head_dim, theta);
+hipError_t step_prep(const float* t_dev, float t_scalar, int B, u16* xs, const float* latent, u16* lat16, int64_t n,
+                     hipStream_t s) {
+  step_prep_kernel<<<16 + cdiv(n / 8, 256), 256, 0, s>>>(t_dev, t_scalar, B, xs, latent, lat16, n / 8);
+  return hipGetLastError();
+}
+
+// tab[pos][i] = (cos, sin)(pos * theta^(-2i/m)), m = head_dim/2, i < m/2, in fp64.
+__device__ __forceinline__ void rope_entry(const RopeArgs& r, int idx) {
+  int pairs = r.head_dim / 4;
+  if (idx >= r.npos * pairs) return;
+  int pos = idx / pairs, i = idx % pairs;
+  double m = r.head_dim / 2;
+  double ang = (double)pos * pow((double)r.theta, -2.0 * i / m);
+  r.tab[2 * idx] = (float)cos(ang);
+  r.tab[2 * idx + 1] = (float)sin(ang);
+}
+__global__ void rope_table_kernel(RopeArgs r) { rope_entry(r, blockIdx.x * 256 + threadIdx.x); }
+hipError_t rope_table(const RopeArgs& r, hipStream_t s) {
+  int n = r.npos * (r.head_dim / 4);
+  if (n > 0) rope_table_kernel<<<cdiv(n, 256), 256, 0, s>>>(r);
   return hipGetLastError();
 }
 
@@ -227,36 +294,6 @@ hipError_t rope_table(float* tab, int npos, int head_dim, float theta, hipStream
 // 8 consecutive elements (16-byte bf16 or 32-byte fp32 accesses), so a row of
 // D <= 512*CH stays in registers for the two-pass mean / variance.
 // ---------------------------------------------------------------------------
-template <typename T> struct Vec8;
-template <> struct Vec8<u16> {
-  static __device__ __forceinline__ void load(const u16* p, float* f) {
-    uint4 u = *(const uint4*)p;
-    uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      f[2 * i] = __uint_as_float(w[i] << 16);
-      f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-  static __device__ __forceinline__ void store(u16* p, const float* f) {
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-      w[i] = (uint32_t)from_f32<u16>(f[2 * i]) | ((uint32_t)from_f32<u16>(f[2 * i + 1]) << 16);
-    *(uint4*)p = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-};
-template <> struct Vec8<float> {
-  static __device__ __forceinline__ void load(const float* p, float* f) {
-    float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-  }
-  static __device__ __forceinline__ void store(float* p, const float* f) {
-    *(float4*)p = make_float4(f[0], f[1], f[2], f[3]);
-    *(float4*)(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
-  }
-};
-
 template <typename T, int CH>
 __global__ void __launch_bounds__(256) ln_modulate_kernel(LnArgs a) {
   int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -341,7 +378,7 @@ __device__ __forceinline__ void opaque(uint4& u) { asm volatile("" : "+v"(u.x), 
 // TeaCache distance, fused with the LayerNorm + modulate that makes the compared input: a wave takes
 // rows of the image stream as in ln_modulate_kernel, rounds h to the storage type, adds |h - h_prev| and
 // |h_prev| in fp64 and replaces h_prev, so h itself is never stored. One partial pair per workgroup
-// (at most TEACACHE_PARTS), summed in a fixed order. Bound by HBM: x and h_prev read, h_prev written.
+// (at most TEACACHE_PARTS; the host, which needs the distance, sums them). Bound by HBM: x and h_prev read, h_prev written.
 // ---------------------------------------------------------------------------
 template <typename T, int CH>
 __global__ void __launch_bounds__(256) teacache_ln_distance_kernel(LnArgs a, T* __restrict__ hp, int measure,
@@ -470,31 +507,6 @@ __global__ void __launch_bounds__(256) teacache_ln_distance_kernel(LnArgs a, T* 
   }
 }
 
-// sums[0..1] of up to TEACACHE_PARTS pairs: a thread per strided share, then a fixed tree
-__global__ void __launch_bounds__(256) teacache_sum_kernel(const double* __restrict__ part, int nparts,
-                                                           double* __restrict__ sums) {
-  __shared__ double sd[4], sp[4];
-  double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += 256) {
-    a += part[2 * i];
-    b += part[2 * i + 1];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    a += __shfl_xor(a, o, 64);
-    b += __shfl_xor(b, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    sd[threadIdx.x >> 6] = a;
-    sp[threadIdx.x >> 6] = b;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    sums[0] = (sd[0] + sd[1]) + (sd[2] + sd[3]);
-    sums[1] = (sp[0] + sp[1]) + (sp[2] + sp[3]);
-  }
-}
-
 template <typename T>
 static void teacache_ln_launch(const LnArgs& a, T* hp, bool measure, double* partials, int grid, hipStream_t s) {
   const int ch = cdiv(a.D, 512);
@@ -504,13 +516,12 @@ static void teacache_ln_launch(const LnArgs& a, T* hp, bool measure, double* par
   else if (ch <= 6) teacache_ln_distance_kernel<T, 6><<<grid, 256, 0, s>>>(a, hp, measure, partials);
   else teacache_ln_distance_kernel<T, 8><<<grid, 256, 0, s>>>(a, hp, measure, partials);
 }
-hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, double* partials, double* sums, int dtype,
-                                hipStream_t s) {
+int teacache_parts(int64_t rows) { return (int)std::min<int64_t>(TEACACHE_PARTS, cdiv(rows, 4)); }
+hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, double* partials, int dtype, hipStream_t s) {
   if (a.rows[0] == 0) return hipSuccess;
-  const int grid = (int)std::min<int64_t>(TEACACHE_PARTS, cdiv(a.rows[0], 4));
+  const int grid = teacache_parts(a.rows[0]);
   if (dtype == DT_BF16) teacache_ln_launch<u16>(a, (u16*)h_prev, measure, partials, grid, s);
   else teacache_ln_launch<float>(a, (float*)h_prev, measure, partials, grid, s);
-  if (measure) teacache_sum_kernel<<<1, 256, 0, s>>>(partials, grid, sums);
   return hipGetLastError();
 }
 
@@ -765,19 +776,24 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a, int b0, int nb) {
 // 16-wide N dimension), so HBM bandwidth, not VALU FMAs, sets the time.
 // A workgroup owns 32 weight rows and splits K over its 4 waves.
 // ---------------------------------------------------------------------------
-__global__ void split_hilo_kernel(const float* __restrict__ in, int64_t stride, int b0, int nb, int K, int silu,
-                                  u16* __restrict__ out) {
-  int k = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+// Workgroups past the first 16 cdiv(K, 256) fill the RoPE table of a block instead, which saves a launch
+// (r.tab null: none).
+__device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
+__global__ void __launch_bounds__(256) split_hilo_kernel(const float* __restrict__ in, int64_t stride, int b0, int nb, int K,
+                                                         int act, u16* __restrict__ out, RopeArgs r) {
+  const int kb = (K + 255) / 256;
+  if ((int)blockIdx.x >= 16 * kb) {
+    rope_entry(r, (blockIdx.x - 16 * kb) * 256 + threadIdx.x);
+    return;
+  }
+  const int k = (blockIdx.x % kb) * 256 + threadIdx.x, b = blockIdx.x / kb;
   if (k >= K) return;
   float x = 0.f;
   if (b < nb) {
     x = in[(int64_t)(b0 + b) * stride + k];
-    if (silu) x = x / (1.0f + __expf(-x));
+    if (act) x = silu(x);
   }
-  __bf16 hi = (__bf16)x;
-  __bf16 lo = (__bf16)(x - (float)hi);
-  out[(int64_t)b * K + k] = __builtin_bit_cast(u16, hi);
-  out[(int64_t)(16 + b) * K + k] = __builtin_bit_cast(u16, lo);
+  split_hilo(x, out[(int64_t)b * K + k], out[(int64_t)(16 + b) * K + k]);
 }
 
 // One workgroup = 16 RB weight rows (RB row blocks of 16, each the A operand of its own MFMA
@@ -895,23 +911,46 @@ __global__ void __launch_bounds__(256) gemv_mfma_kernel(GemvArgs a, const u16* _
     }
   // accumulator register r of lane l in block j: weight row 16 j + 4 (l / 16) + r, sample l % 16
   const int b = lane & 15;
-  if (b >= nb) return;
   const u16* bias = (const u16*)a.bias[s];
+  if (b < nb && bias) {
+#pragma unroll
+    for (int j = 0; j < RB; j++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[j][r] += to_f32(bias[min(n0 + 16 * j + 4 * (lane >> 4) + r, a.N - 1)]);
+  }
+  if (a.xs_out) {   // the next GEMV's input: SiLU of the result, split (zeros past the batch)
+#pragma unroll
+    for (int j = 0; j < RB; j++) {
+      const int n = n0 + 16 * j + 4 * (lane >> 4);
+      if (n >= a.N) continue;
+      u16 h[4], l[4];
+#pragma unroll
+      for (int r = 0; r < 4; r++) split_hilo(b < nb ? silu(acc[j][r]) : 0.f, h[r], l[r]);
+      *(uint2*)(a.xs_out + (int64_t)b * a.N + n) = make_uint2(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16);
+      *(uint2*)(a.xs_out + (int64_t)(16 + b) * a.N + n) = make_uint2(l[0] | (uint32_t)l[1] << 16, l[2] | (uint32_t)l[3] << 16);
+    }
+  }
+  if (b >= nb || !a.out[s]) return;
   float* out = a.out[s] + (int64_t)(b0 + b) * a.out_bstride;
 #pragma unroll
   for (int j = 0; j < RB; j++)
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       int n = n0 + 16 * j + 4 * (lane >> 4) + r;
-      if (n < a.N) out[n] = acc[j][r] + (bias ? to_f32(bias[n]) : 0.f);
+      if (n < a.N) out[n] = acc[j][r];
     }
 }
 
-hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int silu_in, hipStream_t s) {
+hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int input, const RopeArgs& rope, hipStream_t s) {
   if (a.N == 0 || a.B == 0) return hipSuccess;
   for (int b0 = 0; b0 < a.B; b0 += 16) {
     int nb = std::min(16, a.B - b0);
-    split_hilo_kernel<<<dim3(cdiv(a.K, 256), 16), 256, 0, s>>>(a.in, a.in_bstride, b0, nb, a.K, silu_in, xs);
+    if (input != GEMV_SPLIT) {
+      RopeArgs r{};
+      if (b0 == 0 && rope.tab) r = rope;
+      split_hilo_kernel<<<16 * cdiv(a.K, 256) + (r.tab ? cdiv((int64_t)r.npos * (r.head_dim / 4), 256) : 0), 256, 0, s>>>(
+          a.in, a.in_bstride, b0, nb, a.K, input == GEMV_SILU, xs, r);
+    }
     // rows per workgroup by grid size: the step's batched modulation (1.8 GB of weights) streams
     // best with 128; a single block's (0.2 GB) with 64; the timestep and final-layer GEMVs (a few
     // MB) need more workgroups and a pipelined k chain (lab, same box: 30 -> 18 us for 3072 x 3072,
