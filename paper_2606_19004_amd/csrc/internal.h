@@ -141,7 +141,7 @@ struct RopeArgs {
   int npos, head_dim;
   float theta;
 };
-hipError_t gemv(const GemvArgs& a, int dtype, hipStream_t s);   // VALU (fp32 weights)
+hipError_t gemv_f32(const GemvArgs& a, bool silu_in, hipStream_t s);   // VALU, fp32 weights; SiLU(in) when silu_in
 // bf16 weights through MFMA on the input's two bf16 parts, xs [2][16][K], which are made here from a.in
 // (GEMV_RAW) or SiLU(a.in) (GEMV_SILU), or are there already (GEMV_SPLIT, B <= 16). The launch that makes
 // them also fills rope (tab null: none). K must be a multiple of 32
@@ -152,7 +152,6 @@ hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int input, const RopeArgs& rope
 hipError_t step_prep(const float* t_dev, float t_scalar, int B, u16* xs, const float* latent, u16* lat16, int64_t n,
                      hipStream_t s);
 
-hipError_t silu_f32(const float* in, float* out, int64_t n, hipStream_t s);
 hipError_t cast_f32_to_bf16(const float* in, u16* out, int64_t n, hipStream_t s);
 hipError_t timestep_sinusoid(const float* t_dev, float t_scalar, float* e, int B, hipStream_t s);
 hipError_t rope_table(const RopeArgs& r, hipStream_t s);

@@ -4,7 +4,7 @@
 //   ln_modulate    LayerNorm (fp32 statistics) + adaLN modulate, one wave per row
 //   gemv           batched GEMV for the adaLN / timestep / final modulation vectors
 //   reward_stats   per prompt-group mean, std, advantages, stable descending ranks
-//   small helpers  SiLU, fp32->bf16 cast, timestep sinusoid, RoPE cos/sin table
+//   small helpers  fp32->bf16 cast, timestep sinusoid, RoPE cos/sin table
 #include <type_traits>
 
 #include "internal.h"
@@ -40,6 +40,8 @@ template <> struct Vec8<float> {
     *(float4*)(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
   }
 };
+
+__device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -200,18 +202,6 @@ hipError_t flow_update(float* x, const float* v, const float* noise, int64_t n, 
 // ---------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------
-__global__ void silu_kernel(const float* __restrict__ in, float* __restrict__ out, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) {
-    float z = in[i];
-    out[i] = z / (1.0f + __expf(-z));
-  }
-}
-hipError_t silu_f32(const float* in, float* out, int64_t n, hipStream_t s) {
-  if (n > 0) silu_kernel<<<cdiv(n, 256), 256, 0, s>>>(in, out, n);
-  return hipGetLastError();
-}
-
 __global__ void cast_bf16_kernel(const float* __restrict__ in, u16* __restrict__ out, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) out[i] = from_f32<u16>(in[i]);
@@ -720,8 +710,10 @@ hipError_t final_head(const FinalArgs& a, hipStream_t s) {
 // pass. A wave owns 4 weight rows and streams them once (16-byte loads), with
 // the fp32 input read through L1/L2; lanes split K and reduce at the end.
 // ---------------------------------------------------------------------------
-template <typename T, int BMAX>
-__global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a, int b0, int nb) {
+// (fp32 weights; act: SiLU on the input as it is read)
+template <int BMAX>
+__global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a, int b0, int nb, int act) {
+  typedef float T;
   constexpr int R = 4;
   int s = blockIdx.y;
   int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -747,6 +739,10 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a, int b0, int nb) {
       if (b < nb) {
         float x[8];
         Vec8<float>::load(a.in + (int64_t)(b0 + b) * a.in_bstride + k, x);
+        if (act) {
+#pragma unroll
+          for (int i = 0; i < 8; i++) x[i] = silu(x[i]);
+        }
 #pragma unroll
         for (int r = 0; r < R; r++)
 #pragma unroll
@@ -778,7 +774,6 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs a, int b0, int nb) {
 // ---------------------------------------------------------------------------
 // Workgroups past the first 16 cdiv(K, 256) fill the RoPE table of a block instead, which saves a launch
 // (r.tab null: none).
-__device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
 __global__ void __launch_bounds__(256) split_hilo_kernel(const float* __restrict__ in, int64_t stride, int b0, int nb, int K,
                                                          int act, u16* __restrict__ out, RopeArgs r) {
   const int kb = (K + 255) / 256;
@@ -968,20 +963,16 @@ hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int input, const RopeArgs& rope
   return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t gemv_launch(const GemvArgs& a, hipStream_t s) {
+hipError_t gemv_f32(const GemvArgs& a, bool silu_in, hipStream_t s) {
+  if (a.N == 0 || a.B == 0) return hipSuccess;
   dim3 grid(cdiv(a.N, 16), a.nstreams);
   for (int b0 = 0; b0 < a.B; b0 += 16) {
     int nb = std::min(16, a.B - b0);
-    if (nb <= 4) gemv_kernel<T, 4><<<grid, 256, 0, s>>>(a, b0, nb);
-    else if (nb <= 8) gemv_kernel<T, 8><<<grid, 256, 0, s>>>(a, b0, nb);
-    else gemv_kernel<T, 16><<<grid, 256, 0, s>>>(a, b0, nb);
+    if (nb <= 4) gemv_kernel<4><<<grid, 256, 0, s>>>(a, b0, nb, silu_in);
+    else if (nb <= 8) gemv_kernel<8><<<grid, 256, 0, s>>>(a, b0, nb, silu_in);
+    else gemv_kernel<16><<<grid, 256, 0, s>>>(a, b0, nb, silu_in);
   }
   return hipGetLastError();
-}
-hipError_t gemv(const GemvArgs& a, int dtype, hipStream_t s) {
-  if (a.N == 0 || a.B == 0) return hipSuccess;
-  return dtype == DT_BF16 ? gemv_launch<u16>(a, s) : gemv_launch<float>(a, s);
 }
 
 // ---------------------------------------------------------------------------
