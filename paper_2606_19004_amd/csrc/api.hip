@@ -527,17 +527,27 @@ dit_status run_step_start(const dit_block_config* c, const dit_step_weights* w, 
   return run_timestep_chain(c, w, B, xs_e, xs_e + 2 * 16 * 256, (u16*)(inner + BL.xs), temb, s);
 }
 
-// resid (bf16 only, may be null): added to x_img before the head; xs_t: split SiLU(temb) (bf16), or null
-dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B, int C, const float* temb,
-                     const void* x_img, const float* resid, float* v, char* ws, void* xs_t, hipStream_t s) {
+// The velocity head in two parts: its modulation, which needs only temb (xs_t: split SiLU(temb), bf16, or
+// null), and the rest. In a step's inner workspace the modulation lies in the block workspace's own
+// modulation area, which blocks given theirs from outside leave alone.
+struct FinalWs {
+  size_t fm, h, xs;
+};
+FinalWs final_layout(const dit_block_config* c, int64_t B) {
+  FinalWs f;
+  f.fm = al256((size_t)B * c->hidden * 4);
+  f.h = f.fm + al256((size_t)B * 2 * c->hidden * 4);
+  f.xs = f.h + al256((size_t)B * c->n_img * c->hidden * esize(c->dtype));
+  return f;
+}
+dit_status run_final_mod(const dit_block_config* c, const dit_step_weights* w, int B, const float* temb, char* ws,
+                         void* xs_t, hipStream_t s) {
   const int D = c->hidden;
-  float* fm = (float*)(ws + al256((size_t)B * D * 4));
-  char* h = ws + al256((size_t)B * D * 4) + al256((size_t)B * 2 * D * 4);
-  char* xs = h + al256((size_t)B * c->n_img * D * esize(c->dtype));
+  const FinalWs L = final_layout(c, B);
   GemvArgs g{};
   g.W[0] = w->fmod_w;
   g.bias[0] = w->fmod_b;
-  g.out[0] = fm;
+  g.out[0] = (float*)(ws + L.fm);
   g.out_bstride = 2 * D;
   g.in = temb;
   g.in_bstride = D;
@@ -545,8 +555,15 @@ dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B
   g.K = D;
   g.B = B;
   g.nstreams = 1;
-  dit_status st = run_gemv(c, g, true, xs_t ? xs_t : xs, "final_gemv", s, xs_t != nullptr);
-  if (st) return st;
+  return run_gemv(c, g, true, xs_t ? xs_t : ws + L.xs, "final_gemv", s, xs_t != nullptr);
+}
+// resid (bf16 only, may be null): added to x_img before the head
+dit_status run_final_head(const dit_block_config* c, const dit_step_weights* w, int B, int C, const void* x_img,
+                          const float* resid, float* v, char* ws, hipStream_t s) {
+  const int D = c->hidden;
+  const FinalWs L = final_layout(c, B);
+  const float* fm = (const float*)(ws + L.fm);
+  char* h = ws + L.h;
   if (c->dtype == DIT_BF16) {
     FinalArgs f{x_img, resid, fm, w->fout_w, w->fout_b, v, (int64_t)B * c->n_img, c->n_img, D, C, c->ln_eps};
     TIMED("final_head", 2.0 * f.M * D * C, (resid ? 6.0 : 2.0) * f.M * D, s, final_head(f, s));
@@ -571,6 +588,12 @@ dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B
   p.p[0] = problem(h, contiguous_rows(D), w->fout_w, w->fout_b, v, contiguous_rows(C), B * c->n_img, C, D);
   TIMED("gemm_final", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, s));
   return DIT_OK;
+}
+
+dit_status run_final(const dit_block_config* c, const dit_step_weights* w, int B, int C, const float* temb,
+                     const void* x_img, float* v, char* ws, void* xs_t, hipStream_t s) {
+  dit_status st = run_final_mod(c, w, B, temb, ws, xs_t, s);
+  return st ? st : run_final_head(c, w, B, C, x_img, nullptr, v, ws, s);
 }
 
 // ---- fixed device scratch of the allocation-free timestep embedding ----
@@ -900,7 +923,7 @@ dit_status dit_final_layer(const dit_block_config* c, const dit_step_weights* w,
   if (!temb || !x_img || !v || !aligned16(temb) || !aligned16(x_img) || !aligned16(v))
     return set_error(DIT_ERR_INVALID_ARG, "temb/x_img/v NULL or not 16-byte aligned");
   if ((st = check_ws(workspace, workspace_bytes, final_ws(c, batch)))) return st;
-  return run_final(c, w, batch, latent_dim, temb, x_img, nullptr, v, (char*)workspace, nullptr, hs(stream));
+  return run_final(c, w, batch, latent_dim, temb, x_img, v, (char*)workspace, nullptr, hs(stream));
 }
 
 size_t dit_denoise_workspace_bytes(const dit_block_config* c, int32_t batch, int32_t latent_dim) {
@@ -944,7 +967,7 @@ dit_status dit_denoise_step(const dit_block_config* c, const dit_step_weights* s
   if (n_blocks > 0 && (st = check_ws(inner, workspace_bytes - L.inner, BL.total))) return st;
   if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, (float*)(ws + L.mods), inner, BL, xs_ready, s)))
     return st;
-  if ((st = run_final(c, sw, B, C, temb, ximg, nullptr, v, inner, xs_ready ? inner + BL.xs : nullptr, s))) return st;
+  if ((st = run_final(c, sw, B, C, temb, ximg, v, inner, xs_ready ? inner + BL.xs : nullptr, s))) return st;
   TIMED("flow_step", 0, (noise_level > 0.f ? 16.0 : 12.0) * B * c->n_img * C, s,
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;
@@ -965,6 +988,35 @@ TeaCacheLayout teacache_layout(const dit_block_config* c, int64_t B) {
   L.sums = L.parts + up(2 * sizeof(double) * TEACACHE_PARTS);
   L.total = L.sums + 256;
   return L;
+}
+
+// A point of a stream's work that the host can wait for.
+struct StreamMark {
+  hipEvent_t e = nullptr;
+  hipError_t record(hipStream_t s) {
+    hipError_t r = hipEventCreateWithFlags(&e, hipEventDisableTiming);
+    return r != hipSuccess ? r : hipEventRecord(e, s);
+  }
+  hipError_t wait() { return hipEventSynchronize(e); }
+  ~StreamMark() {
+    if (e) (void)hipEventDestroy(e);
+  }
+};
+
+// Where the distance's partial sums land on the host: 8 KB of pinned memory per calling thread, given back
+// when the thread ends (a copy to pageable memory goes through a staging copy and a wait of its own). A
+// call waits for its copy before it returns, so a thread's calls never share it.
+struct HostPartials {
+  double* p = nullptr;
+  ~HostPartials() {
+    if (p) (void)hipHostFree(p);
+  }
+};
+dit_status host_partials(double** out) {
+  static thread_local HostPartials mine;
+  if (!mine.p) HIP_TRY(hipHostMalloc((void**)&mine.p, 2 * sizeof(double) * TEACACHE_PARTS, hipHostMallocPortable));
+  *out = mine.p;
+  return DIT_OK;
 }
 }  // namespace
 
@@ -1045,16 +1097,25 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
         teacache_ln_distance(la, cb + TL.hprev, measure, parts, c->dtype, s));
   double r = std::numeric_limits<double>::quiet_NaN();
   if (measure) {
-    double hp[2 * TEACACHE_PARTS], hsums[2] = {0.0, 0.0};
+    double hsums[2] = {0.0, 0.0};
     const int np = teacache_parts(la.rows[0]);
+    double* hp = nullptr;
+    if ((st = host_partials(&hp))) return st;
     HIP_TRY(hipMemcpyAsync(hp, parts, (size_t)np * 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    StreamMark landed;
+    HIP_TRY(landed.record(s));
+    // the velocity head's modulation does not depend on the decision: it runs while the host waits for the
+    // distance and comes back with the next launches
+    st = run_final_mod(c, sw, B, temb, inner, xs_ready ? inner + BL.xs : nullptr, s);
+    HIP_TRY(landed.wait());
+    if (st) return st;
     for (int i = 0; i < np; i++) {
       hsums[0] += hp[2 * i];
       hsums[1] += hp[2 * i + 1];
     }
     r = hsums[1] > 0.0 ? hsums[0] / hsums[1] : (hsums[0] > 0.0 ? std::numeric_limits<double>::infinity() : 0.0);
   }
+  if (!measure && (st = run_final_mod(c, sw, B, temb, inner, xs_ready ? inner + BL.xs : nullptr, s))) return st;
   int32_t run = 1;
   if (measure && !std::isfinite(r)) {
     run = 1;                 // a zero cached input: no meaningful distance, run the blocks
@@ -1075,8 +1136,7 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   }
   if (ran_blocks) *ran_blocks = run;
   if (rel) *rel = r;
-  if ((st = run_final(c, sw, B, C, temb, ximg, !run && c->dtype == DIT_BF16 ? resid : nullptr, v, inner,
-                      xs_ready ? inner + BL.xs : nullptr, s))) return st;
+  if ((st = run_final_head(c, sw, B, C, ximg, !run && c->dtype == DIT_BF16 ? resid : nullptr, v, inner, s))) return st;
   TIMED("flow_step", 0, (noise_level > 0.f ? 16.0 : 12.0) * B * c->n_img * C, s,
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;
