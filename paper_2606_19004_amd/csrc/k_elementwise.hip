@@ -791,121 +791,16 @@ __global__ void __launch_bounds__(256) split_hilo_kernel(const float* __restrict
   split_hilo(x, out[(int64_t)b * K + k], out[(int64_t)(16 + b) * K + k]);
 }
 
-// One workgroup = 16 RB weight rows (RB row blocks of 16, each the A operand of its own MFMA
-// chain); its 4 waves take every 4th 32-deep k step and the partial sums meet in LDS, so each
-// row block streams with 4 independent load chains. Every k step of a wave reads the split input
-// (2 x 1 KB from L2) once for its RB row blocks (RB x 1 KB of weights), so more row blocks per
-// workgroup mean fewer re-reads of the input per weight byte: with the weights cold in HBM, RB = 8
-// (one k step per wave in flight, 180 registers) streams the 1.81 GB of a step's modulation
-// weights in 426 us against 467 us for RB = 4 with two k steps in flight. Small GEMVs (the
-// timestep and final-layer ones, a few MB of weights) are bound by the latency of each wave's chain
-// of k steps instead: they take fewer rows per workgroup (more workgroups) and, with DEPTH > 0, keep
-// DEPTH of a wave's k steps in flight (the loads of step i + DEPTH - 1 are issued before the MFMAs
-// of step i; loads past the wave's last step are clamped to that step, so that every load is
-// unconditional and the compiler can count the loads in flight). The sums run in the same order
-// either way.
-template <int RB, int U, int DEPTH = 0>
-__global__ void __launch_bounds__(256) gemv_mfma_kernel(GemvArgs a, const u16* __restrict__ xs, int b0, int nb) {
-  __shared__ f32x4 part[4][RB][64];
-  const int s = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n0 = blockIdx.x * 16 * RB;
-  const int K = a.K, nks = K / 32;
-  const int r16 = lane & 15, kq = (lane >> 4) * 8;
-  // operand A: rows n0 + 16 j + r16 (clamped; results of clamped rows are dropped)
-  const u16* W = (const u16*)a.W[s];
-  const u16* w[RB];
-#pragma unroll
-  for (int j = 0; j < RB; j++) w[j] = W + (int64_t)min(n0 + 16 * j + r16, a.N - 1) * K + kq;
-  // operand B: sample r16, hi and lo parts
-  const u16* xh = xs + (int64_t)r16 * K + kq;
-  const u16* xl = xs + (int64_t)(16 + r16) * K + kq;
-  f32x4 acc[RB];
-#pragma unroll
-  for (int j = 0; j < RB; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (DEPTH == 0) {
-    int ks = wave;
-    for (; ks + 4 * (U - 1) < nks; ks += 4 * U) {
-      bf16x8 fw[U][RB], fh[U], fl[U];
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        int k = 32 * (ks + 4 * u);
-#pragma unroll
-        for (int j = 0; j < RB; j++) fw[u][j] = *(const bf16x8*)(w[j] + k);
-        fh[u] = *(const bf16x8*)(xh + k);
-        fl[u] = *(const bf16x8*)(xl + k);
-      }
-#pragma unroll
-      for (int u = 0; u < U; u++)
-#pragma unroll
-        for (int j = 0; j < RB; j++) {
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][j], fh[u], acc[j], 0, 0, 0);
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][j], fl[u], acc[j], 0, 0, 0);
-        }
-    }
-    for (; ks < nks; ks += 4) {
-      int k = 32 * ks;
-      bf16x8 fh = *(const bf16x8*)(xh + k), fl = *(const bf16x8*)(xl + k);
-#pragma unroll
-      for (int j = 0; j < RB; j++) {
-        bf16x8 fw = *(const bf16x8*)(w[j] + k);
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw, fh, acc[j], 0, 0, 0);
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw, fl, acc[j], 0, 0, 0);
-      }
-    }
-  } else {
-    // this wave's k steps are wave + 4 i, i < nloc; the first nmain of them run pipelined
-    const int nloc = nks > wave ? (nks - wave + 3) / 4 : 0;
-    const int nmain = nloc - nloc % DEPTH;
-    bf16x8 fw[DEPTH][RB], fh[DEPTH], fl[DEPTH];
-    auto load = [&](int i, int slot) {
-      const int k = 32 * (wave + 4 * i);
-#pragma unroll
-      for (int j = 0; j < RB; j++) fw[slot][j] = *(const bf16x8*)(w[j] + k);
-      fh[slot] = *(const bf16x8*)(xh + k);
-      fl[slot] = *(const bf16x8*)(xl + k);
-    };
-    auto mma = [&](int slot) {
-#pragma unroll
-      for (int j = 0; j < RB; j++) {
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[slot][j], fh[slot], acc[j], 0, 0, 0);
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[slot][j], fl[slot], acc[j], 0, 0, 0);
-      }
-    };
-    if (nmain > 0) {
-#pragma unroll
-      for (int d = 0; d < DEPTH - 1; d++) load(d, d);
-      __builtin_amdgcn_sched_barrier(0);
-      for (int i = 0; i < nmain; i += DEPTH) {
-#pragma unroll
-        for (int u = 0; u < DEPTH; u++) {
-          load(min(i + u + DEPTH - 1, nloc - 1), (u + DEPTH - 1) % DEPTH);
-          __builtin_amdgcn_sched_barrier(0);   // keep the loads ahead of this step's MFMAs
-          mma(u);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    for (int i = nmain; i < nloc; i++) {
-      load(i, 0);
-      mma(0);
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < RB; j++) part[wave][j][lane] = acc[j];
-  __syncthreads();
-  if (wave != 0) return;
-  // sum the 4 partials in a fixed order (deterministic)
-#pragma unroll
-  for (int q = 1; q < 4; q++)
-#pragma unroll
-    for (int j = 0; j < RB; j++) {
-      f32x4 p = part[q][j][lane];
-#pragma unroll
-      for (int r = 0; r < 4; r++) acc[j][r] += p[r];
-    }
-  // accumulator register r of lane l in block j: weight row 16 j + 4 (l / 16) + r, sample l % 16
-  const int b = lane & 15;
+// Both kernels below are bound by HBM while their weights stream, and next by what a CU takes in besides:
+// every 32-deep k step of a wave also reads the split input (2 KB from L2 for 16 samples) against 1 KB of
+// weights per 16 rows. Rows past the batch are therefore left out of those loads (ALL = false, their
+// lanes zero): for one sample that alone takes 226 MB of weights from 70 to 52 us.
+
+// sums of a wave's accumulators (register r of lane l in block j: weight row n0 + 16 j + 4 (l / 16) + r,
+// sample l % 16) plus bias into out and, when asked, SiLU of them into the next GEMV's split input
+template <int RB>
+__device__ __forceinline__ void gemv_finish(const GemvArgs& a, int s, int n0, f32x4* acc, int b0, int nb) {
+  const int lane = threadIdx.x & 63, b = lane & 15;
   const u16* bias = (const u16*)a.bias[s];
   if (b < nb && bias) {
 #pragma unroll
@@ -913,7 +808,7 @@ __global__ void __launch_bounds__(256) gemv_mfma_kernel(GemvArgs a, const u16* _
 #pragma unroll
       for (int r = 0; r < 4; r++) acc[j][r] += to_f32(bias[min(n0 + 16 * j + 4 * (lane >> 4) + r, a.N - 1)]);
   }
-  if (a.xs_out) {   // the next GEMV's input: SiLU of the result, split (zeros past the batch)
+  if (a.xs_out) {   // (zeros past the batch)
 #pragma unroll
     for (int j = 0; j < RB; j++) {
       const int n = n0 + 16 * j + 4 * (lane >> 4);
@@ -936,6 +831,163 @@ __global__ void __launch_bounds__(256) gemv_mfma_kernel(GemvArgs a, const u16* _
     }
 }
 
+// The loads of U k steps, step u at element k0 + u * kstep: RB row blocks of weights and the split input.
+template <int RB, int U, bool ALL>
+struct GemvGroup {
+  bf16x8 fw[U][RB], fh[U], fl[U];
+  __device__ __forceinline__ void load(const u16* const* w, const u16* xh, const u16* xl, bool on, int k0, int kstep) {
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int j = 0; j < RB; j++) fw[u][j] = *(const bf16x8*)(w[j] + k0 + u * kstep);
+    if constexpr (!ALL) {
+      const bf16x8 z = {};
+#pragma unroll
+      for (int u = 0; u < U; u++) fh[u] = fl[u] = z;
+    }
+    if (ALL || on) {
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        fh[u] = *(const bf16x8*)(xh + k0 + u * kstep);
+        fl[u] = *(const bf16x8*)(xl + k0 + u * kstep);
+      }
+    }
+  }
+  __device__ __forceinline__ void mma(f32x4* acc) const {
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int j = 0; j < RB; j++) {
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][j], fh[u], acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][j], fl[u], acc[j], 0, 0, 0);
+      }
+  }
+};
+
+// One workgroup = 16 RB weight rows (RB row blocks of 16, each the A operand of its own MFMA
+// chain); its 4 waves take every 4th 32-deep k step and the partial sums meet in LDS, so each
+// row block streams with 4 independent load chains. Small GEMVs (the timestep and final-layer ones, a few
+// MB of weights) are bound by the latency of each wave's chain of k steps instead: they take fewer rows
+// per workgroup (more workgroups) and, with DEPTH > 0, keep DEPTH of a wave's k steps in flight (the
+// loads of step i + DEPTH - 1 are issued before the MFMAs of step i; loads past the wave's last step are
+// clamped to that step, so that every load is unconditional and the compiler can count the loads in
+// flight). The sums run in the same order either way.
+template <int RB, int U, int DEPTH, bool ALL>
+__global__ void __launch_bounds__(256) gemv_mfma_kernel(GemvArgs a, const u16* __restrict__ xs, int b0, int nb) {
+  __shared__ f32x4 part[4][RB][64];
+  const int s = blockIdx.y;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int n0 = blockIdx.x * 16 * RB;
+  const int K = a.K, nks = K / 32;
+  const int r16 = lane & 15, kq = (lane >> 4) * 8;
+  const bool on = r16 < nb;
+  // operand A: rows n0 + 16 j + r16 (clamped; results of clamped rows are dropped)
+  const u16* W = (const u16*)a.W[s];
+  const u16* w[RB];
+#pragma unroll
+  for (int j = 0; j < RB; j++) w[j] = W + (int64_t)min(n0 + 16 * j + r16, a.N - 1) * K + kq;
+  // operand B: sample r16, hi and lo parts
+  const u16* xh = xs + (int64_t)r16 * K + kq;
+  const u16* xl = xs + (int64_t)(16 + r16) * K + kq;
+  f32x4 acc[RB];
+#pragma unroll
+  for (int j = 0; j < RB; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (DEPTH == 0) {
+    int ks = wave;
+    for (; ks + 4 * (U - 1) < nks; ks += 4 * U) {
+      GemvGroup<RB, U, ALL> g;
+      g.load(w, xh, xl, on, 32 * ks, 128);
+      g.mma(acc);
+    }
+    for (; ks < nks; ks += 4) {
+      GemvGroup<RB, 1, ALL> g;
+      g.load(w, xh, xl, on, 32 * ks, 0);
+      g.mma(acc);
+    }
+  } else {
+    // this wave's k steps are wave + 4 i, i < nloc; the first nmain of them run pipelined
+    const int nloc = nks > wave ? (nks - wave + 3) / 4 : 0;
+    const int nmain = nloc - nloc % DEPTH;
+    GemvGroup<RB, 1, ALL> g[DEPTH];
+    auto load = [&](int i, int slot) { g[slot].load(w, xh, xl, on, 32 * (wave + 4 * i), 0); };
+    if (nmain > 0) {
+#pragma unroll
+      for (int d = 0; d < DEPTH - 1; d++) load(d, d);
+      __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < nmain; i += DEPTH) {
+#pragma unroll
+        for (int u = 0; u < DEPTH; u++) {
+          load(min(i + u + DEPTH - 1, nloc - 1), (u + DEPTH - 1) % DEPTH);
+          __builtin_amdgcn_sched_barrier(0);   // keep the loads ahead of this step's MFMAs
+          g[u].mma(acc);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    for (int i = nmain; i < nloc; i++) {
+      load(i, 0);
+      g[0].mma(acc);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < RB; j++) part[wave][j][lane] = acc[j];
+  __syncthreads();
+  if (wave != 0) return;
+  // sum the 4 partials in a fixed order (deterministic)
+#pragma unroll
+  for (int q = 1; q < 4; q++)
+#pragma unroll
+    for (int j = 0; j < RB; j++) {
+      f32x4 p = part[q][j][lane];
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[j][r] += p[r];
+    }
+  gemv_finish<RB>(a, s, n0, acc, b0, nb);
+}
+
+// Many weight matrices at once (a step's batched modulation): a wave takes 16 RB rows over the whole of
+// K, the next two k steps loaded ahead, and the four waves of a workgroup walk the same k together, so
+// that the split input comes from L2 once for their 64 RB rows and from the CU's cache otherwise. Needs
+// many workgroups to fill the chip evenly (K a multiple of 64).
+template <int RB, bool ALL>
+__global__ void __launch_bounds__(256) gemv_rows_kernel(GemvArgs a, const u16* __restrict__ xs, int b0, int nb) {
+  constexpr int U = 2;
+  const int s = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int n0 = (blockIdx.x * 4 + wave) * 16 * RB, K = a.K, ng = K / (32 * U);
+  if (n0 >= a.N) return;
+  const int r16 = lane & 15, kq = (lane >> 4) * 8;
+  const bool on = r16 < nb;
+  const u16* w[RB];
+#pragma unroll
+  for (int j = 0; j < RB; j++) w[j] = (const u16*)a.W[s] + (int64_t)min(n0 + 16 * j + r16, a.N - 1) * K + kq;
+  const u16* xh = xs + (int64_t)r16 * K + kq;
+  const u16* xl = xs + (int64_t)(16 + r16) * K + kq;
+  f32x4 acc[RB];
+#pragma unroll
+  for (int j = 0; j < RB; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  GemvGroup<RB, U, ALL> g[2];
+  auto load = [&](int i, int slot) { g[slot].load(w, xh, xl, on, 32 * U * min(i, ng - 1), 32); };
+  load(0, 0);
+  for (int i = 0; i < ng; i += 2) {
+    load(i + 1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    g[0].mma(acc);
+    __builtin_amdgcn_sched_barrier(0);
+    load(i + 2, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + 1 < ng) g[1].mma(acc);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  gemv_finish<RB>(a, s, n0, acc, b0, nb);
+}
+
+template <int RB, int U, int DEPTH>
+static void gemv_mfma_launch(const GemvArgs& a, const u16* xs, int b0, int nb, hipStream_t s) {
+  const dim3 grid(cdiv(a.N, 16 * RB), a.nstreams);
+  if (nb == 16) gemv_mfma_kernel<RB, U, DEPTH, true><<<grid, 256, 0, s>>>(a, xs, b0, nb);
+  else gemv_mfma_kernel<RB, U, DEPTH, false><<<grid, 256, 0, s>>>(a, xs, b0, nb);
+}
+
 hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int input, const RopeArgs& rope, hipStream_t s) {
   if (a.N == 0 || a.B == 0) return hipSuccess;
   for (int b0 = 0; b0 < a.B; b0 += 16) {
@@ -946,19 +998,25 @@ hipError_t gemv_bf16(const GemvArgs& a, u16* xs, int input, const RopeArgs& rope
       split_hilo_kernel<<<16 * cdiv(a.K, 256) + (r.tab ? cdiv((int64_t)r.npos * (r.head_dim / 4), 256) : 0), 256, 0, s>>>(
           a.in, a.in_bstride, b0, nb, a.K, input == GEMV_SILU, xs, r);
     }
-    // rows per workgroup by grid size: the step's batched modulation (1.8 GB of weights) streams
-    // best with 128; a single block's (0.2 GB) with 64; the timestep and final-layer GEMVs (a few
-    // MB) need more workgroups and a pipelined k chain (lab, same box: 30 -> 18 us for 3072 x 3072,
-    // 31 -> 20 us for 6144 x 3072, bit-identical)
+    // By grid size and batch. Measured with cold weights of 18432 x 3072 per slot (us for 2 / 4 / 8 / 12 / 16
+    // slots): 64 rows per workgroup 70 / 115 / 220 / 335 / 445 with 16 samples, 64 / 111 / 206 / 315 / 414
+    // with 8; 32 rows with four k steps in flight 62 / 113 / 221 / 329 / 435 with 8, 57 / 102 / - / - / 385 with
+    // 4, 52 / 91 / 176 / 260 / 345 with 1; whole-K waves 75 / 146 / 222 / 298 / 374 with 16, 58 / 122 / 188 /
+    // 252 / 322 with 1. The timestep and final-layer GEMVs (a few MB) need more workgroups and a pipelined
+    // k chain (30 -> 18 us for 3072 x 3072).
     const int64_t ns = a.nstreams;
-    if ((int64_t)cdiv(a.N, 128) * ns >= 1024)
-      gemv_mfma_kernel<8, 1><<<dim3(cdiv(a.N, 128), a.nstreams), 256, 0, s>>>(a, xs, b0, nb);
-    else if ((int64_t)cdiv(a.N, 64) * ns >= 256)
-      gemv_mfma_kernel<4, 2><<<dim3(cdiv(a.N, 64), a.nstreams), 256, 0, s>>>(a, xs, b0, nb);
-    else if ((int64_t)cdiv(a.N, 32) * ns >= 192)
-      gemv_mfma_kernel<2, 1, 2><<<dim3(cdiv(a.N, 32), a.nstreams), 256, 0, s>>>(a, xs, b0, nb);
-    else
-      gemv_mfma_kernel<1, 1, 4><<<dim3(cdiv(a.N, 16), a.nstreams), 256, 0, s>>>(a, xs, b0, nb);
+    if ((int64_t)cdiv(a.N, 256) * ns >= 768) {
+      const dim3 grid(cdiv(a.N, 256), a.nstreams);
+      if (nb == 16) gemv_rows_kernel<4, true><<<grid, 256, 0, s>>>(a, xs, b0, nb);
+      else gemv_rows_kernel<4, false><<<grid, 256, 0, s>>>(a, xs, b0, nb);
+    } else if ((int64_t)cdiv(a.N, 64) * ns >= 256) {
+      if (nb <= 8 && (int64_t)cdiv(a.N, 64) * ns < (nb <= 4 ? 4096 : 1024)) gemv_mfma_launch<2, 4, 0>(a, xs, b0, nb, s);
+      else gemv_mfma_launch<4, 2, 0>(a, xs, b0, nb, s);
+    } else if ((int64_t)cdiv(a.N, 32) * ns >= 192) {
+      gemv_mfma_launch<2, 1, 2>(a, xs, b0, nb, s);
+    } else {
+      gemv_mfma_launch<1, 1, 4>(a, xs, b0, nb, s);
+    }
   }
   return hipGetLastError();
 }
