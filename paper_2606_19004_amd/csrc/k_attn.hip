@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_bf16(AttnArgs a) {
 // Bound by the fp32 matrix rate; 4 B H S^2 d flops.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256) attn_fwd_f32(AttnArgs a) {
+__global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
   constexpr int KB = D == 64 ? 32 : 16, NKB = KB / 16, LD = D + 4, NDB = D / 16, NKC = D / 16;
   constexpr int CPT = KB * D / 4 / 256;   // 16-byte chunks of K (and of V) each thread stages per tile
   __shared__ __attribute__((aligned(16))) float sk[2][KB * LD];
@@ -382,28 +382,28 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(AttnArgs a) {
   const float* Kg = (const float*)a.k + (int64_t)b * a.qs_b + (int64_t)h * a.qs_h;
   const float* Vg = (const float*)a.v + (int64_t)b * a.qs_b + (int64_t)h * a.qs_h;
   const int qi = blockIdx.x * 64 + wave * 16 + l16;
-  float4 qf[NKC];   // q[qi][16 c + 4 g + 0..3]
+  f32x4 qf[NKC];   // q[qi][16 c + 4 g + 0..3]
   {
     const float* qrow = Q + (int64_t)min(qi, S - 1) * a.qs_s;
 #pragma unroll
-    for (int c = 0; c < NKC; c++) qf[c] = *(const float4*)(qrow + 16 * c + 4 * g);
+    for (int c = 0; c < NKC; c++) qf[c] = *(const f32x4*)(qrow + 16 * c + 4 * g);
   }
-  float4 rk[CPT], rv[CPT];
+  f32x4 rk[CPT], rv[CPT];   // (ext_vector types: an array of float4 structures went to scratch memory here)
   auto fetch = [&](int kt) {   // rows past the end repeat the last key; their scores are masked
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
       const int idx = tid + 256 * i, row = idx / (D / 4), c = idx % (D / 4);
       const int64_t off = (int64_t)min(kt * KB + row, S - 1) * a.qs_s + 4 * c;
-      rk[i] = *(const float4*)(Kg + off);
-      rv[i] = *(const float4*)(Vg + off);
+      rk[i] = *(const f32x4*)(Kg + off);
+      rv[i] = *(const f32x4*)(Vg + off);
     }
   };
   auto stage = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
       const int idx = tid + 256 * i, row = idx / (D / 4), c = idx % (D / 4);
-      *(float4*)(&sk[buf][row * LD + 4 * c]) = rk[i];
-      *(float4*)(&sv[buf][row * LD + 4 * c]) = rv[i];
+      *(f32x4*)(&sk[buf][row * LD + 4 * c]) = rk[i];
+      *(f32x4*)(&sv[buf][row * LD + 4 * c]) = rv[i];
     }
   };
   f32x4 o[NDB];
@@ -418,19 +418,34 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(AttnArgs a) {
     const int buf = kt & 1;
     __syncthreads();   // tile kt is staged, and every wave is done with the other buffer
     if (kt + 1 < nt) fetch(kt + 1);
+    // A tile's K fragments are read in one go, and its V elements as soon as the score MFMAs are issued, so
+    // that neither MFMA chain waits for LDS operand by operand
     f32x4 s[NKB];
+    {
+      f32x4 kf[NKB][NKC];
 #pragma unroll
-    for (int kb = 0; kb < NKB; kb++) {
-      s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kb = 0; kb < NKB; kb++)
 #pragma unroll
-      for (int c = 0; c < NKC; c++) {
-        const float4 kf = *(const float4*)(&sk[buf][(16 * kb + l16) * LD + 16 * c + 4 * g]);
-        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.x, qf[c].x, s[kb], 0, 0, 0);
-        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.y, qf[c].y, s[kb], 0, 0, 0);
-        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.z, qf[c].z, s[kb], 0, 0, 0);
-        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf.w, qf[c].w, s[kb], 0, 0, 0);
-      }
+        for (int c = 0; c < NKC; c++) kf[kb][c] = *(const f32x4*)(&sk[buf][(16 * kb + l16) * LD + 16 * c + 4 * g]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kb = 0; kb < NKB; kb++) s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NKC; c++)
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+#pragma unroll
+          for (int kb = 0; kb < NKB; kb++)
+            s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][c][e], qf[c][e], s[kb], 0, 0, 0);
     }
+    float vf[NKB][4][NDB];
+#pragma unroll
+    for (int kb = 0; kb < NKB; kb++)
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int i = 0; i < NDB; i++) vf[kb][r][i] = sv[buf][(16 * kb + 4 * g + r) * LD + l16 + 16 * i];
+    __builtin_amdgcn_sched_barrier(0);
     float mx = -INFINITY;
 #pragma unroll
     for (int kb = 0; kb < NKB; kb++)
@@ -462,11 +477,9 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(AttnArgs a) {
 #pragma unroll
     for (int kb = 0; kb < NKB; kb++)
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const float* vr = &sv[buf][(16 * kb + 4 * g + r) * LD + l16];
+      for (int r = 0; r < 4; r++)
 #pragma unroll
-        for (int i = 0; i < NDB; i++) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[16 * i], s[kb][r], o[i], 0, 0, 0);
-      }
+        for (int i = 0; i < NDB; i++) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[kb][r][i], s[kb][r], o[i], 0, 0, 0);
     if (kt + 1 < nt) stage(buf ^ 1);
   }
   l_run += __shfl_xor(l_run, 16, 64);
