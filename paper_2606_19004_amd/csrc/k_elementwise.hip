@@ -524,13 +524,16 @@ hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, dou
 // workgroup) is read from L2 straight into operand A. Row sums and the eight partial tiles meet in LDS, in a
 // fixed order. Bound by reading x (and the fp32 residual) once.
 // ---------------------------------------------------------------------------
-// FULL: every wave has exactly NS steps, no test per step
-template <int NS, bool RES, bool FULL>
+// FULL: every wave has exactly NS steps, no test per step. ONE: no tile crosses samples, so a tile's
+// modulation vectors come through LDS once per workgroup (read from L2 by every wave for itself they are
+// half of the loads that a CU has to issue).
+template <int NS, bool RES, bool FULL, bool ONE>
 __global__ void __launch_bounds__(512, 4) final_head_kernel(FinalArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist only in the device pass
   constexpr int NW = 8;
   __shared__ float red[2][NW][16];
-  __shared__ f32x4 part[NW][4][64];
+  // the partial tiles, and before them the sample's shift and scale (at most 2 x 4096 floats)
+  __shared__ union { f32x4 part[NW][4][64]; float mod[2 * 4096]; } sm;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
   const int D = a.D, nks = D / 32;
   const int np = nks / 2, nloc = np > wave ? 2 * ((np - wave + NW - 1) / NW) : 0;   // this wave's k steps
@@ -574,6 +577,8 @@ __global__ void __launch_bounds__(512, 4) final_head_kernel(FinalArgs a) {
     if (FULL || i < nloc) xv[i] = load16(rx, xo, koff(i) * 2);
     else xv[i] = make_uint4(0u, 0u, 0u, 0u);
   }
+  if constexpr (ONE)
+    for (int q = threadIdx.x; q < D / 2; q += 64 * NW) ((uint4*)sm.mod)[q] = load16(rm, q * 16, 0);
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (RES) {
 #pragma unroll
@@ -633,8 +638,13 @@ __global__ void __launch_bounds__(512, 4) final_head_kernel(FinalArgs a) {
       float f[8], sh[8], sc[8];
       opaque(xv[i]);
       unpack(xv[i], f);
-      load_f8(rm, mo, koff(i) * 4, sh);
-      load_f8(rm, mo, (D + koff(i)) * 4, sc);
+      if constexpr (ONE) {
+        Vec8<float>::load(sm.mod + koff(i) + 8 * kq, sh);
+        Vec8<float>::load(sm.mod + D + koff(i) + 8 * kq, sc);
+      } else {
+        load_f8(rm, mo, koff(i) * 4, sh);
+        load_f8(rm, mo, (D + koff(i)) * 4, sc);
+      }
 #pragma unroll
       for (int e = 0; e < 8; e++) f[e] = fmaf((f[e] - mean) * rstd, 1.0f + sc[e], sh[e]);
       xv[i] = pack(f);
@@ -661,15 +671,16 @@ __global__ void __launch_bounds__(512, 4) final_head_kernel(FinalArgs a) {
       for (int j = 0; j < 4; j++)
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i & 1][j], __builtin_bit_cast(bf16x8, xv[i]), acc[j], 0, 0, 0);
     }
+  __syncthreads();   // every wave is done with the modulation vectors
 #pragma unroll
-  for (int j = 0; j < 4; j++) part[wave][j][lane] = acc[j];
+  for (int j = 0; j < 4; j++) sm.part[wave][j][lane] = acc[j];
   __syncthreads();
   if (wave >= 4) return;
   // wave j finishes features c0 + 16 j + 4 kq + 0..3 of row r16
-  f32x4 o = part[0][wave][lane];
+  f32x4 o = sm.part[0][wave][lane];
 #pragma unroll
   for (int q = 1; q < NW; q++) {
-    const f32x4 p = part[q][wave][lane];
+    const f32x4 p = sm.part[q][wave][lane];
 #pragma unroll
     for (int r = 0; r < 4; r++) o[r] += p[r];
   }
@@ -686,8 +697,10 @@ __global__ void __launch_bounds__(512, 4) final_head_kernel(FinalArgs a) {
 
 template <int NS, bool RES>
 static void final_head_ns(const FinalArgs& a, dim3 grid, hipStream_t s) {
-  if (a.D == 256 * NS) final_head_kernel<NS, RES, true><<<grid, 512, 0, s>>>(a);
-  else final_head_kernel<NS, RES, false><<<grid, 512, 0, s>>>(a);
+  const bool one = a.rows_per_batch % 16 == 0;
+  if (a.D == 256 * NS && one) final_head_kernel<NS, RES, true, true><<<grid, 512, 0, s>>>(a);
+  else if (one) final_head_kernel<NS, RES, false, true><<<grid, 512, 0, s>>>(a);
+  else final_head_kernel<NS, RES, false, false><<<grid, 512, 0, s>>>(a);
 }
 template <bool RES>
 static hipError_t final_head_launch(const FinalArgs& a, hipStream_t s) {
