@@ -329,9 +329,11 @@ dit_status dbg_ln(const LnArgs& a, size_t es) {
 #endif
 
 dit_status run_ln(const dit_block_config* c, int B, const void* x_img, const void* x_txt, const float* mod,
-                  char* ws, const BlockWs& L, int shift_off, int scale_off, hipStream_t s) {
+                  char* ws, const BlockWs& L, int shift_off, int scale_off, const GemmSplitWs& split, hipStream_t s) {
   const int D = c->hidden;
   LnArgs a{};
+  a.zero = split.counters;
+  a.nzero = 4 * split.max_tiles;
   a.x[0] = x_img;
   a.x[1] = x_txt;
   a.xmap[0] = stream_rows(c->n_img, D);
@@ -374,7 +376,13 @@ dit_status run_mlp_half(const dit_block_config* c, const dit_block_weights* w, i
   const int rows[2] = {B * c->n_img, B * c->n_txt};
   void* x[2] = {x_img, x_txt};
   const int64_t nstream[2] = {c->n_img, c->n_txt};
-  dit_status st = run_ln(c, B, x_img, x_txt, mod, ws, L, 3 * D, 4 * D, s);
+  // While the down-projection runs, the LayerNorm output and the QKV buffer (adjacent, 8 D bytes per row) are
+  // free for partial tiles, and the SiLU area, which only holds scratch, for their counters (cleared by the
+  // LayerNorm launch)
+  GemmSplitWs split{};
+  if (c->dtype == DIT_BF16 && L.xs - L.silu >= 4 * GEMM_SPLIT_TILES * sizeof(int))
+    split = GemmSplitWs{(float*)(ws + L.h), L.u - L.h, (int*)(ws + L.silu), GEMM_SPLIT_TILES};
+  dit_status st = run_ln(c, B, x_img, x_txt, mod, ws, L, 3 * D, 4 * D, split, s);
   if (st) return st;
   GemmPair up{}, down{};
   up.nprob = down.nprob = 2;
@@ -388,8 +396,8 @@ dit_status run_mlp_half(const dit_block_config* c, const dit_block_weights* w, i
   }
   DBG_CHECK(dbg_gemm(up, esize(c->dtype), "gemm_mlp_up_gelu"));
   DBG_CHECK(dbg_gemm(down, esize(c->dtype), "gemm_mlp_down_gate"));
-  TIMED("gemm_mlp_up_gelu", gemm_flops(up), 0, s, gemm(up, EPI_GELU, c->dtype, s));
-  TIMED("gemm_mlp_down_gate", gemm_flops(down), 0, s, gemm(down, EPI_RESID, c->dtype, s));
+  TIMED("gemm_mlp_up_gelu", gemm_flops(up), 0, s, gemm(up, EPI_GELU, c->dtype, GemmSplitWs{}, s));
+  TIMED("gemm_mlp_down_gate", gemm_flops(down), 0, s, gemm(down, EPI_RESID, c->dtype, split, s));
   return DIT_OK;
 }
 
@@ -502,7 +510,7 @@ dit_status run_patch(const dit_block_config* c, const dit_step_weights* w, int B
   GemmPair p{};
   p.nprob = 1;
   p.p[0] = problem(A, contiguous_rows(C), w->in_w, w->in_b, x_img, contiguous_rows(D), M, D, C);
-  TIMED("gemm_patch_embed", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, s));
+  TIMED("gemm_patch_embed", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, GemmSplitWs{}, s));
   return DIT_OK;
 }
 
@@ -586,7 +594,7 @@ dit_status run_final_head(const dit_block_config* c, const dit_step_weights* w, 
   GemmPair p{};
   p.nprob = 1;
   p.p[0] = problem(h, contiguous_rows(D), w->fout_w, w->fout_b, v, contiguous_rows(C), B * c->n_img, C, D);
-  TIMED("gemm_final", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, s));
+  TIMED("gemm_final", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, GemmSplitWs{}, s));
   return DIT_OK;
 }
 
@@ -666,7 +674,7 @@ dit_status block_body(const dit_block_config* c, const dit_block_weights* w, int
   if (!mod_pre && (st = run_modulation(c, w, B, temb, ws, L, rope_beside ? ra : RopeArgs{}, s))) return st;
   if (rope_due && !rope_beside) TIMED("small_elementwise", 0, 0, s, rope_table(ra, s));
   // pre-attention LN + modulate into h
-  if ((st = run_ln(c, B, x_img, x_txt, mod, ws, L, 0, D, s))) return st;
+  if ((st = run_ln(c, B, x_img, x_txt, mod, ws, L, 0, D, GemmSplitWs{}, s))) return st;
   // QKV projection straight into the joint [B][S][3][H][d] buffer (+ RoPE on image q, k)
   GemmPair qkv{};
   qkv.nprob = 2;
@@ -682,7 +690,7 @@ dit_status block_body(const dit_block_config* c, const dit_block_weights* w, int
     qkv.p[0].rope_npos = std::max(c->grid_h, c->grid_w);
   }
   DBG_CHECK(dbg_gemm(qkv, esize(c->dtype), "gemm_qkv_rope"));
-  TIMED("gemm_qkv_rope", gemm_flops(qkv), 0, s, gemm(qkv, EPI_QKV, c->dtype, s));
+  TIMED("gemm_qkv_rope", gemm_flops(qkv), 0, s, gemm(qkv, EPI_QKV, c->dtype, GemmSplitWs{}, s));
   // joint attention over [text ; image]; output o reuses the h buffer
   AttnArgs at{};
   char* qkvp = ws + L.qkv;
@@ -714,7 +722,7 @@ dit_status block_body(const dit_block_config* c, const dit_block_weights* w, int
     proj.p[i].gate_bstride = 6 * D;
   }
   DBG_CHECK(dbg_gemm(proj, esize(c->dtype), "gemm_out_gate"));
-  TIMED("gemm_out_gate", gemm_flops(proj), 0, s, gemm(proj, EPI_RESID, c->dtype, s));
+  TIMED("gemm_out_gate", gemm_flops(proj), 0, s, gemm(proj, EPI_RESID, c->dtype, GemmSplitWs{}, s));
   return run_mlp_half(c, w, B, x_img, x_txt, mod, ws, L, s);
 }
 

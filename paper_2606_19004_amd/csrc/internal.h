@@ -96,7 +96,16 @@ struct GemmPair {              // up to two problems (image stream, text stream)
 
 enum Dtype { DT_F32 = 0, DT_BF16 = 1 };
 
-hipError_t gemm(const GemmPair& pr, int epi, int dtype, hipStream_t s);
+// Scratch for a bf16 GEMM whose k range is shared out between workgroups (EPI_RESID): room for fp32 partial
+// tiles and counters that are zero when the launch starts, 4 per tile. bytes = 0: none.
+struct GemmSplitWs {
+  float* partials;
+  size_t bytes;
+  int* counters;
+  int max_tiles;
+};
+constexpr int GEMM_SPLIT_TILES = 128;   // more tiles than this fill the chip without a split
+hipError_t gemm(const GemmPair& pr, int epi, int dtype, const GemmSplitWs& split, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // attention
@@ -121,6 +130,7 @@ struct LnArgs {
   const float* mod[2]; int64_t mod_bstride; int shift_off, scale_off;
   int64_t rows[2];     // rows per stream (B * N_s)
   int D; float eps;
+  int* zero; int nzero;   // ints cleared by the way (counters of a later GEMM), or null
 };
 hipError_t ln_modulate(const LnArgs& a, int dtype, hipStream_t s);
 

@@ -286,6 +286,8 @@ hipError_t rope_table(const RopeArgs& r, hipStream_t s) {
 // ---------------------------------------------------------------------------
 template <typename T, int CH>
 __global__ void __launch_bounds__(256) ln_modulate_kernel(LnArgs a) {
+  if (a.zero && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < a.nzero; i += 256) a.zero[i] = 0;
   int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
   int64_t total = a.rows[0] + a.rows[1];

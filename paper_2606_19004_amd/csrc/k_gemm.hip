@@ -212,8 +212,13 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 // RING = 0 (256-row tiles): three LDS stages for A and two for W (160 KB), so the activation
 // operand is loaded two k-tiles ahead. RING > 0 (128 x 128 tiles): a ring of RING LDS stages of both
 // operands.
-template <int BM, int BN, int WM, int WN, int EPI, int RING = 0>
-__global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, int tiles0, int total_tiles) {
+// SPLIT (EPI_RESID): `splits` workgroups (2 or 3) share a tile, each over its part of K. All but the last one
+// to finish leave their accumulators in `split.partials`; the last adds them in the order of the parts
+// (so the result does not depend on which was last) and runs the epilogue. It waits only for workgroups
+// that have taken their ticket, that is, are storing, and wait for nothing themselves.
+template <int BM, int BN, int WM, int WN, int EPI, int RING = 0, bool SPLIT = false>
+__global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, int tiles0, int total_tiles, int splits,
+                                                                 GemmSplitWs split) {
   constexpr int MS = 16, KS = 32;                      // MFMA block and k depth
   constexpr bool TRI = RING == 0;
   constexpr int NW = WM * WN;
@@ -230,7 +235,10 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
   // XCD-aware tile index
   int per = gridDim.x >> 3;
   int t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  if (t >= total_tiles) return;
+  if (t >= (SPLIT ? total_tiles * splits : total_tiles)) return;
+  // parts are the slow index: an XCD's workgroups then share the panels of one part of K
+  const int part = SPLIT ? t / total_tiles : 0;
+  if constexpr (SPLIT) t -= part * total_tiles;
   int pi = t < tiles0 ? 0 : 1;
   const GemmProblem P = pr.p[pi];   // a copy: its fields stay in registers instead of being reloaded per use
   int tl = pi == 0 ? t : t - tiles0;
@@ -268,7 +276,8 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     return smem + (TRI ? 2 * W_BYTES + (kt % 3) * A_BYTES : (kt % (RING + TRI)) * (A_BYTES + W_BYTES) + W_BYTES);
   };
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  const uint64_t pa64 = (uint64_t)P.A, pw64 = (uint64_t)P.W;
+  const int kt_all = K / BK, kt0 = SPLIT ? part * kt_all / splits : 0;   // this workgroup's k-tiles start at kt0
+  const uint64_t pa64 = (uint64_t)P.A + (SPLIT ? kt0 * BK * 2 : 0), pw64 = (uint64_t)P.W + (SPLIT ? kt0 * BK * 2 : 0);
   // refills as one burst per operand: offsets carry -1024 i plus a 4 KB bias taken back from the base
   constexpr bool BA = TRI && (A_LOADS == 3 || A_LOADS == 4), BW = TRI && (W_LOADS == 3 || W_LOADS == 4);
   const uint64_t pa64b = pa64 - (BA ? 4096u : 0u), pw64b = pw64 - (BW ? 4096u : 0u);
@@ -305,7 +314,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
   const int wm = wave / WN, wn = wave % WN;
   // lane -> (fragment row inside an MS-row block, 8-element k chunk inside a KS step)
   const int frow = lane % MS, lkc = lane / MS;
-  const int nk = K / BK;
+  const int nk = SPLIT ? (part + 1) * kt_all / splits - kt0 : kt_all;
   int fwk[TI], fak[TJ];
 #pragma unroll
   for (int i = 0; i < TI; i++) fwk[i] = swz(wn * WTN + MS * i + frow);
@@ -472,6 +481,65 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     for (; kt + 1 < nk; kt++) step(kt, std::integral_constant<int, 1>());
     prefetch_epi();
     step(nk - 1, std::integral_constant<int, 2>());
+  }
+
+  if constexpr (SPLIT) {
+    // The exchange uses stores and loads of device scope (past this XCD's L2, the caches of different XCDs
+    // not being coherent), each completed before the count that announces it. Ordinary accesses with
+    // fences cost far more: a fence writes back, or drops, the whole L2 under every other workgroup
+    // (one-seed MLP down 177 us with them).
+    constexpr int DEVICE = 17;           // sc0 | sc1
+    int* cnt = split.counters + 4 * t;   // tickets taken, partial tiles stored, parts in slots 0 and 1
+    __syncthreads();                     // every wave is done with the operand tiles
+    int* bc = (int*)smem;
+    if (tid == 0) bc[0] = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int ticket = __builtin_amdgcn_readfirstlane(bc[0]);
+    constexpr uint32_t TILE_BYTES = BM * BN * 4, BLOCK = NW * 64 * 16;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (char*)split.partials + (size_t)t * (splits - 1) * TILE_BYTES, (short)0, (int)((splits - 1) * TILE_BYTES), 0x00020000);
+    auto load = [&](uint32_t slot, int blk) {
+      return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16, slot * TILE_BYTES + blk * BLOCK, DEVICE));
+    };
+    if (ticket < splits - 1) {
+#pragma unroll
+      for (int i = 0; i < TI; i++)
+#pragma unroll
+        for (int j = 0; j < TJ; j++)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, tid * 16,
+                                                 ticket * TILE_BYTES + (i * TJ + j) * BLOCK, DEVICE);
+      if (tid == 0) __hip_atomic_store(cnt + 2 + ticket, part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0) __hip_atomic_fetch_add(cnt + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    if (tid == 0) {
+      while (__hip_atomic_load(cnt + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < splits - 1) __builtin_amdgcn_s_sleep(2);
+      // which of the two slots holds the lower part
+      bc[1] = splits > 2 && __hip_atomic_load(cnt + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >
+                                __hip_atomic_load(cnt + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(bc[1]);
+    if (splits == 2) {
+#pragma unroll
+      for (int i = 0; i < TI; i++) {
+#pragma unroll
+        for (int j = 0; j < TJ; j++) acc[i][j] += load(0, i * TJ + j);
+        __builtin_amdgcn_sched_barrier(0);   // a row of blocks in flight: more would not fit the registers
+      }
+    } else {   // (p0 + p1) + p2, whichever of them this one is
+#pragma unroll
+      for (int i = 0; i < TI; i++) {
+#pragma unroll
+        for (int j = 0; j < TJ; j++) {
+          const f32x4 l = load(lo, i * TJ + j), h = load(lo ^ 1, i * TJ + j);
+          acc[i][j] = part == 2 ? (l + h) + acc[i][j] : (l + acc[i][j]) + h;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   }
 
   // ---- epilogue: bias, gate vectors and the RoPE table are staged in LDS once per tile ----
@@ -835,16 +903,17 @@ static hipError_t launch_ksplit(const GemmPair& pr, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int RING = 0>
-static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s) {
+template <int BM, int BN, int WM, int WN, int EPI, int RING = 0, bool SPLIT = false>
+static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s, int splits = 1, const GemmSplitWs& split = GemmSplitWs{}) {
   int tiles[2];
   const int total = count_tiles(pr, BM, BN, tiles);
   if (total == 0) return hipSuccess;
   constexpr size_t lds = RING == 0 ? (size_t)(2 * BN + 3 * BM) * 64 * 2 : RING * (size_t)(BM + BN) * 64 * 2;
   static std::atomic<bool> attr_set[64] = {};
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING>), lds, attr_set);
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT>), lds, attr_set);
   if (e != hipSuccess) return e;
-  gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING><<<8 * cdiv(total, 8), WM * WN * 64, lds, s>>>(pr, tiles[0], total);
+  gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT><<<8 * cdiv((int64_t)total * splits, 8), WM * WN * 64, lds, s>>>(
+      pr, tiles[0], total, splits, split);
   return hipGetLastError();
 }
 
@@ -873,7 +942,7 @@ static int cu_count() {
 // tiles leave part empty (QKV of one seed, 240 tiles against 180: 65 against 74 us); a text problem's own
 // launch of them, after the image rows' whole rounds, takes 0.83.
 enum Tile { TILE_32, TILE_64, TILE_128, TILE_192, TILE_256, TILE_256_192 };
-static Tile pick_tile(const GemmPair& pr) {
+static Tile pick_tile(const GemmPair& pr, const GemmSplitWs& split, int* splits) {
   int t[2];
   const int64_t cus = cu_count();
   const double kt = pr.p[0].K / 64;
@@ -896,12 +965,30 @@ static Tile pick_tile(const GemmPair& pr) {
   consider(TILE_128, rounds(count_tiles(pr, 128, 128, t), cus) * (0.59 * kt + 7.0));
   consider(TILE_64, rounds(count_tiles(pr, 64, 64, t), cus) * (0.30 * kt + 7.0));
   consider(TILE_32, rounds(count_tiles(pr, 32, 32, t), 2 * cus) * (0.22 * kt + 3.0));
+  // 256-row tiles with K shared out, where their partial tiles fit the scratch: 18 us more (24 for 256 x 256) for
+  // storing and adding those. One seed's MLP down at 512x512, 80 tiles in three parts: 125 us on 128 x 128
+  // tiles, 94 us; two seeds' (120 tiles in two parts of 256 x 256): 200 and 150 us.
+  *splits = 1;
+  if (split.bytes > 0)
+    for (int sp = 2; sp <= 3; sp++)
+      for (int bn = 192; bn <= 256; bn += 64) {
+        const int64_t n = count_tiles(pr, 256, bn, t);
+        if (n > split.max_tiles || kt < 8 * sp || (size_t)n * (sp - 1) * 256 * bn * 4 > split.bytes) continue;
+        const double c = rounds(n * sp, cus) * (bn == 192 ? 0.87 : 1.0) * (1.2 * kt / sp + 14.0) + (bn == 192 ? 18.0 : 24.0);
+        if (c < best) best = c, pick = bn == 192 ? TILE_192 : TILE_256, *splits = sp;
+      }
   return pick;
 }
 
 template <int EPI>
-static hipError_t dispatch_bf16(const GemmPair& pr, hipStream_t s) {
-  switch (pick_tile(pr)) {
+static hipError_t dispatch_bf16(const GemmPair& pr, const GemmSplitWs& split, hipStream_t s) {
+  int splits = 1;
+  const Tile tile = pick_tile(pr, split, &splits);
+  if constexpr (EPI == EPI_RESID) {
+    if (splits > 1 && tile == TILE_192) return launch_bf16<256, 192, 4, 2, EPI, 0, true>(pr, s, splits, split);
+    if (splits > 1) return launch_bf16<256, 256, 4, 2, EPI, 0, true>(pr, s, splits, split);
+  }
+  switch (tile) {
     case TILE_32: return launch_ksplit<32, EPI>(pr, s);
     case TILE_64: return launch_ksplit<64, EPI>(pr, s);
     case TILE_128: return launch_bf16<128, 128, 2, 4, EPI, 5>(pr, s);
@@ -1138,7 +1225,7 @@ static hipError_t launch_f32(const GemmPair& pr, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t gemm(const GemmPair& pr, int epi, int dtype, hipStream_t s) {
+hipError_t gemm(const GemmPair& pr, int epi, int dtype, const GemmSplitWs& split, hipStream_t s) {
   if (dtype == DT_F32) {
     switch (epi) {
       case EPI_STORE: return launch_f32<EPI_STORE>(pr, s);
@@ -1149,10 +1236,10 @@ hipError_t gemm(const GemmPair& pr, int epi, int dtype, hipStream_t s) {
     return hipErrorInvalidValue;
   }
   switch (epi) {
-    case EPI_STORE: return dispatch_bf16<EPI_STORE>(pr, s);
-    case EPI_GELU: return dispatch_bf16<EPI_GELU>(pr, s);
-    case EPI_RESID: return dispatch_bf16<EPI_RESID>(pr, s);
-    case EPI_QKV: return dispatch_bf16<EPI_QKV>(pr, s);
+    case EPI_STORE: return dispatch_bf16<EPI_STORE>(pr, GemmSplitWs{}, s);
+    case EPI_GELU: return dispatch_bf16<EPI_GELU>(pr, GemmSplitWs{}, s);
+    case EPI_RESID: return dispatch_bf16<EPI_RESID>(pr, split, s);
+    case EPI_QKV: return dispatch_bf16<EPI_QKV>(pr, GemmSplitWs{}, s);
   }
   return hipErrorInvalidValue;
 }
