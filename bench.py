@@ -135,7 +135,7 @@ def classify_dispatches(rows):
             cls = "attention"
         elif "ln_modulate_kernel" in n:
             cls = "ln_modulate"
-        elif "gemv_mfma_kernel<8" in n:   # only the batched modulation GEMV is large enough for 8 row blocks
+        elif "gemv_rows_kernel" in n:   # only a step's batched modulation has enough matrices for it
             cls = "mod_gemv"
         prev = cur
         out.append(cls)
@@ -195,8 +195,9 @@ def kernel_summary(run_dir, bench_json):
     lines += ["", f"bench.py (no profiler): {b['value']} ms per step; dominant kernel `{r['kernel']}` averaged "
               f"{r['avg_launch_us']} us per launch with HIP events ({r['achieved']} TFLOP/s, "
               f"{100 * r['frac']:.1f}% of {r['peak']}).",
-              "EPI codes in `gemm_bf16_kernel<BM, BN, WM, WN, EPI, OUTF32, MS, TRI>`: 0 plain store, 1 GELU (MLP up), "
-              "2 gated residual (output projection, MLP down), 3 QKV with 2D RoPE; MS is the MFMA block size; TRI marks three LDS stages for the activation operand (long K)."]
+              "EPI codes in `gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT>`: 0 plain store, 1 GELU (MLP up), "
+              "2 gated residual (output projection, MLP down), 3 QKV with 2D RoPE; RING is the number of LDS stages of "
+              "both operands (0: three of the activations, two of the weights); SPLIT marks K shared out between workgroups."]
     with open(os.path.join(ROOT, KERNEL_MD), "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines))
