@@ -389,7 +389,9 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
     for (int c = 0; c < NKC; c++) qf[c] = *(const f32x4*)(qrow + 16 * c + 4 * g);
   }
   f32x4 rk[CPT], rv[CPT];   // (ext_vector types: an array of float4 structures went to scratch memory here)
-  auto fetch = [&](int kt) {   // rows past the end repeat the last key; their scores are masked
+  // Rows past the end repeat the last key, whose scores are masked there, and are staged with a value of
+  // zero: their probability is 0, and 0 times an infinite value would be NaN
+  auto fetch = [&](int kt) {
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
       const int idx = tid + 256 * i, row = idx / (D / 4), c = idx % (D / 4);
@@ -398,12 +400,13 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
       rv[i] = *(const f32x4*)(Vg + off);
     }
   };
-  auto stage = [&](int buf) {
+  auto stage = [&](int kt) {
+    const int buf = kt & 1;
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
       const int idx = tid + 256 * i, row = idx / (D / 4), c = idx % (D / 4);
       *(f32x4*)(&sk[buf][row * LD + 4 * c]) = rk[i];
-      *(f32x4*)(&sv[buf][row * LD + 4 * c]) = rv[i];
+      *(f32x4*)(&sv[buf][row * LD + 4 * c]) = kt * KB + row < S ? rv[i] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
   f32x4 o[NDB];
@@ -480,7 +483,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
       for (int r = 0; r < 4; r++)
 #pragma unroll
         for (int i = 0; i < NDB; i++) o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[kb][r][i], s[kb][r], o[i], 0, 0, 0);
-    if (kt + 1 < nt) stage(buf ^ 1);
+    if (kt + 1 < nt) stage(kt + 1);
   }
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);

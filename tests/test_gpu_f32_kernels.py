@@ -56,3 +56,22 @@ def test_attention_f32_tile_edges(d, hd, seq):
     p = np.exp(s - s.max(-1, keepdims=True))
     want = (p / p.sum(-1, keepdims=True)) @ v
     assert np.max(np.abs(o.cpu().numpy() - want)) <= 1e-5 * np.max(np.abs(v))
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("seq", [1, 17, 33, 47, 64])
+def test_attention_f32_infinite_value_in_the_last_key(d, hd, seq):
+    """An infinite value stays in its own column, also where the last tile of keys is not full: every query gives
+    the last key a positive probability (scores of unit size), so that column is inf and the others are finite."""
+    b, h = 1, 2
+    g = torch.Generator(device="cuda").manual_seed(seq + hd)
+    qkv = torch.randn(b, seq, 3, h, hd, generator=g, device="cuda") * 0.1
+    clean = qkv.clone()
+    qkv[:, -1, 2, :, 5] = float("inf")
+    o = [torch.zeros(b, seq, h, hd, device="cuda") for _ in range(2)]
+    for x, out in zip((qkv, clean), o):
+        d.joint_attention(x[:, :, 0], x[:, :, 1], x[:, :, 2], out, b, h, seq, hd, (seq * 3 * h * hd, 3 * h * hd, hd),
+                          (seq * h * hd, h * hd, hd), dtype="f32")
+    assert torch.isposinf(o[0][..., 5]).all()
+    keep = [e for e in range(hd) if e != 5]
+    assert torch.equal(o[0][..., keep], o[1][..., keep])
