@@ -382,11 +382,15 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
   const float* Kg = (const float*)a.k + (int64_t)b * a.qs_b + (int64_t)h * a.qs_h;
   const float* Vg = (const float*)a.v + (int64_t)b * a.qs_b + (int64_t)h * a.qs_h;
   const int qi = blockIdx.x * 64 + wave * 16 + l16;
-  f32x4 qf[NKC];   // q[qi][16 c + 4 g + 0..3]
+  f32x4 qf[NKC];   // scale q[qi][16 c + 4 g + 0..3]: scaled before the products, which may overflow without
   {
     const float* qrow = Q + (int64_t)min(qi, S - 1) * a.qs_s;
 #pragma unroll
-    for (int c = 0; c < NKC; c++) qf[c] = *(const f32x4*)(qrow + 16 * c + 4 * g);
+    for (int c = 0; c < NKC; c++) {
+      qf[c] = *(const f32x4*)(qrow + 16 * c + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; e++) qf[c][e] *= a.scale;
+    }
   }
   f32x4 rk[CPT], rv[CPT];   // (ext_vector types: an array of float4 structures went to scratch memory here)
   // Rows past the end repeat the last key, whose scores are masked there, and are staged with a value of
@@ -412,7 +416,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
   f32x4 o[NDB];
 #pragma unroll
   for (int i = 0; i < NDB; i++) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float c2 = a.scale * 1.4426950408889634f;
+  constexpr float LOG2E = 1.4426950408889634f;
   float m_run = -INFINITY, l_run = 0.f;
   const int nt = cdiv(S, KB);
   fetch(0);
@@ -454,7 +458,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
     for (int kb = 0; kb < NKB; kb++)
 #pragma unroll
       for (int r = 0; r < 4; r++) {
-        s[kb][r] *= c2;
+        s[kb][r] *= LOG2E;
         if (kt * KB + 16 * kb + 4 * g + r >= S) s[kb][r] = -INFINITY;
         mx = fmaxf(mx, s[kb][r]);
       }

@@ -75,3 +75,21 @@ def test_attention_f32_infinite_value_in_the_last_key(d, hd, seq):
     assert torch.isposinf(o[0][..., 5]).all()
     keep = [e for e in range(hd) if e != 5]
     assert torch.equal(o[0][..., keep], o[1][..., keep])
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("size,scale", [(1e20, 1e-30), (1e-36, 3e38), (1e-36, -3e38)])
+def test_attention_f32_scale_of_any_size(d, hd, size, scale):
+    """Scores that fit fp32 while the unscaled products, or the scale in the exponential's base, do not. Large q and k
+    give scores some 1e10 apart (one key takes all); at 1e-36 sum|q k| scale is below 300, off by at most
+    (d + 2) 2^-24 of that = 2.3e-3, which moves the output by less than twice that of max|v|."""
+    b, h, seq = 1, 2, 37
+    g = torch.Generator(device="cuda").manual_seed(hd)
+    q, k, v = (torch.randn(b, seq, h, hd, generator=g, device="cuda") for _ in range(3))
+    q, k = q * size, k * (size if size > 1 else 1e-2)
+    o = torch.zeros(b, seq, h, hd, device="cuda")
+    d.joint_attention(q, k, v, o, b, h, seq, hd, (seq * h * hd, h * hd, hd), (seq * h * hd, h * hd, hd), scale=scale, dtype="f32")
+    qd, kd, vd = (t.permute(0, 2, 1, 3).double() for t in (q, k, v))
+    p = torch.softmax(qd @ kd.transpose(-1, -2) * scale, -1)
+    want = (p @ vd).permute(0, 2, 1, 3)
+    assert (o.double() - want).abs().max() <= (1e-5 if size > 1 else 4.6e-3) * v.abs().max()
