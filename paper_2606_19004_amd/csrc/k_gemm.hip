@@ -1113,7 +1113,9 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmPair pr, int tiles0, 
 // stands in the k loop and two slices of every wave are in flight; the four partial tiles meet in LDS
 // and are summed in a fixed order. A quarter of the serial chain of the 64 x 64 kernel per tile, at
 // twice its operand bytes per flop.
-template <int EPI>
+// WIDE: for rows so long that a tile's rows span more than a buffer descriptor addresses (2 GiB). The same
+// slices come through registers from 64-bit addresses.
+template <int EPI, bool WIDE>
 __global__ void __launch_bounds__(256) gemm_f32_ksplit_kernel(GemmPair pr, int tiles0, int total_tiles) {
   constexpr int BM = 32, BN = 32, STAGE = (BM + BN) * 128;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1131,12 +1133,18 @@ __global__ void __launch_bounds__(256) gemm_f32_ksplit_kernel(GemmPair pr, int t
   const u32x4_t ra = tile_rsrc((const float*)P.A + a0);
   const u32x4_t rw = tile_rsrc((const float*)P.W + (int64_t)n0 * P.K);
   uint32_t aoff[4], woff[4];
+  const char *ap[4], *wp[4];   // WIDE: the same addresses in full
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const int r = 8 * i + (lane >> 3);
     const uint32_t chunk = ((lane & 7) ^ swz(r)) * 16;
-    aoff[i] = (uint32_t)((row_offset(P.amap, min(m0 + r, P.M - 1)) - a0) * 4) + chunk;
-    woff[i] = (uint32_t)(min(n0 + r, P.N - 1) - n0) * (uint32_t)P.K * 4u + chunk;
+    const int64_t arow = row_offset(P.amap, min(m0 + r, P.M - 1)), wrow = min(n0 + r, P.N - 1);
+    aoff[i] = (uint32_t)((arow - a0) * 4) + chunk;
+    woff[i] = (uint32_t)(wrow - n0) * (uint32_t)P.K * 4u + chunk;
+    if constexpr (WIDE) {
+      ap[i] = (const char*)((const float*)P.A + arow) + chunk;
+      wp[i] = (const char*)((const float*)P.W + wrow * P.K) + chunk;
+    }
   }
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem + wave_s * 2 * STAGE;
@@ -1144,8 +1152,14 @@ __global__ void __launch_bounds__(256) gemm_f32_ksplit_kernel(GemmPair pr, int t
     const uint32_t base = lds0 + st * STAGE;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      dma_b128(ra, base + i * 1024, aoff[i], slice * 128);
-      dma_b128(rw, base + BM * 128 + i * 1024, woff[i], slice * 128);
+      if constexpr (WIDE) {
+        char* dst = smem + (wave_s * 2 + st) * STAGE + i * 1024 + lane * 16;
+        *(f32x4*)dst = *(const f32x4*)(ap[i] + (int64_t)slice * 128);
+        *(f32x4*)(dst + BM * 128) = *(const f32x4*)(wp[i] + (int64_t)slice * 128);
+      } else {
+        dma_b128(ra, base + i * 1024, aoff[i], slice * 128);
+        dma_b128(rw, base + BM * 128 + i * 1024, woff[i], slice * 128);
+      }
     }
   };
   const int r16 = lane & 15, kq = lane >> 4;
@@ -1218,8 +1232,12 @@ static hipError_t launch_f32(const GemmPair& pr, hipStream_t s) {
   // tiles' doubled operand traffic costs them about a quarter
   const int cus = cu_count();
   const double big = 32.0 * cdiv(total, cus), little = 1.25 * 8.0 * cdiv(total_small, cus);
-  if (little < big)
-    gemm_f32_ksplit_kernel<EPI><<<8 * cdiv(total_small, 8), 256, 0, s>>>(pr, small[0], total_small);
+  // and a tile's rows must lie within what its buffer descriptor addresses
+  const int64_t row = (int64_t)pr.p[0].K * 4, span = 0x7fffffff;
+  if (32 * row > span)
+    gemm_f32_ksplit_kernel<EPI, true><<<8 * cdiv(total_small, 8), 256, 0, s>>>(pr, small[0], total_small);
+  else if (little < big || 64 * row > span)
+    gemm_f32_ksplit_kernel<EPI, false><<<8 * cdiv(total_small, 8), 256, 0, s>>>(pr, small[0], total_small);
   else
     gemm_f32_kernel<EPI><<<8 * cdiv(total, 8), 256, 0, s>>>(pr, tiles[0], total);
   return hipGetLastError();

@@ -93,3 +93,23 @@ def test_attention_f32_scale_of_any_size(d, hd, size, scale):
     p = torch.softmax(qd @ kd.transpose(-1, -2) * scale, -1)
     want = (p @ vd).permute(0, 2, 1, 3)
     assert (o.double() - want).abs().max() <= (1e-5 if size > 1 else 4.6e-3) * v.abs().max()
+
+
+def test_gemm_f32_rows_past_2_gib_of_a_tile(d):
+    """An MLP so wide that the 32 rows of a down-projection tile span 2 GiB: everything is zero but the last element
+    of the last row, GELU(8) = 8 exactly in fp32."""
+    hidden, mlp = 64, 16777216 + 64
+    c = d.block_config(hidden, 1, 64, mlp, 1, 0, 1, 1, dtype="f32")
+    w = {k: torch.zeros(shp, device="cuda") for k, shp in
+         {"mod_w": (6 * hidden, hidden), "mod_b": (6 * hidden,), "qkv_w": (3 * hidden, hidden), "qkv_b": (3 * hidden,),
+          "out_w": (hidden, hidden), "out_b": (hidden,), "mlp1_w": (mlp, hidden), "mlp1_b": (mlp,), "mlp2_w": (hidden, mlp),
+          "mlp2_b": (hidden,)}.items()}
+    w["mod_b"][5 * hidden:] = 1.0                             # gate2
+    w["mlp1_b"][-1] = 8.0
+    w["mlp2_w"][-1, -1] = 1.0
+    x = torch.zeros(1, 1, hidden, device="cuda")
+    d.dit_block_mlp(c, d.block_weights(w, w), torch.zeros(1, hidden, device="cuda"), x, None,
+                    d.workspace(d.dit_block_workspace_bytes(c, 1)))
+    want = torch.zeros(hidden, device="cuda")
+    want[-1] = 8.0
+    assert torch.equal(x.view(-1), want)
