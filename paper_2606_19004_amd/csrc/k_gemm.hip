@@ -77,7 +77,14 @@ template <int EPI, typename TW, typename TC>
 __device__ __forceinline__ void epilogue4(const GemmProblem& P, const RowEpi& R, int n, float* v) {
   if (P.bias) {
     float b[4];
-    load4<TW>((const TW*)P.bias + n, b);
+    const TW* bias = (const TW*)P.bias + n;
+    // the biases outside a block are accepted at any element alignment
+    if (sizeof(TW) == 4 || ((uintptr_t)P.bias & 7) == 0) {
+      load4<TW>(bias, b);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; q++) b[q] = to_f32(bias[q]);
+    }
 #pragma unroll
     for (int q = 0; q < 4; q++) v[q] += b[q];
   }

@@ -24,7 +24,7 @@ def d():
     return ditstep
 
 
-def patch(d, b, n, hidden, k, skew=0):
+def patch(d, b, n, hidden, k, skew=0, bias_skew=None):
     g = torch.Generator(device="cuda").manual_seed(b * n + hidden + k)
     c = d.block_config(hidden, hidden // 64, 64, 4 * hidden, n, 0, 1, n)
     # at most 60 nonzero +-1 entries per row keep every partial sum an integer below 2^8
@@ -32,7 +32,8 @@ def patch(d, b, n, hidden, k, skew=0):
     pos = torch.rand(b * n, k, generator=g, device="cuda").argsort(1)[:, :nz]
     lat = torch.zeros(b * n, k, device="cuda").scatter_(1, pos, torch.randint(0, 2, (b * n, nz), generator=g, device="cuda") * 2.0 - 1)
     w = torch.randint(-1, 2, (hidden * k + skew,), generator=g, device="cuda").to(torch.bfloat16)[skew:].view(hidden, k)
-    bias = torch.randint(-2, 3, (hidden + skew,), generator=g, device="cuda").to(torch.bfloat16)[skew:]
+    bias_skew = skew if bias_skew is None else bias_skew
+    bias = torch.randint(-2, 3, (hidden + bias_skew,), generator=g, device="cuda").to(torch.bfloat16)[bias_skew:]
     z = torch.zeros(2 * hidden * max(hidden, 256), dtype=torch.bfloat16, device="cuda")
     sw = {nm: z for nm in ("t1_w", "t1_b", "t2_w", "t2_b", "fmod_w", "fmod_b", "fout_w", "fout_b")}
     sw["in_w"], sw["in_b"] = w, bias
@@ -58,6 +59,12 @@ def test_larger_tiles_exact(d, b, n, hidden, k):
 def test_weights_at_8_byte_alignment(d):
     for rows, hidden, k in ((33, 128, 256), (1281, 1536, 1024), (300, 3072, 512)):
         patch(d, 1, rows, hidden, k, skew=4)
+
+
+def test_patch_bias_at_any_element_alignment(d):
+    for rows, hidden, k in ((33, 128, 256), (200, 3072, 512), (1281, 1536, 1024), (16384, 3072, 64)):
+        for skew in (1, 2, 3):
+            patch(d, 1, rows, hidden, k, bias_skew=skew)
 
 
 # every epilogue with both streams in one launch: 32 x 32, 64 x 64 and 128 x 128 tiles by size
