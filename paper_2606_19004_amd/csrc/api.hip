@@ -1014,10 +1014,16 @@ struct StreamMark {
 // Where the distance's partial sums land on the host: 8 KB of pinned memory per calling thread, given back
 // when the thread ends (a copy to pageable memory goes through a staging copy and a wait of its own). A
 // call waits for its copy before it returns, so a thread's calls never share it.
+// A thread may end at any time, also while another one captures a graph in the global mode, which a free in
+// the thread's own default mode would invalidate; the memory is in no one's graph.
 struct HostPartials {
   double* p = nullptr;
   ~HostPartials() {
-    if (p) (void)hipHostFree(p);
+    if (!p) return;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipHostFree(p);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
 };
 dit_status host_partials(double** out) {

@@ -4,6 +4,7 @@ records only kernels and one device-to-device copy (no memset nodes), so it can 
 callers that run the step in a captured loop. Between replays the test runs eager work of its own
 and synchronises, and the in-place latent is restored from a saved copy before each replay."""
 import dataclasses
+import threading
 
 import numpy as np
 import pytest
@@ -66,3 +67,76 @@ def test_step_graph_replay_matches_eager(d, name, a):
         assert torch.equal(bufs["v"], v_e), f"replay {r}: velocity differs from the eager call"
         assert torch.equal(bufs["lat"], lat_e), f"replay {r}: latent differs from the eager call"
     del g, keep
+
+
+def gated_setup(d, cfg):
+    call, bufs, lat0, keep = setup_step(d, cfg)
+    inp = si.step_inputs(cfg)
+    c = block_cfg(d, cfg)
+    blocks = [d.block_weights(b["img"], b["txt"]) for b in keep[1]]
+    sw = d.step_weights(keep[0])
+    cache = d.workspace(d.dit_teacache_cache_bytes(c, cfg.batch))
+    st = d.teacache_state(1e9)
+
+    def step(t, tn, stream=None):
+        a = cfg.noise_level
+        return d.dit_denoise_step_teacache(c, sw, blocks, t, tn, a, bufs["lat"], bufs["xt"], bufs["eps"] if a > 0 else None,
+                                           bufs["v"], st, cache, bufs["ws"], stream=stream)
+    return step, st, bufs, lat0, keep
+
+
+@pytest.mark.parametrize("when", ["runs", "ends"])
+def test_gated_step_beside_another_threads_capture(d, when):
+    """A thread's first measuring gated step (which sets up the thread's landing place for the distance) runs while
+    another thread captures in the thread-local mode, or the thread ends (and gives it back) while another captures in
+    the global mode: the steps answer as they do alone, and the capture is not disturbed."""
+    cfg = si.CONFIGS["small_step_bf16"]
+    call, gbufs, glat0, gkeep = setup_step(d, cfg)
+    step, st, bufs, lat0, keep = gated_setup(d, cfg)
+    call()
+    call()
+    torch.cuda.synchronize()
+    want_lat, want_v = gbufs["lat"].clone(), gbufs["v"].clone()   # after two steps
+    gbufs["lat"].copy_(glat0)
+    alone = [step(0.8, 0.75), step(0.75, 0.7)]
+    torch.cuda.synchronize()
+    alone_v = bufs["v"].clone()
+    bufs["lat"].copy_(lat0)
+    st.has_prev = st.has_residual = 0
+    st.accumulated = 0.0
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    got, end = [], threading.Event()
+
+    def work():
+        try:
+            got.append(step(0.8, 0.75, stream=side))
+            got.append(step(0.75, 0.7, stream=side))
+        except Exception as e:   # reported by the assertion below
+            got.append(e)
+        stepped.set()
+        end.wait(30)
+
+    stepped, th, g = threading.Event(), threading.Thread(target=work), torch.cuda.CUDAGraph()
+    if when == "ends":
+        th.start()
+        stepped.wait(30)
+        torch.cuda.synchronize()
+    with torch.cuda.graph(g, capture_error_mode="thread_local" if when == "runs" else "global"):
+        call()
+        if when == "runs":
+            th.start()
+        end.set()
+        th.join()
+        call()
+    torch.cuda.synchronize()
+    assert [x if isinstance(x, Exception) else x[0] for x in got] == [True, False], got
+    assert got[1][1] == alone[1][1] and torch.equal(bufs["v"], alone_v)
+    for _ in range(3):
+        gbufs["lat"].copy_(glat0)
+        gbufs["v"].zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(gbufs["lat"], want_lat) and torch.equal(gbufs["v"], want_v)
+    del g, keep, gkeep
