@@ -998,14 +998,21 @@ TeaCacheLayout teacache_layout(const dit_block_config* c, int64_t B) {
   return L;
 }
 
-// A point of a stream's work that the host can wait for.
+// A point of a stream's work that the host can wait for. Where no event can mark it (none to be had, or the
+// stream belongs to a device that is not the current one), the wait is for all of the stream.
 struct StreamMark {
+  hipStream_t s;
   hipEvent_t e = nullptr;
-  hipError_t record(hipStream_t s) {
-    hipError_t r = hipEventCreateWithFlags(&e, hipEventDisableTiming);
-    return r != hipSuccess ? r : hipEventRecord(e, s);
+  bool marked = false;
+  explicit StreamMark(hipStream_t s_) : s(s_) {
+#ifdef DITSTEP_DEBUG
+    if (std::getenv("DITSTEP_DEBUG_NO_EVENT")) return;   // test hook
+#endif
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) e = nullptr;
+    marked = e && hipEventRecord(e, s) == hipSuccess;
+    if (!marked) (void)hipGetLastError();
   }
-  hipError_t wait() { return hipEventSynchronize(e); }
+  hipError_t wait() { return marked ? hipEventSynchronize(e) : hipStreamSynchronize(s); }
   ~StreamMark() {
     if (e) (void)hipEventDestroy(e);
   }
@@ -1116,8 +1123,7 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
     double* hp = nullptr;
     if ((st = host_partials(&hp))) return st;
     HIP_TRY(hipMemcpyAsync(hp, parts, (size_t)np * 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    StreamMark landed;
-    HIP_TRY(landed.record(s));
+    StreamMark landed(s);
     // the velocity head's modulation does not depend on the decision: it runs while the host waits for the
     // distance and comes back with the next launches
     st = run_final_mod(c, sw, B, temb, inner, xs_ready ? inner + BL.xs : nullptr, s);

@@ -56,3 +56,25 @@ def test_debug_build_refuses_an_operand_outside_the_known_buffers():
     assert r.returncode == 0, (r.stdout + r.stderr)[-4000:]
     last = r.stdout.strip().splitlines()[-1]
     assert last.startswith("refused DIT_ERR_INVALID_ARG") and "debug check: gemm_mlp_up_gelu" in last, last
+
+
+def test_gated_step_waits_without_an_event():
+    """Where no event can mark the distance's copy (a test hook of the debug build stands in for that), the gated step
+    waits for its whole stream and decides and answers the same."""
+    code = (
+        "import sys; sys.path.insert(0, '.')\n"
+        "import seeded_inputs as si, torch\n"
+        "from tests.test_gpu_graph import gated_setup\n"
+        "from paper_2606_19004_amd import ditstep as d\n"
+        "step, st, bufs, lat0, keep = gated_setup(d, si.CONFIGS['small_step_bf16'])\n"
+        "st.threshold = 0.3\n"
+        "out = [step(0.8 - 0.05 * i, 0.75 - 0.05 * i) for i in range(8)]\n"
+        "torch.cuda.synchronize()\n"
+        "print(repr(out), bufs['lat'].double().sum().item(), bufs['v'].double().sum().item())\n")
+    got = []
+    for extra in ({}, {"DITSTEP_DEBUG_NO_EVENT": "1"}):
+        env = dict(os.environ, DITSTEP_LIB=os.path.join(PKG, "libditstep_debug.so"), **extra)
+        r = subprocess.run([sys.executable, "-u", "-c", code], capture_output=True, text=True, timeout=300, cwd=ROOT, env=env)
+        assert r.returncode == 0, (r.stdout + r.stderr)[-4000:]
+        got.append(r.stdout.strip().splitlines()[-1])
+    assert got[0] == got[1] and "True" in got[0]
