@@ -158,15 +158,20 @@ RowMap joint_rows(const dit_block_config* c, int stream, int64_t cols) {
 RowMap stream_rows(int64_t n, int64_t cols) { return RowMap{std::max<int64_t>(n, 1), n * cols, cols, 0}; }
 
 // out = W act(in) + b with act = SiLU when silu_in: MFMA (hi/lo split) for bf16
-// weights, VALU for fp32 weights
+// weights, VALU for fp32 weights (which may first write SiLU(in) to silu_buf)
 // (split_ready: xs holds the split input already, bf16 only; rope: a table to fill beside it, bf16 only)
-dit_status run_gemv(const dit_block_config* c, GemvArgs g, bool silu_in, void* xs,
+dit_status run_gemv(const dit_block_config* c, GemvArgs g, bool silu_in, float* silu_buf, void* xs,
                     const char* name, hipStream_t s, bool split_ready = false, const RopeArgs& rope = RopeArgs{}) {
   double flops = 2.0 * g.nstreams * g.B * (double)g.N * g.K;
   double bytes = (double)g.nstreams * g.N * (double)g.K * esize(c->dtype);
   if (c->dtype == DIT_BF16) {
     TIMED(name, flops, bytes, s, gemv_bf16(g, (u16*)xs, split_ready ? GEMV_SPLIT : silu_in ? GEMV_SILU : GEMV_RAW, rope, s));
     return DIT_OK;
+  }
+  if (silu_in && !gemv_f32_folds_silu(g)) {
+    TIMED("small_elementwise", 0, (double)g.B * g.K * 8, s, silu_f32(g.in, silu_buf, (int64_t)g.B * g.in_bstride, s));
+    g.in = silu_buf;
+    silu_in = false;
   }
   TIMED(name, flops, bytes, s, gemv_f32(g, silu_in, s));
   return DIT_OK;
@@ -190,7 +195,7 @@ dit_status run_modulation(const dit_block_config* c, const dit_block_weights* w,
   g.K = D;
   g.B = B;
   g.nstreams = 2;
-  return run_gemv(c, g, true, ws + L.xs, "mod_gemv", s, false, rope);
+  return run_gemv(c, g, true, (float*)(ws + L.silu), ws + L.xs, "mod_gemv", s, false, rope);
 }
 
 // The modulation depends only on the timestep embedding, which every block of a step shares, so the
@@ -215,7 +220,7 @@ dit_status run_modulation_group(const dit_block_config* c, const dit_block_weigh
   g.K = D;
   g.B = B;
   g.nstreams = 2 * n;
-  return run_gemv(c, g, true, ws + L.xs, "mod_gemv", s, split_ready);
+  return run_gemv(c, g, true, (float*)(ws + L.silu), ws + L.xs, "mod_gemv", s, split_ready);
 }
 
 // h = LN(x)(1+scale)+shift for both streams into the joint [B][S][D] buffer
@@ -451,7 +456,7 @@ dit_status run_timestep_chain(const dit_block_config* c, const dit_step_weights*
   g.B = B;
   g.nstreams = 1;
   g.xs_out = xs_h;
-  dit_status st = run_gemv(c, g, false, xs_e, "timestep_gemv", s, true);
+  dit_status st = run_gemv(c, g, false, nullptr, xs_e, "timestep_gemv", s, true);
   if (st) return st;
   g.W[0] = w->t2_w;
   g.bias[0] = w->t2_b;
@@ -459,7 +464,7 @@ dit_status run_timestep_chain(const dit_block_config* c, const dit_step_weights*
   g.out_bstride = c->hidden;
   g.K = c->hidden;
   g.xs_out = xs_t;
-  return run_gemv(c, g, true, xs_h, "timestep_gemv", s, true);
+  return run_gemv(c, g, true, nullptr, xs_h, "timestep_gemv", s, true);
 }
 
 dit_status run_timestep(const dit_block_config* c, const dit_step_weights* w, int B, const float* t_dev, float t,
@@ -472,6 +477,7 @@ dit_status run_timestep(const dit_block_config* c, const dit_step_weights* w, in
   }
   float* e = (float*)ws;
   float* h1 = (float*)(ws + al256((size_t)B * 256 * 4));
+  float* s1 = (float*)(ws + al256((size_t)B * 256 * 4) + al256((size_t)B * D * 4));
   char* xs = ws + al256((size_t)B * 256 * 4) + 2 * al256((size_t)B * D * 4);
   TIMED("small_elementwise", 0, (double)B * 256 * 4, s, timestep_sinusoid(t_dev, t, e, B, s));
   GemvArgs g{};
@@ -485,7 +491,7 @@ dit_status run_timestep(const dit_block_config* c, const dit_step_weights* w, in
   g.K = 256;
   g.B = B;
   g.nstreams = 1;
-  dit_status st = run_gemv(c, g, false, xs, "timestep_gemv", s);
+  dit_status st = run_gemv(c, g, false, nullptr, xs, "timestep_gemv", s);
   if (st) return st;
   g.W[0] = w->t2_w;
   g.bias[0] = w->t2_b;
@@ -493,7 +499,7 @@ dit_status run_timestep(const dit_block_config* c, const dit_step_weights* w, in
   g.in = h1;
   g.in_bstride = D;
   g.K = D;
-  return run_gemv(c, g, true, xs, "timestep_gemv", s);
+  return run_gemv(c, g, true, s1, xs, "timestep_gemv", s);
 }
 
 // cast_ready: ws holds the latent in bf16 already
@@ -563,7 +569,7 @@ dit_status run_final_mod(const dit_block_config* c, const dit_step_weights* w, i
   g.K = D;
   g.B = B;
   g.nstreams = 1;
-  return run_gemv(c, g, true, xs_t ? xs_t : ws + L.xs, "final_gemv", s, xs_t != nullptr);
+  return run_gemv(c, g, true, (float*)ws, xs_t ? xs_t : ws + L.xs, "final_gemv", s, xs_t != nullptr);
 }
 // resid (bf16 only, may be null): added to x_img before the head
 dit_status run_final_head(const dit_block_config* c, const dit_step_weights* w, int B, int C, const void* x_img,
@@ -1102,7 +1108,7 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
   g.K = D;
   g.B = B;
   g.nstreams = 1;
-  if ((st = run_gemv(c, g, true, inner + BL.xs, "mod_gemv", s, xs_ready))) return st;
+  if ((st = run_gemv(c, g, true, (float*)(inner + BL.silu), inner + BL.xs, "mod_gemv", s, xs_ready))) return st;
   const bool measure = state->has_prev != 0;
   LnArgs la{};
   la.x[0] = ximg;

@@ -152,6 +152,8 @@ struct RopeArgs {
   float theta;
 };
 hipError_t gemv_f32(const GemvArgs& a, bool silu_in, hipStream_t s);   // VALU, fp32 weights; SiLU(in) when silu_in
+bool gemv_f32_folds_silu(const GemvArgs& a);   // whether silu_in beats a silu_f32 pass of its own
+hipError_t silu_f32(const float* in, float* out, int64_t n, hipStream_t s);
 // bf16 weights through MFMA on the input's two bf16 parts, xs [2][16][K], which are made here from a.in
 // (GEMV_RAW) or SiLU(a.in) (GEMV_SILU), or are there already (GEMV_SPLIT, B <= 16). The launch that makes
 // them also fills rope (tab null: none). K must be a multiple of 32

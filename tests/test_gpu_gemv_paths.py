@@ -83,3 +83,24 @@ def test_step_equals_its_parts(d, hidden, blocks, b, n_txt):
     assert torch.isfinite(v).all()
     assert (v - v2).abs().max() <= 2e-2 * v2.abs().max()
     assert np.isfinite(lat1.cpu().numpy()).all()
+
+
+# fp32: SiLU folded into the GEMV for few samples, a launch of its own past that (kernels of the second layer's
+# input: 0 or 1 beside the sinusoid). fp32 sums of up to 1088 terms: 1e-5 of max|temb|
+@pytest.mark.parametrize("hidden,b,apart", [(64, 2, 0), (64, 3, 1), (128, 4, 0), (512, 4, 0), (576, 2, 0), (576, 3, 1),
+                                            (512, 5, 1), (1088, 1, 0), (1088, 2, 1), (1088, 17, 1)])
+def test_timestep_embed_f32_silu(d, hidden, b, apart):
+    g = torch.Generator(device="cuda").manual_seed(hidden + b)
+    c = d.block_config(hidden, hidden // 64, 64, 64, 1, 0, 1, 1, dtype="f32")
+    sw = {k: v.float() for k, v in step_weights(g, hidden).items()}
+    t = torch.rand(b, generator=g, device="cuda")
+    temb = torch.full((b, hidden), 5.0, device="cuda")
+    d.dit_profile_begin()
+    d.dit_timestep_embed(c, d.step_weights(sw), t, temb, d.workspace(d.dit_denoise_workspace_bytes(c, b, 64)))
+    launches = {s["name"]: s["launches"] for s in d.dit_profile_end()}
+    assert launches == {"small_elementwise": 1 + apart, "timestep_gemv": 2}
+    f = 1e4 ** (-torch.arange(128, dtype=torch.float64, device="cuda") / 128)
+    arg = 1000.0 * t.double()[:, None] * f
+    h = torch.cat([torch.cos(arg), torch.sin(arg)], 1) @ sw["t1_w"].double().t() + sw["t1_b"].double()
+    want = (h / (1 + torch.exp(-h))) @ sw["t2_w"].double().t() + sw["t2_b"].double()
+    assert (temb.double() - want).abs().max() <= 1e-5 * want.abs().max()
