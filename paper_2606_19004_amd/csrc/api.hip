@@ -374,6 +374,14 @@ GemmProblem problem(const void* A, RowMap am, const void* W, const void* bias, v
   return p;
 }
 
+// While the MLP's down-projection runs, the LayerNorm output and the QKV buffer (adjacent, 8 D bytes per row)
+// are free for partial tiles, and the SiLU area, which only holds scratch, for their counters (cleared by the
+// LayerNorm launch)
+GemmSplitWs mlp_split_ws(const dit_block_config* c, char* ws, const BlockWs& L) {
+  if (c->dtype != DIT_BF16 || L.xs - L.silu < 4 * GEMM_SPLIT_TILES * sizeof(int)) return GemmSplitWs{};
+  return GemmSplitWs{(float*)(ws + L.h), L.u - L.h, (int*)(ws + L.silu), GEMM_SPLIT_TILES};
+}
+
 // the MLP half: h2 = LN(x)(1+scale2)+shift2; u = GELU(W1 h2 + b1); x += gate2 (W2 u + b2)
 dit_status run_mlp_half(const dit_block_config* c, const dit_block_weights* w, int B, void* x_img, void* x_txt,
                         const float* mod, char* ws, const BlockWs& L, hipStream_t s) {
@@ -381,12 +389,7 @@ dit_status run_mlp_half(const dit_block_config* c, const dit_block_weights* w, i
   const int rows[2] = {B * c->n_img, B * c->n_txt};
   void* x[2] = {x_img, x_txt};
   const int64_t nstream[2] = {c->n_img, c->n_txt};
-  // While the down-projection runs, the LayerNorm output and the QKV buffer (adjacent, 8 D bytes per row) are
-  // free for partial tiles, and the SiLU area, which only holds scratch, for their counters (cleared by the
-  // LayerNorm launch)
-  GemmSplitWs split{};
-  if (c->dtype == DIT_BF16 && L.xs - L.silu >= 4 * GEMM_SPLIT_TILES * sizeof(int))
-    split = GemmSplitWs{(float*)(ws + L.h), L.u - L.h, (int*)(ws + L.silu), GEMM_SPLIT_TILES};
+  const GemmSplitWs split = mlp_split_ws(c, ws, L);
   dit_status st = run_ln(c, B, x_img, x_txt, mod, ws, L, 3 * D, 4 * D, split, s);
   if (st) return st;
   GemmPair up{}, down{};
@@ -1167,6 +1170,34 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;
 }
+
+#ifdef DITSTEP_DEBUG
+// Debug builds, for tests of the tile rule: how the bf16 GEMM `op` of a call on (cfg, batch, latent_dim) would
+// run, out = {tile rows, tile columns, columns of a second launch's tiles or 0, workgroups per tile}.
+// op: 0 patch embedding, 1 QKV, 2 output projection, 3 MLP up, 4 MLP down. Host only.
+dit_status dit_debug_gemm_plan(const dit_block_config* c, int32_t batch, int32_t latent_dim, int32_t op, int32_t* out) {
+  dit_status st = check_config(c);
+  if (st) return st;
+  if (c->dtype != DIT_BF16 || batch < 1 || op < 0 || op > 4 || !out)
+    return set_error(DIT_ERR_INVALID_ARG, "bf16, batch >= 1 and op 0..4 only");
+  const int D = c->hidden, F = c->mlp_hidden;
+  const int N[5] = {D, 3 * D, D, F, D}, K[5] = {latent_dim, D, D, D, F};
+  const int epi[5] = {EPI_STORE, EPI_QKV, EPI_RESID, EPI_GELU, EPI_RESID};
+  GemmPair pr{};
+  pr.nprob = op == 0 ? 1 : 2;
+  for (int i = 0; i < pr.nprob; i++) {
+    pr.p[i].M = batch * (i == 0 ? c->n_img : c->n_txt);
+    pr.p[i].N = N[op];
+    pr.p[i].K = K[op];
+  }
+  const GemmPlan p = gemm_plan(pr, epi[op], op == 4 ? mlp_split_ws(c, nullptr, block_layout(c, batch)) : GemmSplitWs{});
+  out[0] = p.tile_m;
+  out[1] = p.tile_n;
+  out[2] = p.second_n;
+  out[3] = p.splits;
+  return DIT_OK;
+}
+#endif
 
 dit_status dit_profile_begin(void) {
   std::lock_guard<std::mutex> g(g_prof.mu);

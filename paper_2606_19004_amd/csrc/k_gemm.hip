@@ -987,6 +987,15 @@ static Tile pick_tile(const GemmPair& pr, const GemmSplitWs& split, int* splits)
   return pick;
 }
 
+GemmPlan gemm_plan(const GemmPair& pr, int epi, const GemmSplitWs& split) {
+  GemmPlan p{0, 0, 0, 1};
+  const Tile t = pick_tile(pr, epi == EPI_RESID ? split : GemmSplitWs{}, &p.splits);
+  p.tile_m = t == TILE_32 ? 32 : t == TILE_64 ? 64 : t == TILE_128 ? 128 : 256;
+  p.tile_n = t == TILE_192 ? 192 : p.tile_m;
+  p.second_n = t == TILE_256_192 ? 192 : 0;
+  return p;
+}
+
 template <int EPI>
 static hipError_t dispatch_bf16(const GemmPair& pr, const GemmSplitWs& split, hipStream_t s) {
   int splits = 1;
