@@ -1173,7 +1173,8 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
 
 #ifdef DITSTEP_DEBUG
 // Debug builds, for tests of the tile rule: how the bf16 GEMM `op` of a call on (cfg, batch, latent_dim) would
-// run, out = {tile rows, tile columns, columns of a second launch's tiles or 0, workgroups per tile}.
+// run, out = {tile rows, tile columns, columns of a second launch's tiles or 0, workgroups per tile,
+// LDS stages of a ring kernel or 0}.
 // op: 0 patch embedding, 1 QKV, 2 output projection, 3 MLP up, 4 MLP down. Host only.
 dit_status dit_debug_gemm_plan(const dit_block_config* c, int32_t batch, int32_t latent_dim, int32_t op, int32_t* out) {
   dit_status st = check_config(c);
@@ -1195,6 +1196,7 @@ dit_status dit_debug_gemm_plan(const dit_block_config* c, int32_t batch, int32_t
   out[1] = p.tile_n;
   out[2] = p.second_n;
   out[3] = p.splits;
+  out[4] = p.ring;
   return DIT_OK;
 }
 #endif

@@ -107,9 +107,9 @@ struct GemmSplitWs {
 constexpr int GEMM_SPLIT_TILES = 128;   // more tiles than this fill the chip without a split
 hipError_t gemm(const GemmPair& pr, int epi, int dtype, const GemmSplitWs& split, hipStream_t s);
 // how gemm() runs a bf16 pair: the tile, the tile width of a launch of its own for the second problem (0: one
-// launch), and the number of workgroups that share a tile's K
+// launch), the number of workgroups that share a tile's K, and the LDS stages of both operands (0: other kernels)
 struct GemmPlan {
-  int tile_m, tile_n, second_n, splits;
+  int tile_m, tile_n, second_n, splits, ring;
 };
 GemmPlan gemm_plan(const GemmPair& pr, int epi, const GemmSplitWs& split);
 

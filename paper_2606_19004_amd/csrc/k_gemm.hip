@@ -217,8 +217,8 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 // The 16x16x32 MFMA form delivers more throughput per watt than 32x32x16 under sustained load with
 // random operands on this chip.
 // RING = 0 (256-row tiles): three LDS stages for A and two for W (160 KB), so the activation
-// operand is loaded two k-tiles ahead. RING > 0 (128 x 128 tiles): a ring of RING LDS stages of both
-// operands.
+// operand is loaded two k-tiles ahead. RING > 0 (128 x 128 and, for short K, 64 x 64 tiles): a ring of RING
+// LDS stages of both operands.
 // SPLIT (EPI_RESID): `splits` workgroups (2 or 3) share a tile, each over its part of K. All but the last one
 // to finish leave their accumulators in `split.partials`; the last adds them in the order of the parts
 // (so the result does not depend on which was last) and runs the epilogue. It waits only for workgroups
@@ -442,8 +442,9 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     // All RING stages are filled up front; the hand-over from tile kt to kt + 1 sits before the last
     // step's MFMAs, whose fragments are in registers: wait until tile kt + 1 has landed (the loads of
     // the RING - 2 tiles after it stay in flight), barrier, then stage kt % RING, which every wave has
-    // read, takes tile kt + RING. Three to four k-tiles (96-128 KB) are on their way at any time, which
-    // is what covers the memory latency when a CU holds this one workgroup.
+    // read, takes tile kt + RING. With five stages three to four k-tiles (96-128 KB) are on their way at any
+    // time, which is what covers the memory latency when a CU holds this one workgroup; with two stages
+    // the other workgroups of the CU do.
     constexpr int L = A_LOADS + W_LOADS;
     static_assert(RING <= 1 || (RING - 2) * L <= 15, "the waits below use the low four bits of vmcnt");
     auto wait_tiles = [&](int n) {   // at most the loads of n tiles in flight, LDS reads done
@@ -948,10 +949,22 @@ static int cu_count() {
 // of a 256 x 256 round (17% more operand bytes per flop) and win where they fill a round that 256 x 256
 // tiles leave part empty (QKV of one seed, 240 tiles against 180: 65 against 74 us); a text problem's own
 // launch of them, after the image rows' whole rounds, takes 0.83.
-enum Tile { TILE_32, TILE_64, TILE_128, TILE_192, TILE_256, TILE_256_192 };
-static Tile pick_tile(const GemmPair& pr, const GemmSplitWs& split, int* splits) {
+enum Tile { TILE_32, TILE_64, TILE_64_RING, TILE_128, TILE_192, TILE_256, TILE_256_192 };
+static Tile pick_tile(const GemmPair& pr, bool plain, const GemmSplitWs& split, int* splits) {
   int t[2];
   const int64_t cus = cu_count();
+  *splits = 1;
+  // Plain stores of short K (the patch embedding) are bound by what a tile costs besides its k loop, which the
+  // estimates below, made for long K, do not tell apart. 64 x 64 tiles in a ring of two stages (32 KB, up to
+  // five workgroups per CU: one's stores overlap another's loads) win where they give every second CU one and
+  // no CU more than six, and at one or two k-tiles also below that. With the rounding of the latent, this / the
+  // tile picked below / the former 64 x 64 and 128 x 128 tiles of two stages (us): 9000 x 64, K 64: 6.4 / 8.5 /
+  // 6.5; 1000 x 640, K 128: 6.2 / 8.0 / 8.6; 4096 x 1280, K 64: 9.5 / 11.5 / 11.8, K 512: 19.7 / 22.8 / 20.6;
+  // outside, 360 x 640, K 512: 9.1 / 6.8 / 12.2; 16384 x 1280, K 512: 51.4 / 44.8 / 48.8.
+  if (plain && pr.p[0].K <= 512) {
+    const int64_t n = count_tiles(pr, 64, 64, t);
+    if (n <= 6 * cus && (2 * n >= cus || pr.p[0].K <= 128)) return TILE_64_RING;
+  }
   const double kt = pr.p[0].K / 64;
   auto rounds = [&](int64_t tiles, int64_t slots) { return (double)((tiles + slots - 1) / slots); };
   const double r256 = 1.2 * kt + 14.0;
@@ -975,7 +988,6 @@ static Tile pick_tile(const GemmPair& pr, const GemmSplitWs& split, int* splits)
   // 256-row tiles with K shared out, where their partial tiles fit the scratch: 18 us more (24 for 256 x 256) for
   // storing and adding those. One seed's MLP down at 512x512, 80 tiles in three parts: 125 us on 128 x 128
   // tiles, 94 us; two seeds' (120 tiles in two parts of 256 x 256): 200 and 150 us.
-  *splits = 1;
   if (split.bytes > 0)
     for (int sp = 2; sp <= 3; sp++)
       for (int bn = 192; bn <= 256; bn += 64) {
@@ -988,18 +1000,20 @@ static Tile pick_tile(const GemmPair& pr, const GemmSplitWs& split, int* splits)
 }
 
 GemmPlan gemm_plan(const GemmPair& pr, int epi, const GemmSplitWs& split) {
-  GemmPlan p{0, 0, 0, 1};
-  const Tile t = pick_tile(pr, epi == EPI_RESID ? split : GemmSplitWs{}, &p.splits);
-  p.tile_m = t == TILE_32 ? 32 : t == TILE_64 ? 64 : t == TILE_128 ? 128 : 256;
+  GemmPlan p{0, 0, 0, 1, 0};
+  const Tile t = pick_tile(pr, epi == EPI_STORE, epi == EPI_RESID ? split : GemmSplitWs{}, &p.splits);
+  p.tile_m = t == TILE_32 ? 32 : t == TILE_64 || t == TILE_64_RING ? 64 : t == TILE_128 ? 128 : 256;
   p.tile_n = t == TILE_192 ? 192 : p.tile_m;
   p.second_n = t == TILE_256_192 ? 192 : 0;
+  p.ring = t == TILE_64_RING ? 2 : t == TILE_128 ? 5 : 0;
   return p;
 }
 
 template <int EPI>
 static hipError_t dispatch_bf16(const GemmPair& pr, const GemmSplitWs& split, hipStream_t s) {
   int splits = 1;
-  const Tile tile = pick_tile(pr, split, &splits);
+  constexpr bool PLAIN = EPI == EPI_STORE;
+  const Tile tile = pick_tile(pr, PLAIN, split, &splits);
   if constexpr (EPI == EPI_RESID) {
     if (splits > 1 && tile == TILE_192) return launch_bf16<256, 192, 4, 2, EPI, 0, true>(pr, s, splits, split);
     if (splits > 1) return launch_bf16<256, 256, 4, 2, EPI, 0, true>(pr, s, splits, split);
@@ -1007,6 +1021,9 @@ static hipError_t dispatch_bf16(const GemmPair& pr, const GemmSplitWs& split, hi
   switch (tile) {
     case TILE_32: return launch_ksplit<32, EPI>(pr, s);
     case TILE_64: return launch_ksplit<64, EPI>(pr, s);
+    case TILE_64_RING:
+      if constexpr (PLAIN) return launch_bf16<64, 64, 2, 2, EPI, 2>(pr, s);
+      break;
     case TILE_128: return launch_bf16<128, 128, 2, 4, EPI, 5>(pr, s);
     case TILE_192: return launch_bf16<256, 192, 4, 2, EPI>(pr, s);
     case TILE_256: return launch_bf16<256, 256, 4, 2, EPI>(pr, s);

@@ -11,11 +11,12 @@ _lib = None
 
 
 def gemm_plan(cfg, batch, op, latent_dim=64):
-    """(tile rows, tile columns, columns of a second launch's tiles or 0, workgroups that share a tile's K)"""
+    """(tile rows, tile columns, columns of a second launch's tiles or 0, workgroups that share a tile's K, LDS stages of
+    a ring kernel or 0)"""
     global _lib
     if _lib is None:
         _lib = C.CDLL(LIB)
         _lib.dit_debug_gemm_plan.argtypes = [C.POINTER(ditstep.BlockConfig), C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
-    out = (C.c_int32 * 4)()
+    out = (C.c_int32 * 5)()
     assert _lib.dit_debug_gemm_plan(C.byref(cfg), batch, latent_dim, OPS.index(op), out) == 0
     return tuple(out)

@@ -14,6 +14,7 @@ import seeded_inputs as si
 from oracle import dit_oracle as O
 from tests.conftest import weights_f64
 from tests.gpu_util import block_cfg, dev, host64, rel_err, upload_block
+from tests.plan_util import gemm_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -54,6 +55,15 @@ def test_small_tiles_exact(d, rows, hidden, k):
 @pytest.mark.parametrize("b,n,hidden", [(2, 161, 3072), (3, 427, 1536), (5, 205, 3008), (1, 1024, 3072), (4, 1000, 2048)])
 def test_larger_tiles_exact(d, b, n, hidden, k):
     patch(d, b, n, hidden, k)
+
+
+# 64 x 64 tiles in a ring of two stages: one to many k-tiles, whole and ragged rows, one tile to six per compute unit
+@pytest.mark.parametrize("rows,hidden,k", [(1, 64, 64), (65, 128, 128), (2177, 320, 64), (1000, 640, 192), (8193, 64, 256),
+                                           (700, 3072, 320), (1999, 3072, 512), (24575, 256, 448)])
+def test_short_k_ring_exact(d, rows, hidden, k):
+    c = d.block_config(hidden, hidden // 64, 64, 4 * hidden, rows, 0, 1, rows)
+    assert gemm_plan(c, 1, "patch", k) == (64, 64, 0, 1, 2)
+    patch(d, 1, rows, hidden, k)
 
 
 def test_weights_at_8_byte_alignment(d):
