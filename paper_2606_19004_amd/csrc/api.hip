@@ -574,18 +574,20 @@ dit_status run_final_mod(const dit_block_config* c, const dit_step_weights* w, i
   g.nstreams = 1;
   return run_gemv(c, g, true, (float*)ws, xs_t ? xs_t : ws + L.xs, "final_gemv", s, xs_t != nullptr);
 }
-// resid (bf16 only, may be null): added to x_img before the head
+// resid (may be null): added to x_img, which is the step's own then, before the head
 dit_status run_final_head(const dit_block_config* c, const dit_step_weights* w, int B, int C, const void* x_img,
                           const float* resid, float* v, char* ws, hipStream_t s) {
   const int D = c->hidden;
   const FinalWs L = final_layout(c, B);
   const float* fm = (const float*)(ws + L.fm);
   char* h = ws + L.h;
-  if (c->dtype == DIT_BF16) {
-    FinalArgs f{x_img, resid, fm, w->fout_w, w->fout_b, v, (int64_t)B * c->n_img, c->n_img, D, C, c->ln_eps};
+  const FinalArgs f{x_img, resid, fm, w->fout_w, w->fout_b, v, (int64_t)B * c->n_img, c->n_img, D, C, c->ln_eps};
+  if (c->dtype == DIT_BF16 && final_head_in_one_pass(f)) {
     TIMED("final_head", 2.0 * f.M * D * C, (resid ? 6.0 : 2.0) * f.M * D, s, final_head(f, s));
     return DIT_OK;
   }
+  if (resid)
+    TIMED("small_elementwise", 0, 0, s, teacache_residual(const_cast<void*>(x_img), const_cast<float*>(resid), f.M * D, 2, c->dtype, s));
   LnArgs a{};
   a.x[0] = x_img;
   a.xmap[0] = stream_rows(c->n_img, D);
@@ -603,7 +605,8 @@ dit_status run_final_head(const dit_block_config* c, const dit_step_weights* w, 
   GemmPair p{};
   p.nprob = 1;
   p.p[0] = problem(h, contiguous_rows(D), w->fout_w, w->fout_b, v, contiguous_rows(C), B * c->n_img, C, D);
-  TIMED("gemm_final", gemm_flops(p), 0, s, gemm(p, EPI_STORE, c->dtype, GemmSplitWs{}, s));
+  TIMED("gemm_final", gemm_flops(p), 0, s,
+        gemm(p, c->dtype == DIT_BF16 ? EPI_STORE_F32 : EPI_STORE, c->dtype, GemmSplitWs{}, s));
   return DIT_OK;
 }
 
@@ -1160,12 +1163,10 @@ dit_status dit_denoise_step_teacache(const dit_block_config* c, const dit_step_w
     if ((st = run_blocks(c, blocks, n_blocks, B, temb, ximg, xtxt, mods, inner, BL, xs_ready, s))) return st;
     TIMED("small_elementwise", 0, 0, s, teacache_residual(ximg, resid, n_act, 1, c->dtype, s));
     state->has_residual = 1;
-  } else if (c->dtype != DIT_BF16) {   // bf16: the velocity head adds the residual as it reads x
-    TIMED("small_elementwise", 0, 0, s, teacache_residual(ximg, resid, n_act, 2, c->dtype, s));
   }
   if (ran_blocks) *ran_blocks = run;
   if (rel) *rel = r;
-  if ((st = run_final_head(c, sw, B, C, ximg, !run && c->dtype == DIT_BF16 ? resid : nullptr, v, inner, s))) return st;
+  if ((st = run_final_head(c, sw, B, C, ximg, run ? nullptr : resid, v, inner, s))) return st;
   TIMED("flow_step", 0, (noise_level > 0.f ? 16.0 : 12.0) * B * c->n_img * C, s,
         flow_update(latent, v, noise_level > 0.f ? noise : nullptr, (int64_t)B * c->n_img * C, cx, cv, ce, s));
   return DIT_OK;

@@ -74,7 +74,8 @@ __host__ __device__ __forceinline__ int cdiv(int64_t a, int64_t b) { return (int
 // ---------------------------------------------------------------------------
 // GEMM: C[m][n] = epilogue( sum_k A[m][k] W[n][k] + bias[n] ), W stored [N][K]
 // ---------------------------------------------------------------------------
-enum Epi { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_QKV = 3 };
+// (EPI_STORE_F32: fp32 output of a bf16 problem)
+enum Epi { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_QKV = 3, EPI_STORE_F32 = 4 };
 
 struct GemmProblem {
   const void* A;  RowMap amap;   // rows of A (K contiguous)
@@ -184,7 +185,7 @@ int teacache_parts(int64_t rows);
 hipError_t teacache_ln_distance(const LnArgs& a, void* h_prev, bool measure, double* partials, int dtype, hipStream_t s);
 // velocity head, bf16: v[m][c] = sum_k W[c][k] h[m][k] + bias[c], h = LN(x + resid)(1 + scale) + shift with
 // (shift, scale) = mod[b][0..D), mod[b][D..2D), b = m / rows_per_batch; resid (fp32) may be null. D a
-// multiple of 32 and at most 4096, C a multiple of 64.
+// multiple of 64 and at most 4096, C a multiple of 64.
 struct FinalArgs {
   const void* x; const float* resid; const float* mod; const void* W; const void* bias; float* v;
   int64_t M, rows_per_batch;
@@ -192,7 +193,8 @@ struct FinalArgs {
   float eps;
 };
 hipError_t final_head(const FinalArgs& a, hipStream_t s);
-// residual r (fp32) of the activation x (n elements): mode 0 r = x, 1 r = x - r, 2 x = x + r (fp32 x only)
+bool final_head_in_one_pass(const FinalArgs& a);   // whether it beats LayerNorm + modulate and a GEMM
+// residual r (fp32) of the activation x (n elements): mode 0 r = x, 1 r = x - r, 2 x = x + r
 hipError_t teacache_residual(void* x, float* r, int64_t n, int mode, int dtype, hipStream_t s);
 constexpr int TEACACHE_PARTS = 512;
 hipError_t flow_update(float* x, const float* v, const float* noise, int64_t n,

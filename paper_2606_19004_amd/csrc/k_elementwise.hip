@@ -169,7 +169,7 @@ hipError_t teacache_residual(void* x, float* r, int64_t n, int mode, int dtype, 
   if (dtype == DT_BF16) {
     if (mode == 0) teacache_residual_kernel<u16, 0><<<grid, 256, 0, s>>>((u16*)x, r, n4);
     else if (mode == 1) teacache_residual_kernel<u16, 1><<<grid, 256, 0, s>>>((u16*)x, r, n4);
-    else return hipErrorInvalidValue;   // the bf16 velocity head adds the residual itself
+    else teacache_residual_kernel<u16, 2><<<grid, 256, 0, s>>>((u16*)x, r, n4);
   } else {
     if (mode == 0) teacache_residual_kernel<float, 0><<<grid, 256, 0, s>>>((float*)x, r, n4);
     else if (mode == 1) teacache_residual_kernel<float, 1><<<grid, 256, 0, s>>>((float*)x, r, n4);
@@ -720,9 +720,24 @@ static hipError_t final_head_launch(const FinalArgs& a, hipStream_t s) {
   if (ns <= 2) final_head_ns<2, RES>(a, grid, s);
   else if (ns <= 4) final_head_ns<4, RES>(a, grid, s);
   else if (ns <= 8) final_head_ns<8, RES>(a, grid, s);
+  else if constexpr (!RES) return hipErrorInvalidValue;   // wider rows without a residual take two kernels
   else if (ns <= 12) final_head_ns<12, RES>(a, grid, s);
   else final_head_ns<16, RES>(a, grid, s);
   return hipGetLastError();
+}
+// One pass, or LayerNorm + modulate and a GEMM. Every 64 output features have a workgroup of their own, which reads
+// x and normalises it again, and W_out is read again for every 16 rows; where tiles span samples (tokens not a
+// multiple of 16) each wave reads the modulation from L2. So one pass wins while all of that stays small, and loses
+// to the latency of its own chain at widths past 1024 with few workgroups. Measured (us, two kernels / one pass,
+// modulation GEMV included): 1024 rows x 512 -> 64 features: 13.0 / 11.3; 8192 x 1024 -> 64: 27.8 / 19.8;
+// 16384 x 3072 -> 64: 76.9 / 80.9; 16384 x 1024 -> 64: 34.5 / 31.6, in tiles that span samples 34.9 / 36.5;
+// 8192 x 1024 -> 128: 29.7 / 29.7; 2048 x 2048 -> 192: 25.9 / 31.6; 14820 x 1664 -> 1024: 81 / 540. With a residual to
+// add, one pass also saves a pass over x and wins at 64 features throughout (16384 x 3072: by 42 us).
+bool final_head_in_one_pass(const FinalArgs& a) {
+  const int64_t groups = a.C / 64, wgs = cdiv(a.M, 16) * groups;
+  if (a.resid && groups == 1) return true;
+  if (a.D > 1024 && (a.D > 1792 || wgs < 100)) return false;
+  return wgs * groups * a.D * (a.rows_per_batch % 16 ? 1.5 : 1.0) <= 1.2e6;
 }
 hipError_t final_head(const FinalArgs& a, hipStream_t s) {
   if (a.M == 0) return hipSuccess;

@@ -560,7 +560,8 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
   // and with 256 stores per tile that issue time, not HBM, bounded the epilogue. The paired layout
   // needs 16-byte aligned output rows; otherwise the accumulator layout is stored as it is.
   static_assert(TI % 2 == 0, "the paired store joins blocks 2p and 2p + 1");
-  const bool pairs = (P.N & 7) == 0 && ((uintptr_t)P.C & 15) == 0 &&
+  constexpr bool OUTF32 = EPI == EPI_STORE_F32;   // 16 bytes per block as it is
+  const bool pairs = !OUTF32 && (P.N & 7) == 0 && ((uintptr_t)P.C & 15) == 0 &&
                      ((P.cmap.batch_stride | P.cmap.row_stride | P.cmap.offset) & 7) == 0;
   const int pair_col = 16 * (lkc & 1) + 8 * (lkc >> 1);
   // The residual values of this wave's whole sub-tile (64 registers, free now that the
@@ -680,7 +681,8 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
           v[2] = a1 * t.z - b1 * t.w;
           v[3] = a1 * t.w + b1 * t.z;
         }
-        store4<u16>((u16*)P.C + R.off + n, v);
+        if constexpr (OUTF32) store4<float>((float*)P.C + R.off + n, v);
+        else store4<u16>((u16*)P.C + R.off + n, v);
       }
     }
   };
@@ -753,7 +755,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
   // XALL: every residual load has landed before the first store. The compiler cannot order stores
   // against loads on this counter, so inside the loop it would instead wait for earlier stores.
   if constexpr (XALL) __builtin_amdgcn_s_waitcnt(0);
-  if (pairs) {
+  if (pairs) {   // (never with fp32 output)
     if (staged) store_pairs(std::true_type());
     else store_pairs(std::false_type());
   } else {
@@ -868,7 +870,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_ksplit_kernel(GemmPair pr, int 
     const int m = m0 + 16 * j + r16, n = n0 + 16 * i + 4 * kq;
     if (m < P.M && n < P.N) {
       float v[4] = {c[0], c[1], c[2], c[3]};
-      epilogue4<EPI, u16, u16>(P, row_epi(P, m), n, v);
+      epilogue4<EPI, u16, std::conditional_t<EPI == EPI_STORE_F32, float, u16>>(P, row_epi(P, m), n, v);
     }
   }
 #endif
@@ -1001,7 +1003,7 @@ static Tile pick_tile(const GemmPair& pr, bool plain, const GemmSplitWs& split, 
 
 GemmPlan gemm_plan(const GemmPair& pr, int epi, const GemmSplitWs& split) {
   GemmPlan p{0, 0, 0, 1, 0};
-  const Tile t = pick_tile(pr, epi == EPI_STORE, epi == EPI_RESID ? split : GemmSplitWs{}, &p.splits);
+  const Tile t = pick_tile(pr, epi == EPI_STORE || epi == EPI_STORE_F32, epi == EPI_RESID ? split : GemmSplitWs{}, &p.splits);
   p.tile_m = t == TILE_32 ? 32 : t == TILE_64 || t == TILE_64_RING ? 64 : t == TILE_128 ? 128 : 256;
   p.tile_n = t == TILE_192 ? 192 : p.tile_m;
   p.second_n = t == TILE_256_192 ? 192 : 0;
@@ -1012,7 +1014,7 @@ GemmPlan gemm_plan(const GemmPair& pr, int epi, const GemmSplitWs& split) {
 template <int EPI>
 static hipError_t dispatch_bf16(const GemmPair& pr, const GemmSplitWs& split, hipStream_t s) {
   int splits = 1;
-  constexpr bool PLAIN = EPI == EPI_STORE;
+  constexpr bool PLAIN = EPI == EPI_STORE || EPI == EPI_STORE_F32;
   const Tile tile = pick_tile(pr, PLAIN, split, &splits);
   if constexpr (EPI == EPI_RESID) {
     if (splits > 1 && tile == TILE_192) return launch_bf16<256, 192, 4, 2, EPI, 0, true>(pr, s, splits, split);
@@ -1291,6 +1293,7 @@ hipError_t gemm(const GemmPair& pr, int epi, int dtype, const GemmSplitWs& split
     case EPI_GELU: return dispatch_bf16<EPI_GELU>(pr, GemmSplitWs{}, s);
     case EPI_RESID: return dispatch_bf16<EPI_RESID>(pr, split, s);
     case EPI_QKV: return dispatch_bf16<EPI_QKV>(pr, GemmSplitWs{}, s);
+    case EPI_STORE_F32: return dispatch_bf16<EPI_STORE_F32>(pr, GemmSplitWs{}, s);
   }
   return hipErrorInvalidValue;
 }
