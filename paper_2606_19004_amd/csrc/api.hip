@@ -1202,6 +1202,11 @@ dit_status dit_debug_gemm_plan(const dit_block_config* c, int32_t batch, int32_t
 }
 #endif
 
+#ifdef DITSTEP_DEBUG
+// Debug builds, for tests: whether group_reward_stats_async checks the rewards in its statistics launch. Host only.
+int32_t dit_debug_reward_check_in_launch(int32_t groups, int32_t n) { return reward_check_in_launch(groups, n); }
+#endif
+
 dit_status dit_profile_begin(void) {
   std::lock_guard<std::mutex> g(g_prof.mu);
   for (auto& r : g_prof.recs) {

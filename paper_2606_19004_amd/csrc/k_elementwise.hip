@@ -1220,17 +1220,25 @@ static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
 }
 
+// Whether the statistics launch also checks the rewards, every workgroup all of them, against a second launch (1.4
+// us). A look costs a workgroup 5e-5 us per reward, and all of them together 7e-8 us per group and reward from L2:
+// 1024 groups of 16, apart / in the launch: 6.9 / 6.7 us; 512 of 32: 6.5 / 6.0; 4096 of 4: 10.5 / 14.7; 8192 of
+// 2: 15.8 / 25.0; 256 of 128: 9.4 / 9.7.
+bool reward_check_in_launch(int G, int n) {
+  const int64_t count = (int64_t)G * n;
+  return count <= 16384 && G * count <= (int64_t)1 << 24;
+}
+
 hipError_t reward_stats(const float* r, int G, int n, float adv_eps, int k, float* mean, float* stdv, float* adv,
                         int32_t* order, int32_t* sel, int32_t* status, int32_t bad_code, hipStream_t s) {
   if (G == 0) return hipSuccess;
   const int64_t count = (int64_t)G * n;
   const size_t in = (size_t)count * 4;
-  // One launch where every workgroup can afford to look at all rewards (up to 16 K of them, 64 loads per
-  // thread, against a second launch) and no output lies over the rewards, which a workgroup may still
-  // be checking while another writes.
+  // One launch where that is the faster one and no output lies over the rewards, which a workgroup may still be
+  // checking while another writes.
   const bool shared = overlap(mean, (size_t)G * 4, r, in) || overlap(stdv, (size_t)G * 4, r, in) || overlap(adv, in, r, in) ||
                       overlap(order, in, r, in) || overlap(sel, (size_t)G * k * 4, r, in) || overlap(status, 4, r, in);
-  const bool fused = status && count <= 16384 && !shared;
+  const bool fused = status && !shared && reward_check_in_launch(G, n);
   if (status && !fused) {
     reward_check_kernel<<<1, 1024, 0, s>>>(r, count, bad_code, status);
     hipError_t e = hipGetLastError();

@@ -1,5 +1,5 @@
 """Reward statistics on both sides of each choice: ranks up to 256 seeds and an LDS sort past that, the
-finiteness check inside the statistics launch up to 16384 rewards and as a pass of its own past that or
+finiteness check inside the statistics launch up to 16384 rewards and as a pass of its own past that, for many groups or
 when an output lies over the rewards. Orders are compared exactly with the oracle's stable sort."""
 import numpy as np
 import pytest
@@ -32,7 +32,7 @@ def check(r, out, k):
 
 # 256 | 257 seeds; powers of two and their neighbours; the largest group; 16384 | 16512 rewards in all
 @pytest.mark.parametrize("g,n,k", [(1, 1, 1), (3, 2, 2), (128, 128, 5), (129, 128, 4), (4, 129, 129), (2, 255, 0),
-                                   (2, 256, 7), (3, 257, 8), (70, 200, 9), (2, 511, 511), (2, 512, 3), (2, 513, 2), (4, 4096, 64), (5, 4095, 3)])
+                                   (2, 256, 7), (3, 257, 8), (70, 200, 9), (2100, 8, 3), (5000, 3, 2), (2, 511, 511), (2, 512, 3), (2, 513, 2), (4, 4096, 64), (5, 4095, 3)])
 @pytest.mark.parametrize("ties", [False, True])
 def test_reward_sizes(d, g, n, k, ties):
     rng = np.random.default_rng(g * 10007 + n)

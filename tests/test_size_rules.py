@@ -1,9 +1,9 @@
-"""The bf16 GEMM's choice of tile on the host: each tile is the choice somewhere, and the sizes that the rule was
+"""The library's size rules on the host. The bf16 GEMM's choice of tile: each tile is the choice somewhere, and the sizes that the rule was
 measured at keep theirs."""
 import pytest
 
 from paper_2606_19004_amd import ditstep as d
-from tests.plan_util import gemm_plan
+from tests.plan_util import gemm_plan, reward_check_in_launch
 
 
 def cfg(hidden, n_img, n_txt, mlp=None):
@@ -31,3 +31,11 @@ def test_tiles_by_size(hidden, n, n_txt, b, op, want):
                                              (640, 1000, 576, (64, 64, 0, 1, 0)), (3072, 16384, 64, (256, 256, 0, 1, 0))])
 def test_short_k(hidden, n, k, want):
     assert gemm_plan(cfg(hidden, n, 0), 1, "patch", k) == want
+
+
+# the check of the rewards inside the statistics launch: up to 16384 rewards, and not where many groups each look at
+# all of them
+@pytest.mark.parametrize("groups,n,want", [(1, 1, True), (64, 16, True), (4, 4096, True), (5, 4096, False), (1024, 16, True),
+                                           (512, 32, True), (4096, 1, True), (2048, 8, False), (4096, 4, False), (16384, 1, False)])
+def test_reward_check(groups, n, want):
+    assert reward_check_in_launch(groups, n) == want
