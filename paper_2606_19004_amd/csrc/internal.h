@@ -104,6 +104,9 @@ struct GemmSplitWs {
   size_t bytes;
   int* counters;
   int max_tiles;
+  // set by the launch: bytes of one part's partial tiles, and whether those leave out rows that do not exist
+  uint32_t slot_bytes;
+  bool dense;
 };
 constexpr int GEMM_SPLIT_TILES = 128;   // more tiles than this fill the chip without a split
 hipError_t gemm(const GemmPair& pr, int epi, int dtype, const GemmSplitWs& split, hipStream_t s);

@@ -503,19 +503,85 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     if (tid == 0) bc[0] = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(bc[0]);
-    constexpr uint32_t TILE_BYTES = BM * BN * 4, BLOCK = NW * 64 * 16;
+    // A slot holds the tiles one after the other, each as [i][j][wave] blocks of 1 KB. Where the scratch has no room for
+    // that (split.dense), it holds the rows that exist and no others, so that two partial sums of any number of rows
+    // fit in 8 bytes per row and column: a ragged tile as [i][j][wm][wn] blocks of 16 columns and up to 16 rows.
+    const int vr = split.dense ? min(P.M - m0, BM) : BM;
+    const size_t first = split.dense ? (size_t)(pi == 0 ? 0 : pr.p[0].M) * cdiv(pr.p[0].N, BN) + (size_t)m0 * nt + (size_t)tn * vr
+                                     : (size_t)t * BM;   // row of the slot that this tile starts at, a row being BN sums
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (char*)split.partials + (size_t)t * (splits - 1) * TILE_BYTES, (short)0, (int)((splits - 1) * TILE_BYTES), 0x00020000);
-    auto load = [&](uint32_t slot, int blk) {
-      return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16, slot * TILE_BYTES + blk * BLOCK, DEVICE));
+        (char*)split.partials + first * BN * 4, (short)0, (int)((splits - 2) * split.slot_bytes + vr * BN * 4), 0x00020000);
+    // Block (i, j) of this wave: a scalar offset in the slot, and this lane's place there (past the buffer where the
+    // block has no such row), which are constants in a whole tile.
+    struct Whole {
+      uint32_t v;
+      __device__ __forceinline__ uint32_t soff(int i, int j) const { return (uint32_t)(i * TJ + j) * (NW * 1024u); }
+      __device__ __forceinline__ uint32_t voff(int) const { return v; }
+      __device__ __forceinline__ bool has(int) const { return true; }
     };
-    if (ticket < splits - 1) {
+    struct Ragged {
+      uint32_t istep, b[TJ], v[TJ];
+      __device__ __forceinline__ uint32_t soff(int i, int j) const { return i * istep + b[j]; }
+      __device__ __forceinline__ uint32_t voff(int j) const { return v[j]; }
+      __device__ __forceinline__ bool has(int j) const { return v[j] != 0x80000000u; }
+    };
+    auto ragged = [&]() {
+      const int wm_s = wave_s / WN, wn_s = wave_s % WN;
+      Ragged r;
+      r.istep = (uint32_t)vr * WN * 64u;
+      int before = 0;   // rows in blocks (0, j') of j' < j
+#pragma unroll
+      for (int j = 0; j < TJ; j++) {
+        int rows = 0, mine = 0, lower = before;
+#pragma unroll
+        for (int w = 0; w < WM; w++) {
+          const int q = min(max(vr - w * WTM - MS * j, 0), MS);
+          if (w < wm_s) lower += q;
+          if (w == wm_s) mine = q;
+          rows += q;
+        }
+        r.b[j] = mine > 0 ? (uint32_t)(lower * WN + mine * wn_s) * 64u : 0u;
+        r.v[j] = frow < mine ? (uint32_t)(lkc * mine + frow) * 16u : OOB;
+        before += rows;
+      }
+      return r;
+    };
+    auto store = [&](const auto& at) {
 #pragma unroll
       for (int i = 0; i < TI; i++)
 #pragma unroll
         for (int j = 0; j < TJ; j++)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, tid * 16,
-                                                 ticket * TILE_BYTES + (i * TJ + j) * BLOCK, DEVICE);
+          if (at.has(j))
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, at.voff(j),
+                                                   ticket * split.slot_bytes + at.soff(i, j), DEVICE);
+    };
+    auto add = [&](const auto& at, uint32_t lo) {
+      auto load = [&](uint32_t slot, int i, int j) {   // (zeros for rows past the end)
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, at.voff(j), slot * split.slot_bytes + at.soff(i, j), DEVICE));
+      };
+      if (splits == 2) {
+#pragma unroll
+        for (int i = 0; i < TI; i++) {
+#pragma unroll
+          for (int j = 0; j < TJ; j++) acc[i][j] += load(0, i, j);
+          __builtin_amdgcn_sched_barrier(0);   // a row of blocks in flight: more would not fit the registers
+        }
+      } else {   // (p0 + p1) + p2, whichever of them this one is
+#pragma unroll
+        for (int i = 0; i < TI; i++) {
+#pragma unroll
+          for (int j = 0; j < TJ; j++) {
+            const f32x4 l = load(lo, i, j), h = load(lo ^ 1, i, j);
+            acc[i][j] = part == 2 ? (l + h) + acc[i][j] : (l + acc[i][j]) + h;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    const bool whole = vr == BM;
+    if (ticket < splits - 1) {
+      if (whole) store(Whole{tid * 16u});
+      else store(ragged());
       if (tid == 0) __hip_atomic_store(cnt + 2 + ticket, part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
@@ -530,24 +596,8 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     }
     __syncthreads();
     const uint32_t lo = __builtin_amdgcn_readfirstlane(bc[1]);
-    if (splits == 2) {
-#pragma unroll
-      for (int i = 0; i < TI; i++) {
-#pragma unroll
-        for (int j = 0; j < TJ; j++) acc[i][j] += load(0, i * TJ + j);
-        __builtin_amdgcn_sched_barrier(0);   // a row of blocks in flight: more would not fit the registers
-      }
-    } else {   // (p0 + p1) + p2, whichever of them this one is
-#pragma unroll
-      for (int i = 0; i < TI; i++) {
-#pragma unroll
-        for (int j = 0; j < TJ; j++) {
-          const f32x4 l = load(lo, i * TJ + j), h = load(lo ^ 1, i * TJ + j);
-          acc[i][j] = part == 2 ? (l + h) + acc[i][j] : (l + acc[i][j]) + h;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    if (whole) add(Whole{tid * 16u}, lo);
+    else add(ragged(), lo);
   }
 
   // ---- epilogue: bias, gate vectors and the RoPE table are staged in LDS once per tile ----
@@ -900,6 +950,14 @@ static int count_tiles(const GemmPair& pr, int bm, int bn, int* tiles) {
   return total;
 }
 
+// bytes of one part's partial sums in tiles of bn columns, for the rows that exist
+static size_t split_slot_bytes(const GemmPair& pr, int bn) {
+  size_t b = 0;
+  for (int i = 0; i < pr.nprob; i++)
+    if (pr.p[i].M > 0 && pr.p[i].N > 0) b += (size_t)pr.p[i].M * cdiv(pr.p[i].N, bn) * bn * 4;
+  return b;
+}
+
 template <int T, int EPI>
 static hipError_t launch_ksplit(const GemmPair& pr, hipStream_t s) {
   int tiles[2];
@@ -922,8 +980,11 @@ static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s, int splits = 1,
   static std::atomic<bool> attr_set[64] = {};
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT>), lds, attr_set);
   if (e != hipSuccess) return e;
+  GemmSplitWs ws = split;
+  ws.dense = (size_t)total * (splits - 1) * BM * BN * 4 > split.bytes;
+  ws.slot_bytes = ws.dense ? (uint32_t)split_slot_bytes(pr, BN) : (uint32_t)total * BM * BN * 4;
   gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT><<<8 * cdiv((int64_t)total * splits, 8), WM * WN * 64, lds, s>>>(
-      pr, tiles[0], total, splits, split);
+      pr, tiles[0], total, splits, ws);
   return hipGetLastError();
 }
 
@@ -987,17 +1048,25 @@ static Tile pick_tile(const GemmPair& pr, bool plain, const GemmSplitWs& split, 
   consider(TILE_128, rounds(count_tiles(pr, 128, 128, t), cus) * (0.59 * kt + 7.0));
   consider(TILE_64, rounds(count_tiles(pr, 64, 64, t), cus) * (0.30 * kt + 7.0));
   consider(TILE_32, rounds(count_tiles(pr, 32, 32, t), 2 * cus) * (0.22 * kt + 3.0));
-  // 256-row tiles with K shared out, where their partial tiles fit the scratch: 18 us more (24 for 256 x 256) for
-  // storing and adding those. One seed's MLP down at 512x512, 80 tiles in three parts: 125 us on 128 x 128
-  // tiles, 94 us; two seeds' (120 tiles in two parts of 256 x 256): 200 and 150 us.
-  if (split.bytes > 0)
+  // 256-row tiles with K shared out, where the partial tiles fit the scratch: storing and adding those takes 5 us and
+  // 0.6 us per MB, with 256 x 256 tiles, whose registers hold fewer loads in flight, 10 us in two parts and 18 in
+  // three. Measured with every form forced in turn (us, unsplit / two parts on 256 x 192 / three / two on 256 x 256 /
+  // three; - where it does not fit): hidden 3072, 1024 + 256 rows: 128 / 119 / 101 / 140 / 116, 1024 + 250: 129 / 122 /
+  // 104 / 143 / 121, 2046 + 500: 207 / - / - / 166 / -; hidden 576, 4784 + 2004 rows: 41 / 38 / 43 / 49 / 41; hidden 832,
+  // 6708 + 4: 62 / 63 / - / 69 / -. Within 3% the unsplit form stays: its estimate is high where 128 x 128 tiles leave
+  // half of the CUs idle (hidden 1152, 1130 + 64 rows: 42 / - / 45 / - / -).
+  if (split.bytes > 0) {
+    best *= 0.97;
     for (int sp = 2; sp <= 3; sp++)
       for (int bn = 192; bn <= 256; bn += 64) {
         const int64_t n = count_tiles(pr, 256, bn, t);
-        if (n > split.max_tiles || kt < 8 * sp || (size_t)n * (sp - 1) * 256 * bn * 4 > split.bytes) continue;
-        const double c = rounds(n * sp, cus) * (bn == 192 ? 0.87 : 1.0) * (1.2 * kt / sp + 14.0) + (bn == 192 ? 18.0 : 24.0);
+        const size_t partials = (sp - 1) * split_slot_bytes(pr, bn);
+        if (n > split.max_tiles || kt < 8 * sp || partials > split.bytes) continue;
+        const double c = rounds(n * sp, cus) * (bn == 192 ? 0.87 : 1.0) * (1.2 * kt / sp + 14.0) + 0.6e-6 * partials +
+                         (bn == 192 ? 5.0 : sp == 2 ? 10.0 : 18.0);
         if (c < best) best = c, pick = bn == 192 ? TILE_192 : TILE_256, *splits = sp;
       }
+  }
   return pick;
 }
 

@@ -1,10 +1,13 @@
 """The MLP down-projection with K shared out between workgroups (few rows, long K), against float64, run
 after run the same bits: which workgroup of a tile finishes last differs from run to run, the order of the
-sum does not. Sizes: three parts on 256 x 192 tiles, two on 256 x 256, whole and ragged row tiles, columns
-that do not fill the last tile, both streams, one of them of a single row, and k-tile counts that the
-parts do not share evenly."""
+sum does not. Each size names the tile columns and the number of parts that it has to take: two and three parts
+on 256 x 192 and 256 x 256 tiles, whole and ragged row tiles, columns that do not fill the last tile, both
+streams, one of them of a single row, and k-tile counts that the parts do not share evenly. Parts = 1: near the
+sizes above, but on 128 x 128 tiles."""
 import pytest
 import torch
+
+from tests.plan_util import gemm_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -19,11 +22,18 @@ def lin(x, w, b):
     return x @ w.double().t() + b.double()
 
 
-@pytest.mark.parametrize("hidden,mlp,gh,gw,n_txt,b", [(1024, 16384, 32, 32, 256, 1), (1024, 16384, 25, 40, 217, 1),
-                                                      (1088, 16448, 37, 27, 1, 1), (3072, 12288, 32, 32, 256, 1),
-                                                      (3072, 12288, 32, 32, 256, 2), (3072, 12288, 31, 33, 250, 2),
-                                                      (2048, 8192, 22, 28, 15, 2)])
-def test_mlp_down_split(d, hidden, mlp, gh, gw, n_txt, b):
+@pytest.mark.parametrize("hidden,mlp,gh,gw,n_txt,b,cols,parts",
+                         [(1024, 16384, 32, 32, 256, 1, 256, 3), (1024, 16384, 25, 40, 217, 1, 256, 3),
+                          (1088, 16448, 37, 27, 1, 1, 128, 1), (3072, 12288, 32, 32, 256, 1, 192, 3),
+                          (3072, 12288, 32, 32, 256, 2, 256, 2), (3072, 12288, 31, 33, 250, 2, 256, 2),
+                          (2048, 8192, 22, 28, 15, 2, 128, 1),
+                          # rows that do not fill their tiles do not need the tiles' scratch
+                          (3072, 12288, 31, 33, 250, 1, 192, 3), (3072, 12288, 25, 40, 256, 1, 192, 3),
+                          (1536, 6144, 28, 23, 1, 1, 192, 3), (1152, 6400, 41, 22, 1, 1, 192, 3),
+                          (704, 2240, 42, 40, 250, 3, 192, 2), (1984, 7936, 43, 45, 1, 1, 192, 2),
+                          (640, 2560, 1283, 1, 478, 4, 192, 2), (1216, 4544, 40, 28, 7, 4, 256, 2),
+                          (1024, 4096, 43, 30, 1, 4, 256, 2), (1792, 11648, 24, 23, 1, 1, 256, 3)])
+def test_mlp_down_split(d, hidden, mlp, gh, gw, n_txt, b, cols, parts):
     bf, n = torch.bfloat16, gh * gw
     g = torch.Generator(device="cuda").manual_seed(hidden + mlp + b * n)
 
@@ -31,6 +41,7 @@ def test_mlp_down_split(d, hidden, mlp, gh, gw, n_txt, b):
         return torch.empty(shape, dtype=dtype, device="cuda").normal_(0.0, std, generator=g)
 
     c = d.block_config(hidden, hidden // 64, 64, mlp, n, n_txt, gh, gw)
+    assert gemm_plan(c, b, "mlp_down")[1::2] == (cols, parts)
     w = [{k + s: randn(*(shp if s == "_w" else shp[:1]), std=0.02) for k, shp in
           {"mod": (6 * hidden, hidden), "qkv": (3 * hidden, hidden), "out": (hidden, hidden), "mlp1": (mlp, hidden),
            "mlp2": (hidden, mlp)}.items() for s in ("_w", "_b")} for _ in range(2)]

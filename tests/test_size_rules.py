@@ -18,6 +18,11 @@ def test_one_seed_at_512(op, want):
 @pytest.mark.parametrize("hidden,n,n_txt,b,op,want", [(320, 143, 37, 2, "out", (32, 32, 0, 1, 0)), (3072, 256, 64, 1, "out", (64, 64, 0, 1, 0)),
                                                       (3072, 1024, 256, 16, "qkv", (256, 256, 192, 1, 0)),
                                                       (3072, 1024, 256, 2, "mlp_down", (256, 256, 0, 2, 0)),
+                                                      # as above with rows that do not fill their tiles
+                                                      (3072, 1024, 250, 1, "mlp_down", (256, 192, 0, 3, 0)),
+                                                      (3072, 1023, 256, 1, "mlp_down", (256, 192, 0, 3, 0)),
+                                                      (3072, 640, 64, 1, "mlp_down", (256, 192, 0, 3, 0)),
+                                                      (576, 1196, 501, 4, "mlp_down", (256, 192, 0, 2, 0)),
                                                       (3072, 1024, 256, 8, "mlp_down", (256, 256, 0, 1, 0))])
 def test_tiles_by_size(hidden, n, n_txt, b, op, want):
     assert gemm_plan(cfg(hidden, n, n_txt), b, op) == want
