@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_bf16(AttnArgs a) {
 // one tile ahead into two LDS buffers. Scores are computed transposed, S^T = K Q^T, so that a lane owns
 // one query (lane % 16) and keys 16 kb + 4 (lane / 16) + r; P then is operand B of O^T = V^T P^T as it
 // sits in the score registers: MFMA r of a key block sums over keys 4 g + r, g = lane / 16. Online
-// softmax in the exp2 domain, one rescale per tile. LDS rows are padded by 4 floats, which spreads
+// softmax, one rescale per tile. LDS rows are padded by 4 floats, which spreads
 // both the 16-byte K reads (16 rows) and the 4-byte V reads (4 rows, 4 apart) over the banks.
 // Bound by the fp32 matrix rate; 4 B H S^2 d flops.
 // ---------------------------------------------------------------------------
@@ -416,7 +416,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
   f32x4 o[NDB];
 #pragma unroll
   for (int i = 0; i < NDB; i++) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  constexpr float LOG2E = 1.4426950408889634f;
+  constexpr float LOG2E = 1.4426950408889634f;   // applied to differences: a score times it may overflow
   float m_run = -INFINITY, l_run = 0.f;
   const int nt = cdiv(S, KB);
   fetch(0);
@@ -458,14 +458,13 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
     for (int kb = 0; kb < NKB; kb++)
 #pragma unroll
       for (int r = 0; r < 4; r++) {
-        s[kb][r] *= LOG2E;
         if (kt * KB + 16 * kb + 4 * g + r >= S) s[kb][r] = -INFINITY;
         mx = fmaxf(mx, s[kb][r]);
       }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     const float m_new = fmaxf(m_run, mx);
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * LOG2E);
     m_run = m_new;
     l_run *= alpha;
 #pragma unroll
@@ -477,7 +476,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_f32(AttnArgs a) {
     for (int kb = 0; kb < NKB; kb++)
 #pragma unroll
       for (int r = 0; r < 4; r++) {
-        s[kb][r] = __builtin_amdgcn_exp2f(s[kb][r] - m_new);
+        s[kb][r] = __builtin_amdgcn_exp2f((s[kb][r] - m_new) * LOG2E);
         psum += s[kb][r];
       }
     l_run += psum;

@@ -95,6 +95,20 @@ def test_attention_f32_scale_of_any_size(d, hd, size, scale):
     assert (o.double() - want).abs().max() <= (1e-5 if size > 1 else 4.6e-3) * v.abs().max()
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+def test_attention_f32_scores_near_the_largest_float(d, hd):
+    """Scores up to 3e38, which no factor above 1.13 leaves finite: the largest takes all, exactly."""
+    b, h, seq = 1, 2, 37
+    g = torch.Generator(device="cuda").manual_seed(hd)
+    q, k = (torch.zeros(b, seq, h, hd, device="cuda") for _ in range(2))
+    v = torch.randn(b, seq, h, hd, generator=g, device="cuda")
+    q[..., 0] = 1e19
+    k[..., 0] = (torch.randperm(seq, generator=g, device="cuda").float() * (6e19 / 36) - 3e19)[None, :, None]
+    o = torch.zeros(b, seq, h, hd, device="cuda")
+    d.joint_attention(q, k, v, o, b, h, seq, hd, (seq * h * hd, h * hd, hd), (seq * h * hd, h * hd, hd), scale=1.0, dtype="f32")
+    assert torch.equal(o, v[:, k[0, :, 0, 0].argmax()][:, None].expand_as(o))
+
+
 def test_gemm_f32_rows_past_2_gib_of_a_tile(d):
     """An MLP so wide that the 32 rows of a down-projection tile span 2 GiB: everything is zero but the last element
     of the last row, GELU(8) = 8 exactly in fp32."""
