@@ -101,12 +101,9 @@ enum Dtype { DT_F32 = 0, DT_BF16 = 1 };
 // tiles and counters that are zero when the launch starts, 4 per tile. bytes = 0: none.
 struct GemmSplitWs {
   float* partials;
-  size_t bytes;
+  size_t bytes;   // (in the kernel, where tiles are not stored whole: of one part's rows)
   int* counters;
   int max_tiles;
-  // set by the launch: bytes of one part's partial tiles, and whether those leave out rows that do not exist
-  uint32_t slot_bytes;
-  bool dense;
 };
 constexpr int GEMM_SPLIT_TILES = 128;   // more tiles than this fill the chip without a split
 hipError_t gemm(const GemmPair& pr, int epi, int dtype, const GemmSplitWs& split, hipStream_t s);

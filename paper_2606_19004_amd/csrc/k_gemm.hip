@@ -223,7 +223,7 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 // to finish leave their accumulators in `split.partials`; the last adds them in the order of the parts
 // (so the result does not depend on which was last) and runs the epilogue. It waits only for workgroups
 // that have taken their ticket, that is, are storing, and wait for nothing themselves.
-template <int BM, int BN, int WM, int WN, int EPI, int RING = 0, bool SPLIT = false>
+template <int BM, int BN, int WM, int WN, int EPI, int RING = 0, bool SPLIT = false, bool DENSE = false>
 __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, int tiles0, int total_tiles, int splits,
                                                                  GemmSplitWs split) {
   constexpr int MS = 16, KS = 32;                      // MFMA block and k depth
@@ -503,14 +503,16 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
     if (tid == 0) bc[0] = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(bc[0]);
-    // A slot holds the tiles one after the other, each as [i][j][wave] blocks of 1 KB. Where the scratch has no room for
-    // that (split.dense), it holds the rows that exist and no others, so that two partial sums of any number of rows
-    // fit in 8 bytes per row and column: a ragged tile as [i][j][wm][wn] blocks of 16 columns and up to 16 rows.
-    const int vr = split.dense ? min(P.M - m0, BM) : BM;
-    const size_t first = split.dense ? (size_t)(pi == 0 ? 0 : pr.p[0].M) * cdiv(pr.p[0].N, BN) + (size_t)m0 * nt + (size_t)tn * vr
-                                     : (size_t)t * BM;   // row of the slot that this tile starts at, a row being BN sums
+    // A tile's slots lie one after the other, each as [i][j][wave] blocks of 1 KB. Where the scratch has no room for
+    // that, every slot holds, for all tiles, the rows that exist and no others (DENSE), so that two partial sums of any
+    // number of rows fit in 8 bytes per row and column: a ragged tile as [i][j][wm][wn] blocks of 16 columns and up to
+    // 16 rows.
+    const int vr = DENSE ? min(P.M - m0, BM) : BM;
+    const size_t first = DENSE ? (size_t)(pi == 0 ? 0 : pr.p[0].M) * cdiv(pr.p[0].N, BN) + (size_t)m0 * nt + (size_t)tn * vr
+                               : (size_t)t * (splits - 1) * BM;   // row of BN sums that this tile starts at
+    const uint32_t slot_bytes = DENSE ? (uint32_t)split.bytes : BM * BN * 4;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (char*)split.partials + first * BN * 4, (short)0, (int)((splits - 2) * split.slot_bytes + vr * BN * 4), 0x00020000);
+        (char*)split.partials + first * BN * 4, (short)0, (int)((splits - 2) * slot_bytes + vr * BN * 4), 0x00020000);
     // Block (i, j) of this wave: a scalar offset in the slot, and this lane's place there (past the buffer where the
     // block has no such row), which are constants in a whole tile.
     struct Whole {
@@ -553,11 +555,11 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
         for (int j = 0; j < TJ; j++)
           if (at.has(j))
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, at.voff(j),
-                                                   ticket * split.slot_bytes + at.soff(i, j), DEVICE);
+                                                   ticket * slot_bytes + at.soff(i, j), DEVICE);
     };
     auto add = [&](const auto& at, uint32_t lo) {
       auto load = [&](uint32_t slot, int i, int j) {   // (zeros for rows past the end)
-        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, at.voff(j), slot * split.slot_bytes + at.soff(i, j), DEVICE));
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, at.voff(j), slot * slot_bytes + at.soff(i, j), DEVICE));
       };
       if (splits == 2) {
 #pragma unroll
@@ -578,7 +580,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
         }
       }
     };
-    const bool whole = vr == BM;
+    const bool whole = !DENSE || vr == BM;
     if (ticket < splits - 1) {
       if (whole) store(Whole{tid * 16u});
       else store(ragged());
@@ -971,19 +973,21 @@ static hipError_t launch_ksplit(const GemmPair& pr, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int RING = 0, bool SPLIT = false>
+template <int BM, int BN, int WM, int WN, int EPI, int RING = 0, bool SPLIT = false, bool DENSE = false>
 static hipError_t launch_bf16(const GemmPair& pr, hipStream_t s, int splits = 1, const GemmSplitWs& split = GemmSplitWs{}) {
   int tiles[2];
   const int total = count_tiles(pr, BM, BN, tiles);
   if (total == 0) return hipSuccess;
+  GemmSplitWs ws = split;
+  if constexpr (SPLIT && !DENSE)
+    if ((size_t)total * (splits - 1) * BM * BN * 4 > split.bytes)
+      return launch_bf16<BM, BN, WM, WN, EPI, RING, true, true>(pr, s, splits, split);
+  if constexpr (DENSE) ws.bytes = split_slot_bytes(pr, BN);
   constexpr size_t lds = RING == 0 ? (size_t)(2 * BN + 3 * BM) * 64 * 2 : RING * (size_t)(BM + BN) * 64 * 2;
   static std::atomic<bool> attr_set[64] = {};
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT>), lds, attr_set);
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT, DENSE>), lds, attr_set);
   if (e != hipSuccess) return e;
-  GemmSplitWs ws = split;
-  ws.dense = (size_t)total * (splits - 1) * BM * BN * 4 > split.bytes;
-  ws.slot_bytes = ws.dense ? (uint32_t)split_slot_bytes(pr, BN) : (uint32_t)total * BM * BN * 4;
-  gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT><<<8 * cdiv((int64_t)total * splits, 8), WM * WN * 64, lds, s>>>(
+  gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT, DENSE><<<8 * cdiv((int64_t)total * splits, 8), WM * WN * 64, lds, s>>>(
       pr, tiles[0], total, splits, ws);
   return hipGetLastError();
 }
