@@ -98,7 +98,7 @@ CONFIGS = {
     "small_bf16": Shape("small_bf16", 256, 2, 128, 7, 9, 21, 3),
     "small_bf16_d64": Shape("small_bf16_d64", 320, 5, 64, 11, 13, 37, 2),
     # MLP half with a long down-projection (K = 4*2176 = 8704) and ragged rows and columns
-    # (63 + 21 tokens x 3 seeds; 2176 output features): the three-stage GEMM path with partial tiles
+    # (63 + 21 tokens x 3 seeds; 2176 output features): partial tiles of few rows, whose waves share K
     "mlp_long_k": Shape("mlp_long_k", 2176, 17, 128, 7, 9, 21, 3, rope=False),
     # MLP halves with short up projections (K = 128 and 192: two and three 64-deep k-tiles) over
     # 16 x (64x64 + 100) rows, enough 256 x 256 tiles to take the large-tile GEMM path, with a

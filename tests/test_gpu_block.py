@@ -116,7 +116,7 @@ def test_block_mlp_half(d):
 
 
 def test_block_mlp_long_k_ragged(d):
-    """MLP half whose down projection has K >= 8192 (three A stages in LDS) on partial tiles: 189 image
+    """MLP half whose down projection has K >= 8192 on partial tiles (64 x 64 ones whose waves share K): 189 image
     and 63 text rows, 2176 output columns; every row is compared."""
     cfg = si.CONFIGS["mlp_long_k"]
     assert cfg.mlp_hidden >= 8192 and cfg.hidden % 256 != 0

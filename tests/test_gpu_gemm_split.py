@@ -3,7 +3,7 @@ after run the same bits: which workgroup of a tile finishes last differs from ru
 sum does not. Each size names the tile columns and the number of parts that it has to take: two and three parts
 on 256 x 192 and 256 x 256 tiles, whole and ragged row tiles, columns that do not fill the last tile, both
 streams, one of them of a single row, and k-tile counts that the parts do not share evenly. Parts = 1: near the
-sizes above, but on 128 x 128 tiles."""
+sizes above, but unshared, on 128 x 128 tiles or, with more rows, on the three-stage 256-row ones."""
 import pytest
 import torch
 
@@ -31,8 +31,9 @@ def lin(x, w, b):
                           (3072, 12288, 31, 33, 250, 1, 192, 3), (3072, 12288, 25, 40, 256, 1, 192, 3),
                           (1536, 6144, 28, 23, 1, 1, 192, 3), (1152, 6400, 41, 22, 1, 1, 192, 3),
                           (704, 2240, 42, 40, 250, 3, 192, 2), (1984, 7936, 43, 45, 1, 1, 192, 2),
-                          (640, 2560, 1283, 1, 478, 4, 192, 2), (1216, 4544, 40, 28, 7, 4, 256, 2),
-                          (1024, 4096, 43, 30, 1, 4, 256, 2), (1792, 11648, 24, 23, 1, 1, 256, 3)])
+                          (640, 2560, 1283, 1, 478, 4, 192, 2), (1088, 8704, 39, 41, 63, 6, 192, 1),
+                          (1216, 4544, 40, 28, 7, 4, 256, 2),
+                          (1024, 4096, 43, 30, 1, 4, 256, 2), (1792, 11648, 24, 23, 1, 1, 256, 3), (1088, 8704, 39, 41, 21, 8, 256, 1)])
 def test_mlp_down_split(d, hidden, mlp, gh, gw, n_txt, b, cols, parts):
     bf, n = torch.bfloat16, gh * gw
     g = torch.Generator(device="cuda").manual_seed(hidden + mlp + b * n)

@@ -1,11 +1,11 @@
 """Every bf16 GEMM tile shape at its edges, with integer operands whose results are exact in any order.
 
-Through the patch embedding (plain GEMM): rows and features around the 32, 64 and 128 tile edges and one
-to many 64-deep k-tiles, so that each of the four waves of a split-K workgroup gets none, one or several
-slices and the 128 x 128 ring is shorter than, as long as and longer than its five stages. Which tile a
-shape takes is the library's choice; the sizes below lie in the ranges of all of them (few rows: 32 x 32;
-hundreds: 64 x 64 and 128 x 128; thousands: 256-row tiles). A block then runs every epilogue on the
-small tiles, two streams in one launch, against the oracle."""
+Through the patch embedding (plain GEMM): rows and features around the tile edges and one to many 64-deep k-tiles.
+Which tile a size takes is the library's choice, so test_tile_exact names it for every size and asks the library:
+32 x 32 and 64 x 64 tiles whose four waves share K (none, one or several slices each, evenly or not; 64 x 64 is the
+choice from nine k-tiles on), the ring of two stages on 64 x 64 tiles, the ring of five on 128 x 128 (again from
+nine), and the three-stage 256 x 192 and 256 x 256 tiles from one k-tile on. A block then runs every epilogue on
+the small tiles, two streams in one launch, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -57,6 +57,24 @@ def test_larger_tiles_exact(d, b, n, hidden, k):
     patch(d, b, n, hidden, k)
 
 
+T32, T64, RING64, T128, T192, T256 = ((32, 32, 0, 1, 0), (64, 64, 0, 1, 0), (64, 64, 0, 1, 2), (128, 128, 0, 1, 5),
+                                      (256, 192, 0, 1, 0), (256, 256, 0, 1, 0))
+
+
+@pytest.mark.parametrize("tile,rows,hidden,ks", [(T32, 1, 64, (192, 256, 320, 576)), (T32, 33, 128, (192, 384, 1280)),
+                                                 (T32, 127, 448, (256, 320, 576)), (RING64, 65, 320, (64, 128)),
+                                                 (RING64, 161, 3072, (192, 512)), (T64, 200, 3072, (576, 640, 704, 1024)),
+                                                 (T64, 2000, 320, (576, 640, 704, 1280)), (T64, 3000, 192, (576, 832)),
+                                                 (T128, 700, 1536, (576, 640, 704, 1280)), (T128, 1025, 3008, (576, 1024)),
+                                                 (T192, 16383, 448, (64, 128, 192, 256, 320, 576)), (T192, 4000, 2048, (64, 384)),
+                                                 (T256, 24001, 448, (64, 128, 192, 256, 320, 576)), (T256, 16384, 3072, (64, 192))])
+def test_tile_exact(d, tile, rows, hidden, ks):
+    c = d.block_config(hidden, hidden // 64, 64, 4 * hidden, rows, 0, 1, rows)
+    for k in ks:
+        assert gemm_plan(c, 1, "patch", k) == tile
+        patch(d, 1, rows, hidden, k)
+
+
 # 64 x 64 tiles in a ring of two stages: one to many k-tiles, whole and ragged rows, one tile to six per compute unit
 @pytest.mark.parametrize("rows,hidden,k", [(1, 64, 64), (65, 128, 128), (2177, 320, 64), (1000, 640, 192), (8193, 64, 256),
                                            (700, 3072, 320), (1999, 3072, 512), (24575, 256, 448)])
@@ -77,7 +95,7 @@ def test_patch_bias_at_any_element_alignment(d):
             patch(d, 1, rows, hidden, k, bias_skew=skew)
 
 
-# every epilogue with both streams in one launch: 32 x 32, 64 x 64 and 128 x 128 tiles by size
+# every epilogue with both streams in one launch, on 32 x 32 to 256 x 192 tiles by size
 @pytest.mark.parametrize("hidden,hd,gh,gw,n_txt,b", [(128, 64, 3, 11, 1, 2), (576, 64, 13, 9, 45, 2), (1024, 128, 19, 21, 90, 2),
                                                      (1024, 64, 9, 7, 130, 1)])
 def test_block_small_tiles(d, hidden, hd, gh, gw, n_txt, b):
