@@ -195,9 +195,10 @@ def kernel_summary(run_dir, bench_json):
     lines += ["", f"bench.py (no profiler): {b['value']} ms per step; dominant kernel `{r['kernel']}` averaged "
               f"{r['avg_launch_us']} us per launch with HIP events ({r['achieved']} TFLOP/s, "
               f"{100 * r['frac']:.1f}% of {r['peak']}).",
-              "EPI codes in `gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT>`: 0 plain store, 1 GELU (MLP up), "
+              "EPI codes in `gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT, DENSE>`: 0 plain store, 1 GELU (MLP up), "
               "2 gated residual (output projection, MLP down), 3 QKV with 2D RoPE; RING is the number of LDS stages of "
-              "both operands (0: three of the activations, two of the weights); SPLIT marks K shared out between workgroups."]
+              "both operands (0: three of the activations, two of the weights); SPLIT marks K shared out between workgroups "
+              "(DENSE: with partial tiles of existing rows only)."]
     with open(os.path.join(ROOT, KERNEL_MD), "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines))
@@ -503,8 +504,8 @@ def next_rows(torch, d, cfg, x):
         torch.cuda.synchronize()
         run_ms = (time.perf_counter() - t0) / 3 * 1e3
         out["teacache"] = {"skipped_step_ms": round(skip_ms, 3), "computed_step_ms": round(run_ms, 3),
-                           "note": "wall clock per gated step (one host sync each); the computed step also runs "
-                                   "block 0's modulation and LN once more for the distance"}
+                           "note": "wall clock per gated step (one host wait each); the computed step also runs two of "
+                                   "the six rows of block 0's image modulation and its LN once more for the distance"}
     pl = pn.Planner([4, 8, 16, 24, 32], [12, 14, 16, 18, 20], beta=0.5, window=10, prompts=32)
     rng = np.random.default_rng(0)
     fb = rng.uniform(0.8, 2.0, 2000).tolist()

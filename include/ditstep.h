@@ -15,10 +15,15 @@
  *     unless stated otherwise; the library never frees them and performs no
  *     device allocation on the hot path. Scratch memory comes from a
  *     caller-provided workspace whose size the *_workspace_bytes() calls give.
+ *     On the host, dit_denoise_step_teacache keeps 8 KB of pinned memory per
+ *     calling thread (allocated by the thread's first step that measures a
+ *     distance, given back when the thread ends) and creates and destroys one
+ *     event per such step.
  *   - Every call is asynchronous on `stream` (a hipStream_t; NULL = the null
  *     stream), except group_reward_stats, which synchronises `stream` once
  *     to check its small input for NaN (group_reward_stats_async checks on the
- *     device instead).
+ *     device instead), and dit_denoise_step_teacache, which waits for the
+ *     distance it decides by.
  *   - Arguments are validated before any launch; on any error nothing is
  *     written, the status says why and dit_last_error_message() (per host
  *     thread) gives detail. Launch failures return DIT_ERR_HIP.
@@ -29,10 +34,13 @@
  *     velocity, noise and rewards are always fp32.
  *   - Thread safety: no mutable global state besides the per-thread error
  *     text, per-device caches filled once (atomics: the device's compute
- *     unit count and the kernels' LDS limits) and the fixed scratch array of
- *     dit_timestep_embed_noalloc (one per GPU; overlapping calls of that entry
- *     point on one GPU race); calls on different streams with disjoint
- *     buffers may overlap, also on their first call.
+ *     unit count and the kernels' LDS limits), the pinned memory of a thread
+ *     above and the fixed scratch array of dit_timestep_embed_noalloc (one per
+ *     GPU; overlapping calls of that entry point on one GPU race); calls on
+ *     different streams with disjoint buffers may overlap, also on their first
+ *     call. A thread's end frees its pinned memory in the relaxed capture mode,
+ *     which leaves another thread's graph capture alone; a thread's first
+ *     measuring step allocates in the thread's own mode.
  */
 #ifndef DITSTEP_H
 #define DITSTEP_H
@@ -223,10 +231,11 @@ dit_status group_reward_stats(const float* rewards, int32_t groups, int32_t n, f
                               int32_t* order, int32_t* selected, dit_stream stream);
 
 /* group_reward_stats without the host synchronisation, for callers that keep the stream
- * asynchronous (a step loop, HIP graph capture): the finiteness check runs on the device. A
- * one-workgroup pass over the G x n rewards writes *status (device int32) = DIT_OK, or
- * DIT_ERR_NAN when any reward is NaN or infinite; the statistics kernel then writes its outputs
- * only when *status is DIT_OK, so on bad input nothing but *status is written. The caller reads
+ * asynchronous (a step loop, HIP graph capture): the finiteness check runs on the device, in the
+ * statistics launch for few rewards and groups (when no output overlaps the rewards), else in a
+ * pass of its own before it. It writes *status (device int32) = DIT_OK, or DIT_ERR_NAN when any
+ * reward is NaN or infinite; the statistics are written only when that is DIT_OK, so on bad input
+ * nothing but *status is written. The caller reads
  * *status after synchronising. Same outputs, bit for bit, as group_reward_stats on finite input.
  * Arguments are validated on the host as there (DIT_ERR_INVALID_ARG, also for status NULL);
  * groups == 0 writes nothing, not even *status. */
@@ -321,8 +330,9 @@ size_t dit_teacache_cache_bytes(const dit_block_config* cfg, int32_t batch);
  * n_blocks >= 1). Computes h, updates the cache's h_prev, and either runs the blocks (then
  * stores the residual x_out - x_in) or adds the stored residual to the patch-embedded input.
  * *ran_blocks (may be NULL) receives the decision and *rel (may be NULL) the distance (NaN on
- * a step without a previous input). The decision needs the distance on the host, so the call
- * synchronises `stream` once. DIT_ERR_WORKSPACE if cache_bytes is too small. */
+ * a step without a previous input). The decision needs the distance on the host, so a step with a
+ * previous input waits for that point of `stream` (work of the step queued behind it goes on; where
+ * no event can be had, for all of `stream`). DIT_ERR_WORKSPACE if cache_bytes is too small. */
 dit_status dit_denoise_step_teacache(const dit_block_config* cfg, const dit_step_weights* sw,
                                      const dit_block_weights* blocks, int32_t n_blocks, int32_t batch,
                                      int32_t latent_dim, float t, float t_next, float noise_level,

@@ -99,6 +99,7 @@ dit_status check_ws(void* ws, size_t have, size_t need) {
 }
 
 // offsets into the block workspace
+// (silu: SiLU(temb) of the fp32 GEMVs that do not fold it; with bf16, counters of a GEMM)
 struct BlockWs {
   size_t mod, silu, xs, rope, h, qkv, u, total;
 };
@@ -996,7 +997,7 @@ dit_status dit_denoise_step(const dit_block_config* c, const dit_step_weights* s
 // ---- TeaCache gate ----
 namespace {
 struct TeaCacheLayout {
-  size_t hprev, resid, parts, sums, total;
+  size_t hprev, resid, parts, total;
 };
 TeaCacheLayout teacache_layout(const dit_block_config* c, int64_t B) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -1005,8 +1006,7 @@ TeaCacheLayout teacache_layout(const dit_block_config* c, int64_t B) {
   L.hprev = 0;
   L.resid = up(n * esize(c->dtype));
   L.parts = L.resid + up(n * 4);
-  L.sums = L.parts + up(2 * sizeof(double) * TEACACHE_PARTS);
-  L.total = L.sums + 256;
+  L.total = L.parts + up(2 * sizeof(double) * TEACACHE_PARTS);
   return L;
 }
 

@@ -492,11 +492,11 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
   }
 
   if constexpr (SPLIT) {
-    // The exchange uses stores and loads of device scope (past this XCD's L2, the caches of different XCDs
+    // The exchange uses stores and loads of system scope (past this XCD's L2, the caches of different XCDs
     // not being coherent), each completed before the count that announces it. Ordinary accesses with
     // fences cost far more: a fence writes back, or drops, the whole L2 under every other workgroup
     // (one-seed MLP down 177 us with them).
-    constexpr int DEVICE = 17;           // sc0 | sc1
+    constexpr int SYSTEM = 17;           // cache policy bits sc0 | sc1
     int* cnt = split.counters + 4 * t;   // tickets taken, partial tiles stored, parts in slots 0 and 1
     __syncthreads();                     // every wave is done with the operand tiles
     int* bc = (int*)smem;
@@ -555,11 +555,11 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_kernel(GemmPair pr, in
         for (int j = 0; j < TJ; j++)
           if (at.has(j))
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, at.voff(j),
-                                                   ticket * slot_bytes + at.soff(i, j), DEVICE);
+                                                   ticket * slot_bytes + at.soff(i, j), SYSTEM);
     };
     auto add = [&](const auto& at, uint32_t lo) {
       auto load = [&](uint32_t slot, int i, int j) {   // (zeros for rows past the end)
-        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, at.voff(j), slot * slot_bytes + at.soff(i, j), DEVICE));
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, at.voff(j), slot * slot_bytes + at.soff(i, j), SYSTEM));
       };
       if (splits == 2) {
 #pragma unroll
@@ -1132,8 +1132,9 @@ __device__ __forceinline__ void mfma_k16(float4 w, float4 a, f32x4& c) {
 }
 
 // 64 x 64 tile, 4 waves of 32 x 32, 32-deep k-tiles in a ring of three LDS stages (48 KB, three
-// workgroups per CU), one barrier per k-tile. Bound by the fp32 matrix rate (256 flop per clock and
-// CU): a k-tile takes 1024 cycles of it and moves 16 KB.
+// workgroups per CU), one barrier per k-tile, which takes 1024 cycles of the fp32 matrix rate (256 flop per clock and
+// CU) and moves 16 KB. 83-101 TFLOP/s in a block of hidden 768 and 2176 rows (a large library product: 137), whose
+// 408 tiles of the output projection and MLP down fill the second round of 256 CUs by 60%.
 template <int EPI>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmPair pr, int tiles0, int total_tiles) {
   constexpr int BM = 64, BN = 64, ST = 3, STAGE = (BM + BN) * 128;
