@@ -196,7 +196,7 @@ def kernel_summary(run_dir, bench_json):
               f"{r['avg_launch_us']} us per launch with HIP events ({r['achieved']} TFLOP/s, "
               f"{100 * r['frac']:.1f}% of {r['peak']}).",
               "EPI codes in `gemm_bf16_kernel<BM, BN, WM, WN, EPI, RING, SPLIT, DENSE>`: 0 plain store, 1 GELU (MLP up), "
-              "2 gated residual (output projection, MLP down), 3 QKV with 2D RoPE; RING is the number of LDS stages of "
+              "2 gated residual (output projection, MLP down), 3 QKV with 2D RoPE, 4 plain fp32 store (velocity head); RING is the number of LDS stages of "
               "both operands (0: three of the activations, two of the weights); SPLIT marks K shared out between workgroups "
               "(DENSE: with partial tiles of existing rows only)."]
     with open(os.path.join(ROOT, KERNEL_MD), "w") as f:
