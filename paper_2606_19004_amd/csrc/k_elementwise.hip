@@ -710,8 +710,13 @@ __global__ void __launch_bounds__(512, 4) final_head_kernel(FinalArgs a) {
 template <int NS, bool RES>
 static void final_head_ns(const FinalArgs& a, dim3 grid, hipStream_t s) {
   const bool one = a.rows_per_batch % 16 == 0;
-  if (a.D == 256 * NS && one) final_head_kernel<NS, RES, true, true><<<grid, 512, 0, s>>>(a);
-  else if (one) final_head_kernel<NS, RES, false, true><<<grid, 512, 0, s>>>(a);
+  if constexpr (RES || NS < 8) {   // (rows of 2048 without a residual take two kernels)
+    if (a.D == 256 * NS && one) {
+      final_head_kernel<NS, RES, true, true><<<grid, 512, 0, s>>>(a);
+      return;
+    }
+  }
+  if (one) final_head_kernel<NS, RES, false, true><<<grid, 512, 0, s>>>(a);
   else final_head_kernel<NS, RES, false, false><<<grid, 512, 0, s>>>(a);
 }
 template <bool RES>
@@ -721,7 +726,7 @@ static hipError_t final_head_launch(const FinalArgs& a, hipStream_t s) {
   if (ns <= 2) final_head_ns<2, RES>(a, grid, s);
   else if (ns <= 4) final_head_ns<4, RES>(a, grid, s);
   else if (ns <= 8) final_head_ns<8, RES>(a, grid, s);
-  else if constexpr (!RES) return hipErrorInvalidValue;   // wider rows without a residual take two kernels
+  else if constexpr (!RES) return hipErrorInvalidValue;   // wider rows without a residual take two kernels too
   else if (ns <= 12) final_head_ns<12, RES>(a, grid, s);
   else final_head_ns<16, RES>(a, grid, s);
   return hipGetLastError();
